@@ -19,6 +19,9 @@ namespace hs {
 hipError_t launch_pack(int kind, int kmajor, const PackArgs &a, hipStream_t st);
 hipError_t launch_pack_mn(int kind, const PackArgs &a, hipStream_t st);
 hipError_t launch_mm(int fam, int form, const MainArgs &a, hipStream_t st);
+hipError_t launch_wave(int fam, int form, int t, const WaveArgs &a, hipStream_t st);
+int wave_chunk_bytes(int fam);
+int wave_tile(int fam, int t);
 hipError_t launch_backshift(int f64, const void *W, int64_t plane, int K, int64_t M, int64_t N,
                             void *Cout, int64_t ldc, hipStream_t st);
 hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t ldc, hipStream_t st);
@@ -90,11 +93,18 @@ struct Plan {
     int64_t tiles_k, tiles_ra, tiles_rb;
     int nsplit, split_stages;         // workgroups per output tile, stages each
     size_t off_part;                  // their partial planes (nsplit > 1)
+    int wave;                         // MFMA tiles per side of the wave kernel's tile; 0: mm_kernel
+    int kg;                           // its waves per workgroup
 };
 
 // Compute units of the MI355X: a launch with fewer output tiles than this
 // leaves CUs idle unless each tile's stage sequence is split.
 const int64_t kCUs = 256;
+
+// Bytes of a packed operand.
+int64_t operand_bytes(const OperandGeom &g) {
+    return g.striped == OPG_CLASSES ? g.K * g.class_bytes : g.n_groups * g.group_bytes;
+}
 
 // Threads of the pack kernel: one per 16-byte unit; a K-major source is
 // walked in 8 x 8 (row, unit) blocks, so both counts round up to 8.
@@ -102,6 +112,116 @@ int64_t pack_units(const OperandGeom &g, int kmajor) {
     const int64_t nu = g.nch * (g.chunk_bytes / 16);
     if (kmajor) return g.n_groups * g.p * ((nu + 7) / 8 * 8) * ((g.grp_rows + 7) / 8 * 8);
     return g.n_groups * g.p * nu * g.grp_rows;
+}
+
+// Workspace layout: the two packed operands (no partial planes: the collector
+// keeps every partial in registers), the FP8 tile exponents or the two-piece
+// FP16 row amaxes, and the split planes.
+void layout_workspace(Plan *P) {
+    size_t off = 0;
+    P->off_a = off; off = align_up(off + (size_t)operand_bytes(P->ga));
+    P->off_b = off; off = align_up(off + (size_t)operand_bytes(P->gb));
+    P->tiles_k = ceil_div(P->Kd, FP8_TILE);
+    P->tiles_ra = ceil_div(P->M, FP8_TILE);
+    P->tiles_rb = ceil_div(P->N, FP8_TILE);
+    P->off_ea = P->off_eb = off;
+    if (P->f.fam == FAM_FP8) {
+        P->off_ea = off; off = align_up(off + (size_t)P->tiles_ra * P->tiles_k * 2 * sizeof(int32_t));
+        P->off_eb = off; off = align_up(off + (size_t)P->tiles_rb * P->tiles_k * 2 * sizeof(int32_t));
+    }
+    if (P->f.pack == PK_SPLIT2F16) {
+        P->off_ea = off; off = align_up(off + (size_t)P->M * sizeof(uint32_t));
+        P->off_eb = off; off = align_up(off + (size_t)P->N * sizeof(uint32_t));
+    }
+    P->off_part = off;
+    if (P->nsplit > 1) off = align_up(off + (size_t)P->nsplit * P->M * P->N * (P->f.out_f64 ? 8 : 4));
+    P->total = (P->M == 0 || P->N == 0 || P->Kd == 0) ? 0 : off;
+}
+
+// Whether the wave kernel takes the product that *P plans for mm_kernel, and
+// with which tile.  mm_kernel needs its 256 x 256 tiles to fill the chip: a
+// launch of `tiles` of them keeps u = tiles / (256 rounds) of the CUs busy.
+// The wave kernel's 64 x 64 tiles fill it from about a thousand waves on, but
+// every wave reads its own fragments, so at u = 1 it reaches a fraction r of
+// mm_kernel's rate; below u = r it is the faster one.  r, measured at 4096^3
+// to 8192^3 (main kernel, us, mm / wave): FP32 932 / 963 and 7305 / 7389,
+// split-BF16 528 / 696 and 4154 / 6310, two-piece FP16 322 / 406 and
+// 2429 / 3427, BF16 124 / 179 and 866 / 1394, FP8 84 / 93 and 533 / 704,
+// refined FP8 161 / 181 and 1183 / 1571.  Left of the line: 1024^3 (16 tiles)
+// FP32 251 / 26, split-BF16 111 / 22, BF16 43 / 13; 5000^3 (400 tiles) FP32
+// 3425 / 1877, refined FP8 507 / 383.  FP64 always takes it (an LDS-tiled
+// 64 x 64 kernel measured 3075 us at 4096^3 against 1852, 400 against 259 at
+// 2048^3, 18.6 against 6.4 at 256^3).
+int wave_percent(const FormInfo &f) {
+    switch (f.fam) {
+        case FAM_F64: return 101;
+        case FAM_F32: return 95;
+        case FAM_FP8: return f.form ? 78 : 80;
+        default: return f.form == 1 ? 70 : f.form == 2 ? 75 : 65;
+    }
+}
+
+// MFMA tiles per side of the wave kernel's tile, and waves per workgroup.
+// The forms with cheap fragments (FP32, FP64: an MFMA takes 64 cycles for two
+// fragments of 16 bytes a lane) keep small tiles until 900 large ones exist
+// and 4 waves a workgroup until 8192 (FP32 2048^3, 1024 large tiles: 143 us
+// with 4 waves, 195 with 2, 255 with 1, since workgroups of one wave share
+// SIMDs while others idle).  The 16-bit and FP8 forms are bound by fragment
+// reads, which a large tile halves: large from 256 tiles (split: 1024^3 22 us
+// against 24) or 400 (plain: BF16 1100x900x1000, 270 tiles, 14.5 us small
+// against 16.9), and only as many waves as fill the SIMDs.
+void wave_shape(const FormInfo &f, int64_t small, int64_t large, int64_t chunks, int *t, int *kg) {
+    const bool slow = f.fam == FAM_F64 || f.fam == FAM_F32;
+    *t = large >= (slow ? 900 : f.form ? 256 : 400) ? 2 : 1;
+    const int64_t n = *t == 2 ? large : small;
+    if (slow) *kg = n >= 8192 ? 1 : 4;
+    else if (*t == 2) *kg = n >= 1500 ? 1 : n >= 512 ? 2 : 4;
+    else *kg = n >= 768 ? 1 : n >= 384 ? 2 : 4;
+    if (n <= 128 && chunks >= 256) *kg = 8;     // long sums on few tiles: 300x320x6000 BF16 15 us against 17
+    while (*kg > 1 && chunks < 2 * *kg) *kg /= 2;
+}
+
+// Replans *P for the wave kernel where that is the faster one.  The packed
+// operands never take more workspace than mm_kernel's plan (rows of a class
+// are not padded, columns and chunks to smaller units) and neither do the
+// planes, so a call that fits a given workspace still does.
+void plan_wave(Plan *P) {
+    if (P->M == 0 || P->N == 0 || P->Kd == 0) return;
+    const int fam = P->f.fam;
+    const int64_t tiles = (int64_t)P->K * ceil_div(P->Kt, P->G) * P->ga.GS * P->gb.GS * P->nsplit;
+    if (tiles * 100 >= ceil_div(tiles, kCUs) * kCUs * wave_percent(P->f)) return;
+    Plan W = *P;
+    const int64_t L = (int64_t)P->Kt * P->ga.S_r;         // rows of a residue class
+    const int CBY = wave_chunk_bytes(fam);
+    const int64_t nch = ceil_div(P->ga.S_k, CBY / P->f.packed_esz), chunks = P->p * nch;
+    auto count = [&](int t) {
+        const int64_t R = wave_tile(fam, t);
+        return (int64_t)P->K * ceil_div(L, R) * ceil_div(P->N, R);
+    };
+    wave_shape(P->f, count(1), count(2), chunks, &W.wave, &W.kg);
+    const int64_t wt = count(W.wave);
+    if (wt * 4 > std::numeric_limits<int32_t>::max()) return;   // grid padded in both directions
+    const int R = wave_tile(fam, W.wave);
+    OperandGeom &a = W.ga, &b = W.gb;
+    a.striped = OPG_CLASSES; a.K = P->K;
+    a.grp_rows = (int)std::min<int64_t>(R, L);
+    a.GS = ceil_div(L, a.grp_rows); a.n_groups = P->K * a.GS;
+    a.last_rows = (int)(L - (a.GS - 1) * a.grp_rows);
+    b.grp_rows = R; b.GS = ceil_div(P->N, R); b.n_groups = b.GS;
+    for (OperandGeom *g : {&a, &b}) {
+        g->nch = nch; g->chunk_bytes = CBY;
+        g->piece_bytes = chunks * g->grp_rows * CBY;
+        g->group_bytes = g->pieces * g->piece_bytes;
+    }
+    a.class_bytes = L * a.pieces * chunks * CBY;
+    const int64_t kMaxUnits = ((int64_t)1 << 32) - 512;   // 32-bit unit numbers
+    if (pack_units(a, 1) > kMaxUnits || pack_units(b, 1) > kMaxUnits) return;
+    int64_t ns = std::min<int64_t>({(int64_t)P->nsplit, kCUs / wt, chunks / (16 * W.kg)});
+    if (ns < 2) ns = 1;
+    W.split_stages = (int)ceil_div(chunks, ns);
+    W.nsplit = (int)ceil_div(chunks, W.split_stages);
+    layout_workspace(&W);
+    *P = W;
 }
 
 // Geometry of one product C[M,N] = X[M,Kd] Y[Kd,N] under schedule (p, K).
@@ -131,7 +251,6 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
     const int MS = (int)std::min<int64_t>(BMT, S_r);
     P->G = (int)std::max<int64_t>(1, std::min<int64_t>(P->Kt, BMT / MS));
     const int NP = fp8 ? (P->f.form == 1 ? 2 : 1) : (P->f.form == 1 ? 3 : P->f.form == 2 ? 2 : 1);
-    const bool rowscale = P->f.pack == PK_SPLIT2F16;
     if (fp8) {
         // every 32-row / 32-column MFMA tile and every 64-deep chunk must lie
         // inside one 128 x 128 scale tile: whole 64-chunks per block, 32-row
@@ -140,14 +259,14 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
     }
 
     OperandGeom &a = P->ga;
-    a.R = M; a.Kd = Kd; a.striped = 1; a.S_r = S_r; a.grp_rows = MS;
+    a.R = M; a.Kd = Kd; a.striped = OPG_STRIPES; a.S_r = S_r; a.grp_rows = MS;
     a.GS = ceil_div(S_r, MS); a.n_groups = (int64_t)p * a.GS; a.p = p;
     a.S_k = S_k; a.nch = nch; a.chunk_bytes = CBY; a.pieces = NP;
     a.piece_bytes = (int64_t)p * nch * MS * CBY;
     a.group_bytes = NP * a.piece_bytes;
 
     OperandGeom &b = P->gb;
-    b.R = N; b.Kd = Kd; b.striped = 0; b.S_r = 0; b.grp_rows = BNT;
+    b.R = N; b.Kd = Kd; b.striped = OPG_TILES; b.S_r = 0; b.grp_rows = BNT;
     b.GS = ceil_div(N, BNT); b.n_groups = b.GS; b.p = p;
     b.S_k = S_k; b.nch = nch; b.chunk_bytes = CBY; b.pieces = NP;
     b.piece_bytes = (int64_t)p * nch * BNT * CBY;
@@ -182,27 +301,11 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
         P->nsplit = (int)ceil_div(nstages, P->split_stages);
     }
 
-    // workspace: the two packed operands (no partial planes: the collector
-    // keeps every partial in registers), the FP8 tile exponents or the
-    // two-piece FP16 row amaxes, and the split planes
-    size_t off = 0;
-    P->off_a = off; off = align_up(off + (size_t)(a.n_groups * a.group_bytes));
-    P->off_b = off; off = align_up(off + (size_t)(b.n_groups * b.group_bytes));
-    P->tiles_k = ceil_div(Kd, FP8_TILE);
-    P->tiles_ra = ceil_div(M, FP8_TILE);
-    P->tiles_rb = ceil_div(N, FP8_TILE);
-    P->off_ea = P->off_eb = off;
-    if (fp8) {
-        P->off_ea = off; off = align_up(off + (size_t)P->tiles_ra * P->tiles_k * 2 * sizeof(int32_t));
-        P->off_eb = off; off = align_up(off + (size_t)P->tiles_rb * P->tiles_k * 2 * sizeof(int32_t));
-    }
-    if (rowscale) {
-        P->off_ea = off; off = align_up(off + (size_t)M * sizeof(uint32_t));
-        P->off_eb = off; off = align_up(off + (size_t)N * sizeof(uint32_t));
-    }
-    P->off_part = off;
-    if (P->nsplit > 1) off = align_up(off + (size_t)P->nsplit * M * N * (P->f.out_f64 ? 8 : 4));
-    P->total = (M == 0 || N == 0 || Kd == 0) ? 0 : off;
+    P->wave = 0;
+    P->kg = 0;
+    layout_workspace(P);
+    plan_wave(P);
+    if (P->f.fam == FAM_F64 && P->wave == 0 && P->total > 0) return HS_ERR_NOT_SUPPORTED;   // no other FP64 kernel
     return HS_OK;
 }
 
@@ -268,12 +371,23 @@ bool pack_mn_ok(const Plan &P, const Operand &X, const OperandGeom &g) {
     if (X.kmajor || X.embed != EMB_NONE) return false;
     if (P.f.pack != PK_F32 && P.f.pack != PK_SPLIT3 && P.f.pack != PK_FP8 && P.f.pack != PK_SPLIT2F16)
         return false;
-    return X.ld % 4 == 0 && aligned(X.ptr, 16) && g.grp_rows % 4 == 0 && (!g.striped || g.S_r % 4 == 0);
+    return X.ld % 4 == 0 && aligned(X.ptr, 16) && g.grp_rows % 4 == 0 && (g.striped == OPG_TILES || g.S_r % 4 == 0);
 }
 
 hipError_t pack_operand(const Plan &P, const Operand &X, const PackArgs &pa, const OperandGeom &g, hipStream_t st) {
     if (pack_mn_ok(P, X, g)) return launch_pack_mn(P.f.pack, pa, st);
     return launch_pack(P.f.pack, X.kmajor, pa, st);
+}
+
+// 32 workgroups per XCD batch: grp_v class members x grp_t column tiles.
+void batch_shape(int64_t nt, int64_t members, int64_t *grp_v, int64_t *grp_t, int64_t *n_ug, int64_t *n_tg) {
+    int64_t gt = 1;
+    while (gt * 2 <= 8 && gt * 2 <= nt) gt *= 2;
+    int64_t gv = 32 / gt;
+    while (gv > 1 && gv / 2 >= members) gv /= 2;
+    *grp_t = gt; *grp_v = gv;
+    *n_tg = ceil_div(nt, gt);
+    *n_ug = ceil_div(members, gv);
 }
 
 // One product through the hyper-systolic path.  The plan must come from
@@ -317,13 +431,33 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
     e = pack_operand(P, Y, pb, P.gb, stream);
     if (e != hipSuccess) return HS_ERR_LAUNCH_FAILED;
 
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    if (P.wave) {
+        WaveArgs v{};
+        v.A = w + P.off_a; v.a_group = P.ga.group_bytes; v.a_class = P.ga.class_bytes;
+        v.B = w + P.off_b; v.b_group = P.gb.group_bytes;
+        v.a_rows = P.ga.grp_rows; v.a_last = P.ga.last_rows; v.GS = P.ga.GS;
+        v.a_exps = ea; v.b_exps = eb; v.a_tiles_k = P.tiles_k; v.b_tiles_k = P.tiles_k;
+        v.S_k = P.ga.S_k; v.Kd = P.Kd;
+        v.out = out; v.ldo = ldo;
+        v.p = P.p; v.K = P.K; v.Kt = P.Kt; v.nch = P.ga.nch; v.S_r = P.ga.S_r;
+        v.M = P.M; v.N = P.N; v.n_ntiles = P.gb.GS;
+        batch_shape(P.gb.GS, P.ga.GS, &v.grp_v, &v.grp_t, &v.n_ug, &v.n_tg);
+        v.kg = P.kg; v.nsplit = P.nsplit; v.split_chunks = P.split_stages; v.part = w + P.off_part;
+        if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
+        e = launch_wave(P.f.fam, P.f.form, P.wave, v, stream);
+        if (g_prof) keep_timing(ev0, ev1);
+        if (e == hipSuccess && P.nsplit > 1)
+            e = launch_backshift(f64, v.part, P.M * P.N, P.nsplit, P.M, P.N, out, ldo, stream);
+        return launch_status(e);
+    }
     MainArgs m{};
     m.A = w + P.off_a; m.a_piece = P.ga.piece_bytes; m.a_group = P.ga.group_bytes;
     m.B = w + P.off_b; m.b_piece = P.gb.piece_bytes; m.b_group = P.gb.group_bytes;
     m.a_span = P.a_span;
     m.p = P.p; m.K = P.K; m.Kt = P.Kt;
     m.MS = P.ga.grp_rows; m.G = P.G; m.GS = P.ga.GS; m.nch = P.ga.nch; m.S_r = P.ga.S_r;
-    m.M = P.M; m.N = P.N; m.out_f64 = f64;
+    m.M = P.M; m.N = P.N;
     m.a_exps = ea; m.b_exps = eb; m.a_tiles_k = P.tiles_k; m.b_tiles_k = P.tiles_k;
     m.S_k = P.ga.S_k; m.Kd = P.Kd;
     m.out = out;
@@ -332,18 +466,7 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
     m.nsplit = P.nsplit;
     m.split_stages = P.split_stages;
     m.part = w + P.off_part;
-    {   // 32 workgroups per XCD: grp_v class members x grp_t column tiles
-        const int64_t nt = P.gb.GS;
-        int64_t gt = 1;
-        while (gt * 2 <= 8 && gt * 2 <= nt) gt *= 2;
-        const int64_t members = ceil_div(P.Kt, P.G) * P.ga.GS;
-        int64_t gv = 32 / gt;
-        while (gv > 1 && gv / 2 >= members) gv /= 2;
-        m.grp_t = gt; m.grp_v = gv;
-        m.n_tg = ceil_div(nt, gt);
-        m.n_ug = ceil_div(members, gv);
-    }
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    batch_shape(P.gb.GS, ceil_div(P.Kt, P.G) * P.ga.GS, &m.grp_v, &m.grp_t, &m.n_ug, &m.n_tg);
     if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
     e = launch_mm(P.f.fam, P.f.form, m, stream);
     if (g_prof) keep_timing(ev0, ev1);

@@ -67,14 +67,28 @@ struct Fp8ExpArgs {
     int32_t *exps;            // [tile_r][tile_k][2]
 };
 
+// How an operand's rows are cut into groups.
+enum OperandGroups : int {
+    OPG_TILES = 0,    // runs of grp_rows rows
+    OPG_STRIPES = 1,  // p stripes of S_r rows, each in GS groups of MS = grp_rows rows
+    OPG_CLASSES = 2   // the stripes of each residue class mod K, one after the other, as one
+                      // list of K~ S_r rows cut into groups of grp_rows (the last one shorter,
+                      // nothing padded): position q of class c is row q mod S_r of stripe
+                      // c + (q / S_r) K.  Group gi of class c starts at c class_bytes +
+                      // gi group_bytes, and its own row count is the stride of its planes.
+};
+
 struct OperandGeom {
     int64_t R;        // logical rows
     int64_t Kd;       // contraction length
-    int striped;      // 1: p stripes of S_r rows, groups of MS; 0: groups of grp_rows
+    int striped;      // OPG_TILES, OPG_STRIPES or OPG_CLASSES
     int64_t S_r;      // stripe height (striped) -- ceil(R / p)
     int grp_rows;     // rows per group (MS or BN)
-    int64_t GS;       // groups per stripe (striped) or total groups (tiles)
-    int64_t n_groups; // logical groups (p GS striped, GS otherwise)
+    int64_t GS;       // groups per stripe, per class, or total groups (tiles)
+    int64_t n_groups; // logical groups (p GS, K GS or GS)
+    int K;            // OPG_CLASSES: residue classes
+    int last_rows;    // OPG_CLASSES: rows of a class's last group (the others have grp_rows)
+    int64_t class_bytes;  // OPG_CLASSES: one class, all its groups
     int p;
     int64_t S_k;      // contraction block length -- ceil(Kd / p)
     int64_t nch;      // chunks per block (padded)
@@ -142,7 +156,6 @@ struct MainArgs {
     int64_t S_r;             // stripe height
     int64_t M, N;
     int64_t n_ntiles;        // column tiles
-    int out_f64;             // out element type: 1 double, 0 float
     // workgroup groups: grp_v class members x grp_t column tiles run together
     int64_t grp_v, grp_t, n_ug, n_tg;
     // launches with fewer output tiles than CUs: nsplit workgroups per tile,
@@ -150,6 +163,35 @@ struct MainArgs {
     // in planes [nsplit][M][N] of part (element type as out), summed after
     int nsplit;
     int split_stages;
+    void *part;
+};
+
+// The wave-tile kernel (launches that 256 x 256 tiles leave most of the chip
+// idle): one workgroup of kg waves per output tile of one group of a residue
+// class's rows (OPG_CLASSES) by bn columns; each wave walks its own run of
+// the tile's chunks in the step order, and the kg sums are added in LDS.
+struct WaveArgs {
+    const uint8_t *A;
+    const uint8_t *B;
+    int64_t a_group, a_class;      // bytes between groups of a class, between classes
+    int64_t b_group;
+    int a_rows, a_last;            // rows of a group, of a class's last group
+    int64_t GS;                    // groups per class
+    const int32_t *a_exps;         // as in MainArgs
+    const int32_t *b_exps;
+    int64_t a_tiles_k, b_tiles_k;
+    int64_t S_k, Kd;
+    void *out;
+    int64_t ldo;
+    int p, K, Kt;
+    int64_t nch;                   // chunks per contraction block
+    int64_t S_r;
+    int64_t M, N;
+    int64_t n_ntiles;
+    int64_t grp_v, grp_t, n_ug, n_tg;
+    int kg;                        // waves per workgroup, a power of two
+    int nsplit;                    // workgroups per tile (planes of part if > 1)
+    int split_chunks;              // chunks each of them walks
     void *part;
 };
 

@@ -30,21 +30,9 @@
 
 #include <type_traits>
 
-#include "hs_internal.h"
+#include "hs_mfma.h"
 
 namespace hs {
-
-#define DEVI __device__ __forceinline__
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes, a native vector
-typedef int i32x8 __attribute__((ext_vector_type(8)));             // 32 fp8 values
 
 // ---------------------------------------------------------------------------
 // number formats
@@ -176,11 +164,6 @@ __global__ __launch_bounds__(512) void fp8_tile_exp_kernel(Fp8ExpArgs a) {
     }
 }
 
-// Scale exponent of an operand row from its amax bits: the largest e with
-// amax 2^e < 2^15 is 15 - frexp_exp(amax) (frexp_exp(0) = 0: any e suits
-// a row of zeros).
-DEVI int row_scale_exp(uint32_t amax_bits) { return 15 - __builtin_amdgcn_frexp_expf(__uint_as_float(amax_bits)); }
-
 // Eight floats of one row -> the 16-byte units of their two FP16 pieces,
 // x' = x 2^e, a0 = f16(x'), a1 = f16(x' - a0): round to nearest even, the
 // residual exact in FP32 (a0 is within a factor 2 of x', or both lie below
@@ -204,6 +187,23 @@ template <> struct PackTraits<PK_SPLIT3> { typedef float S; static const int UE 
 template <> struct PackTraits<PK_FP8> { typedef float S; static const int UE = 16; static const int ESZ = 1; static const int NP = 2; };
 template <> struct PackTraits<PK_SPLIT2F16> { typedef float S; static const int UE = 8; static const int ESZ = 2; static const int NP = 2; };
 
+// The operand row at position rr of group grp, and whether it exists (rows
+// past a stripe, a class's list or the operand are padding).
+DEVI void group_row(const OperandGeom &g, uint32_t grp, uint32_t rr, int64_t &row, bool &valid) {
+    const int64_t at = (int64_t)(g.striped == OPG_TILES ? grp : grp % (uint32_t)g.GS) * g.grp_rows + rr;
+    if (g.striped == OPG_TILES) {
+        row = at;
+        valid = row < g.R;
+    } else if (g.striped == OPG_STRIPES) {
+        row = (int64_t)(grp / (uint32_t)g.GS) * g.S_r + at;
+        valid = at < g.S_r && row < g.R;
+    } else {
+        const uint32_t S = (uint32_t)g.S_r, i = (uint32_t)at / S;   // at < R + grp_rows
+        row = (int64_t)(grp / (uint32_t)g.GS + i * (uint32_t)g.K) * g.S_r + ((uint32_t)at - i * S);
+        valid = i < (uint32_t)(g.p / g.K) && row < g.R;
+    }
+}
+
 // Write one 16-byte unit (of each piece) of the packed image: row rr of
 // group grp, block kb, chunk ch, plane half, from the unit's values.
 template <int KIND>
@@ -211,11 +211,22 @@ DEVI void pack_emit(const PackArgs &a, uint32_t grp, uint32_t kb, uint32_t ch, u
                     int64_t row, bool rvalid, int64_t kk0, const float *vals_f, const double *vals_d,
                     const uint16_t *vals_h) {
     const OperandGeom &g = a.g;
-    const uint32_t nch = (uint32_t)g.nch, gr = (uint32_t)g.grp_rows;
+    const uint32_t nch = (uint32_t)g.nch;
+    int64_t base = (int64_t)grp * g.group_bytes, piece = g.piece_bytes;
+    uint32_t gr = (uint32_t)g.grp_rows;
+    if (g.striped == OPG_CLASSES) {             // the last group of a class has its own row count
+        const uint32_t cls = grp / (uint32_t)g.GS, gi = grp % (uint32_t)g.GS;
+        base = cls * g.class_bytes + gi * g.group_bytes;
+        if (gi + 1 == (uint32_t)g.GS) {
+            gr = (uint32_t)g.last_rows;
+            if (rr >= gr) return;
+            piece = (int64_t)g.p * nch * gr * g.chunk_bytes;
+        }
+    }
     // chunk = UPR planes of 16 bytes per row: [plane][row][16 bytes]
     // [group][piece][block][chunk][plane][row][16 bytes]
     const int64_t inner = ((int64_t)kb * nch + ch) * gr * g.chunk_bytes + ((int64_t)half * gr + rr) * 16;
-    uint8_t *dst = (uint8_t *)a.dst + (int64_t)grp * g.group_bytes + inner;
+    uint8_t *dst = (uint8_t *)a.dst + base + inner;
     auto put = [&](int64_t at, const u32x4 &w) { *(u32x4 *)(dst + at) = w; };
     if constexpr (KIND == PK_F64) {
         put(0, __builtin_bit_cast(u32x4, make_double2(vals_d[0], vals_d[1])));
@@ -252,13 +263,13 @@ DEVI void pack_emit(const PackArgs &a, uint32_t grp, uint32_t kb, uint32_t ch, u
             }
         }
         put(0, w0);
-        if (a.refine) put(g.piece_bytes, w1);
+        if (a.refine) put(piece, w1);
     } else if constexpr (KIND == PK_SPLIT2F16) {
         const int e = rvalid ? row_scale_exp(((const uint32_t *)a.exps)[row]) : 0;
         u32x4 w0, w1;
         split2_f16_units(*(const float(*)[8])vals_f, e, w0, w1);
         put(0, w0);
-        put(g.piece_bytes, w1);
+        put(piece, w1);
     } else {   // PK_SPLIT3: a0 = bf16(a), a1 = bf16(a - a0), a2 = bf16(a - a0 - a1)
         float x[8];
 #pragma unroll
@@ -266,8 +277,8 @@ DEVI void pack_emit(const PackArgs &a, uint32_t grp, uint32_t kb, uint32_t ch, u
         u32x4 w0, w1, w2;
         split3_units(x, w0, w1, w2);
         put(0, w0);
-        put(g.piece_bytes, w1);
-        put(2 * g.piece_bytes, w2);
+        put(piece, w1);
+        put(2 * piece, w2);
     }
 }
 
@@ -374,15 +385,7 @@ DEVI MnUnit mn_decode(uint32_t u, const OperandGeom &g) {
     d.ch = t % nch;   t /= nch;
     d.kb = t % p;
     d.grp = t / p;
-    if (g.striped) {
-        const int64_t stripe = d.grp / g.GS, msub = d.grp % g.GS;
-        const int64_t within = msub * gr + d.rr;
-        d.row = stripe * g.S_r + within;
-        d.rvalid = within < g.S_r && d.row < g.R;
-    } else {
-        d.row = (int64_t)d.grp * gr + d.rr;
-        d.rvalid = d.row < g.R;
-    }
+    group_row(g, d.grp, d.rr, d.row, d.rvalid);
     d.kin0 = (int64_t)d.ch * KC + d.half * T::UE;
     d.kk0 = (int64_t)d.kb * g.S_k + d.kin0;
     return d;
@@ -416,14 +419,7 @@ __global__ __launch_bounds__(256) void pack_mn_kernel(PackArgs a) {
             if (d.kin0 + e < g.S_k && kk < g.Kd) {
                 bool rv[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (g.striped) {
-                        const int64_t within = (int64_t)(d.grp % g.GS) * g.grp_rows + d.rr + r;
-                        rv[r] = within < g.S_r && d.row + r < g.R;
-                    } else {
-                        rv[r] = d.row + r < g.R;
-                    }
-                }
+                for (int r = 0; r < 4; ++r) rv[r] = d.rvalid && d.row + r < g.R;   // one stripe: S_r % 4 == 0
                 const float *q4 = src + kk * a.ld + d.row;
                 if (rv[0] && rv[1] && rv[2] && rv[3]) {
                     v = *(const float4 *)q4;
@@ -491,15 +487,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
     }
     int64_t row;
     bool rvalid;
-    if (g.striped) {
-        const int64_t stripe = grp / g.GS, msub = grp % g.GS;
-        const int64_t within = msub * gr + rr;
-        row = stripe * g.S_r + within;
-        rvalid = within < g.S_r && row < g.R;
-    } else {
-        row = (int64_t)grp * gr + rr;
-        rvalid = row < g.R;
-    }
+    group_row(g, grp, rr, row, rvalid);
     const int64_t kin0 = (int64_t)ch * KC + half * T::UE;
     const int64_t kk0 = (int64_t)kb * g.S_k + kin0;
     const S *src = (const S *)a.src;
@@ -562,27 +550,6 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
 // ---------------------------------------------------------------------------
 // the hyper-systolic main loop on MFMA
 // ---------------------------------------------------------------------------
-// FORM 0: one piece per operand, one product.  FORM 1: three bf16 pieces,
-// the six products a_i b_j with i + j <= 2, smallest first.  FORM 2: two
-// f16 pieces of the row-scaled operands, the three products a_i b_j with
-// i + j <= 1, smallest first; the epilogue removes the row scales.
-template <int FORM> struct Form;
-template <> struct Form<0> { static const int NP = 1; static const int NPROD = 1; };
-template <> struct Form<1> { static const int NP = 3; static const int NPROD = 6; };
-template <> struct Form<2> { static const int NP = 2; static const int NPROD = 3; };
-
-template <int FAM> struct Mfma;
-template <> struct Mfma<FAM_F64> { static const int T = 16; typedef f64x4 Acc; };
-template <> struct Mfma<FAM_F32> { static const int T = 32; typedef f32x16 Acc; };
-template <> struct Mfma<FAM_BF16> { static const int T = 32; typedef f32x16 Acc; };
-template <> struct Mfma<FAM_F16> { static const int T = 32; typedef f32x16 Acc; };
-template <> struct Mfma<FAM_FP8> { static const int T = 32; typedef f32x16 Acc; };
-
-// Pieces per operand: split-BF16 3, two-piece FP16 2, refined FP8 2 (q0,
-// q1), otherwise 1.
-template <int FAM, int FORM>
-struct Pieces { static const int NP = FAM == FAM_FP8 ? (FORM ? 2 : 1) : Form<FORM>::NP; };
-
 template <int FAM, int FORM, int BM, int BN, int CPS, int WAVES>
 struct MmCfg {
     static const int NP = Pieces<FAM, FORM>::NP;
@@ -604,112 +571,52 @@ struct MmCfg {
     // by hand (FP32, plain BF16 and FP16)
     static const bool W1 = WAVES == 4 && BM == 256;
     // B fragments straight from memory into registers (32x32 families)
-    static const bool BD = FAM != FAM_F64 && FAM != FAM_FP8 && !W1;
+    static const bool BD = FAM != FAM_FP8 && !W1;
     static const int LDS_BYTES = W1 ? 0 : 2 * (BD ? A_STAGE : STAGE);   // dynamic LDS: two slots
 };
 
-// One pipeline stage of block products from LDS: for every chunk of the
-// stage, the wave's MFMA tiles accumulate A_rows x B_cols.
-// For FP8, sa[c][P][mi] / sb[c][P][ni] are the E8M0 block-scale bytes of
-// chunk c, piece P, row / column tile (uniform across the wave).
+// One FP8 pipeline stage from LDS: for every chunk of the stage, the wave's
+// MFMA tiles accumulate A_rows x B_cols.  sa[c][P][mi] / sb[c][P][ni] are the
+// E8M0 block-scale bytes of chunk c, piece P, row / column tile (uniform
+// across the wave).
 template <int FAM, int FORM, int BM, int BN, int CPS, int WAVES, typename AccArr, typename SA, typename SB>
 DEVI void mm_compute(AccArr &acc, const uint8_t *Ab, const uint8_t *Bb, int lane, int wm, int wn,
-                     const SA &sa, const SB &sb) {
+                const SA &sa, const SB &sb) {
     typedef MmCfg<FAM, FORM, BM, BN, CPS, WAVES> C;
 #pragma unroll
     for (int c = 0; c < CPS; ++c) {
-        if constexpr (FAM == FAM_FP8) {
-            // lane group g holds contraction elements 32g..32g+31 of the
-            // 64-element chunk: planes 2g and 2g+1 of the row
-            const int r32 = lane & 31, g = lane >> 5;
-            i32x8 bv[C::NP][C::TN];
+        // lane group g holds contraction elements 32g..32g+31 of the
+        // 64-element chunk: planes 2g and 2g+1 of the row
+        const int r32 = lane & 31, g = lane >> 5;
+        i32x8 bv[C::NP][C::TN];
 #pragma unroll
-            for (int P = 0; P < C::NP; ++P)
+        for (int P = 0; P < C::NP; ++P)
 #pragma unroll
-                for (int ni = 0; ni < C::TN; ++ni) {
-                    const uint8_t *q = Bb + (P * CPS + c) * BN * C::CB + (2 * g) * BN * 16 + (wn * C::WN + ni * 32 + r32) * 16;
-                    const u32x4 lo = *(const u32x4 *)q, hi = *(const u32x4 *)(q + BN * 16);
-                    bv[P][ni] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-                }
-#pragma unroll
-            for (int mi = 0; mi < C::TM; ++mi) {
-                i32x8 av[C::NP];
-#pragma unroll
-                for (int P = 0; P < C::NP; ++P) {
-                    const uint8_t *q = Ab + (P * CPS + c) * BM * C::CB + (2 * g) * BM * 16 + (wm * C::WM + mi * 32 + r32) * 16;
-                    const u32x4 lo = *(const u32x4 *)q, hi = *(const u32x4 *)(q + BM * 16);
-                    av[P] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-                }
-#pragma unroll
-                for (int ni = 0; ni < C::TN; ++ni) {
-                    if constexpr (C::NP == 2) {
-                        // q1 q0', q0 q1', q0 q0': smallest first
-                        acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            av[1], bv[0][ni], acc[mi][ni], 0, 0, 0, sa[c][1][mi], 0, sb[c][0][ni]);
-                        acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            av[0], bv[1][ni], acc[mi][ni], 0, 0, 0, sa[c][0][mi], 0, sb[c][1][ni]);
-                    }
-                    acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        av[0], bv[0][ni], acc[mi][ni], 0, 0, 0, sa[c][0][mi], 0, sb[c][0][ni]);
-                }
+            for (int ni = 0; ni < C::TN; ++ni) {
+                const uint8_t *q = Bb + (P * CPS + c) * BN * C::CB + (2 * g) * BN * 16 + (wn * C::WN + ni * 32 + r32) * 16;
+                const u32x4 lo = *(const u32x4 *)q, hi = *(const u32x4 *)(q + BN * 16);
+                bv[P][ni] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
             }
-        } else if constexpr (FAM == FAM_F64) {
-            const int r16 = lane & 15, g = lane >> 4;
-            double av[C::TM], bv[C::TN];
 #pragma unroll
-            for (int mi = 0; mi < C::TM; ++mi)
-                av[mi] = *(const double *)(Ab + (c * 2 + (g >> 1)) * BM * 16 + (wm * C::WM + mi * 16 + r16) * 16 + (g & 1) * 8);
+        for (int mi = 0; mi < C::TM; ++mi) {
+            i32x8 av[C::NP];
 #pragma unroll
-            for (int ni = 0; ni < C::TN; ++ni)
-                bv[ni] = *(const double *)(Bb + (c * 2 + (g >> 1)) * BN * 16 + (wn * C::WN + ni * 16 + r16) * 16 + (g & 1) * 8);
+            for (int P = 0; P < C::NP; ++P) {
+                const uint8_t *q = Ab + (P * CPS + c) * BM * C::CB + (2 * g) * BM * 16 + (wm * C::WM + mi * 32 + r32) * 16;
+                const u32x4 lo = *(const u32x4 *)q, hi = *(const u32x4 *)(q + BM * 16);
+                av[P] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            }
 #pragma unroll
-            for (int mi = 0; mi < C::TM; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < C::TN; ++ni)
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[mi], bv[ni], acc[mi][ni], 0, 0, 0);
-        } else {
-            const int r32 = lane & 31, g = lane >> 5;
-            // all B fragments of the chunk, then one row tile of A at a time
-            u32x4 bv[C::NP][C::TN];
-#pragma unroll
-            for (int P = 0; P < C::NP; ++P)
-#pragma unroll
-                for (int ni = 0; ni < C::TN; ++ni)
-                    bv[P][ni] = *(const u32x4 *)(Bb + (P * CPS + c) * BN * C::CB + g * BN * 16 +
-                                                 (wn * C::WN + ni * 32 + r32) * 16);
-#pragma unroll
-            for (int mi = 0; mi < C::TM; ++mi) {
-                u32x4 av[C::NP];
-#pragma unroll
-                for (int P = 0; P < C::NP; ++P)
-                    av[P] = *(const u32x4 *)(Ab + (P * CPS + c) * BM * C::CB + g * BM * 16 +
-                                             (wm * C::WM + mi * 32 + r32) * 16);
-#pragma unroll
-                for (int ni = 0; ni < C::TN; ++ni) {
-                    if constexpr (FAM == FAM_F32) {
-                        // lane group g holds contraction elements 4g..4g+3 of
-                        // the chunk; MFMA t takes element t of A and B alike
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                                __uint_as_float(av[0][t]), __uint_as_float(bv[0][ni][t]), acc[mi][ni], 0, 0, 0);
-                    } else if constexpr (FAM == FAM_F16) {
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                            __builtin_bit_cast(f16x8, av[0]), __builtin_bit_cast(f16x8, bv[0][ni]), acc[mi][ni], 0, 0, 0);
-                    } else if constexpr (FORM == 0) {
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            __builtin_bit_cast(bf16x8, av[0]), __builtin_bit_cast(bf16x8, bv[0][ni]), acc[mi][ni], 0, 0, 0);
-                    } else {
-                        // a2 b0, a1 b1, a0 b2, a1 b0, a0 b1, a0 b0: smallest first
-#pragma unroll
-                        for (int q = 0; q < 6; ++q) {
-                            const int pa = q < 3 ? 2 - q : (q == 3 ? 1 : 0);
-                            const int pb = q < 3 ? q : (q == 4 ? 1 : 0);
-                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                __builtin_bit_cast(bf16x8, av[pa]), __builtin_bit_cast(bf16x8, bv[pb][ni]), acc[mi][ni], 0, 0, 0);
-                        }
-                    }
+            for (int ni = 0; ni < C::TN; ++ni) {
+                if constexpr (C::NP == 2) {
+                    // q1 q0', q0 q1', q0 q0': smallest first
+                    acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                        av[1], bv[0][ni], acc[mi][ni], 0, 0, 0, sa[c][1][mi], 0, sb[c][0][ni]);
+                    acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                        av[0], bv[1][ni], acc[mi][ni], 0, 0, 0, sa[c][0][mi], 0, sb[c][1][ni]);
                 }
+                acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                    av[0], bv[0][ni], acc[mi][ni], 0, 0, 0, sa[c][0][mi], 0, sb[c][0][ni]);
             }
         }
     }
@@ -727,41 +634,6 @@ DEVI void read_a_frags(AV &av, const uint8_t *Ab, int c, int mi, int lane, int w
         av[P] = *(const u32x4 *)(Ab + (P * CPS + c) * BM * C::CB + g * BM * 16 + (wm * C::WM + mi * 32 + r32) * 16);
 }
 
-template <int FAM, int FORM, int TN, typename AccRow, typename AV, typename BV>
-DEVI void mfma_row(AccRow &accr, const AV &av, const BV &bv) {
-#pragma unroll
-    for (int ni = 0; ni < TN; ++ni) {
-        if constexpr (FAM == FAM_F32) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                accr[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[0][t]), __uint_as_float(bv[0][ni][t]),
-                                                               accr[ni], 0, 0, 0);
-        } else if constexpr (FAM == FAM_F16 && FORM == 2) {
-            // a1 b0, a0 b1, a0 b0: smallest first
-            accr[ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, av[1]),
-                                                              __builtin_bit_cast(f16x8, bv[0][ni]), accr[ni], 0, 0, 0);
-            accr[ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, av[0]),
-                                                              __builtin_bit_cast(f16x8, bv[1][ni]), accr[ni], 0, 0, 0);
-            accr[ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, av[0]),
-                                                              __builtin_bit_cast(f16x8, bv[0][ni]), accr[ni], 0, 0, 0);
-        } else if constexpr (FAM == FAM_F16) {
-            accr[ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, av[0]),
-                                                              __builtin_bit_cast(f16x8, bv[0][ni]), accr[ni], 0, 0, 0);
-        } else if constexpr (FORM == 0) {
-            accr[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[0]),
-                                                               __builtin_bit_cast(bf16x8, bv[0][ni]), accr[ni], 0, 0, 0);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const int pa = q < 3 ? 2 - q : (q == 3 ? 1 : 0);
-                const int pb = q < 3 ? q : (q == 4 ? 1 : 0);
-                accr[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[pa]),
-                                                                   __builtin_bit_cast(bf16x8, bv[pb][ni]), accr[ni], 0, 0, 0);
-            }
-        }
-    }
-}
-
 // One stage of a 32x32 family whose B fragments are already in registers
 // (bq[chunk][piece][column tile]); A fragments come from the LDS slot.
 template <int FAM, int FORM, int BM, int BN, int CPS, int WAVES, typename AccArr, typename BQ>
@@ -775,12 +647,6 @@ DEVI void mm_compute_bd(AccArr &acc, const uint8_t *Ab, const BQ &bq, int lane, 
             read_a_frags<FAM, FORM, BM, BN, CPS, WAVES>(av, Ab, c, mi, lane, wm);
             mfma_row<FAM, FORM, C::TN>(acc[mi], av, bq[c]);
         }
-}
-
-// Buffer resource over a packed operand (raw buffer, byte addressed; the
-// third dword is the gfx9 default format word).
-DEVI __amdgpu_buffer_rsrc_t packed_rsrc(const uint8_t *base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)bytes, 0x00020000);
 }
 
 // Global -> registers for one stage: 16-byte buffer loads of the K static
@@ -1222,30 +1088,24 @@ void mm_kernel(MainArgs a) {
     for (int mi = 0; mi < C::TM; ++mi) {
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            int rho;
-            if constexpr (FAM == FAM_F64)      // 16x16x4 f64: element e of lane -> row 4e + lane/16
-                rho = wm * C::WM + mi * 16 + 4 * e + (lane >> 4);
-            else                               // 32x32 f32 accumulators
-                rho = wm * C::WM + mi * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+            const int rho = wm * C::WM + mi * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
             const int i = rho / MS, ir = rho % MS;
             const int64_t within = msub * MS + ir;
             const int64_t row = (int64_t)(r0 + i * K) * S_r + within;
             const bool rok = i < ng && within < S_r && row < a.M;
-            const int64_t cbase = ntile * BN + wn * C::WN + (FAM == FAM_F64 ? (lane & 15) : (lane & 31));
+            const int64_t cbase = ntile * BN + wn * C::WN + (lane & 31);
             int erow = 0;
             if constexpr (ROWSCALE) erow = rok ? row_scale_exp(((const uint32_t *)a.a_exps)[row]) : 0;
             // the element's destination: C, or plane `split` of a.part (rows of N)
             const bool to_part = a.nsplit > 1;
             const int64_t obase = to_part ? ((int64_t)split * a.M + row) * a.N + cbase : row * a.ldo + cbase;
-            void *dst = to_part ? a.part : a.out;
+            float *dst = (float *)(to_part ? a.part : a.out);
 #pragma unroll
             for (int ni = 0; ni < C::TN; ++ni) {
                 const bool ok = rok && cbase + ni * C::MT < a.N;
                 if (ok) {
-                    if (a.out_f64) ((double *)dst)[obase + ni * C::MT] = (double)acc[mi][ni][e];
-                    else if constexpr (ROWSCALE)
-                        ((float *)dst)[obase + ni * C::MT] = ldexpf((float)acc[mi][ni][e], -(erow + ecol[ni]));
-                    else ((float *)dst)[obase + ni * C::MT] = (float)acc[mi][ni][e];
+                    if constexpr (ROWSCALE) dst[obase + ni * C::MT] = ldexpf(acc[mi][ni][e], -(erow + ecol[ni]));
+                    else dst[obase + ni * C::MT] = acc[mi][ni][e];
                 }
             }
         }
@@ -1525,7 +1385,8 @@ static hipError_t launch_mm_t(const MainArgs &a, hipStream_t st) {
 }
 
 // Tile shapes per family: rows of the workgroup tile (K groups of MS rows),
-// columns, and chunks per pipeline stage.
+// columns, and chunks per pipeline stage.  FP64 runs on the wave kernel
+// alone; its entries are the geometry in which a call's limits are stated.
 int mm_tile_rows(int fam) { return fam == FAM_F64 ? 64 : 256; }
 int mm_tile_cols(int fam) { return fam == FAM_F64 ? 64 : 256; }
 int mm_chunks_per_stage(int fam, int form) {
@@ -1542,10 +1403,8 @@ int mm_chunks_per_stage(int fam, int form) {
 // 8 waves (2 per SIMD) for the split forms' and FP8's 256 x 256 tiles, 4
 // (one per SIMD) for FP32, plain BF16 and FP16 (measured at n = 8192 on
 // one box against 8 waves: FP32 7.33 against 7.61 ms, BF16 0.930 against
-// 0.970 ms, FP16 0.970 against 1.008 ms, with two chunks per stage) and for
-// FP64's 64 x 64.
+// 0.970 ms, FP16 0.970 against 1.008 ms, with two chunks per stage).
 hipError_t launch_mm(int fam, int form, const MainArgs &a, hipStream_t st) {
-    if (fam == FAM_F64) return launch_mm_t<FAM_F64, 0, 64, 64, 4, 4>(a, st);
     if (fam == FAM_F32) return launch_mm_t<FAM_F32, 0, 256, 256, 2, 4>(a, st);
     if (fam == FAM_F16 && form == 0) return launch_mm_t<FAM_F16, 0, 256, 256, 4, 4>(a, st);
     if (fam == FAM_F16 && form == 2) return launch_mm_t<FAM_F16, 2, 256, 256, 1, 8>(a, st);

@@ -1,0 +1,335 @@
+// hs_wave.hip -- the hyper-systolic main loop for launches whose 256 x 256
+// output tiles would leave most of the chip idle (small, narrow and
+// medium-sized products).
+//
+// What bounds such a launch is not the MFMA rate but how many SIMDs have work
+// and how long one wave's chain of chunks is.  So the output tile is small
+// (64 x 64, or 32 x 32 where even those are fewer than the CUs), and the
+// workgroup's kg waves share one tile: each walks its own run of the
+// tile's chunks in the step order of mm_kernel (partials l = K-1 .. 0, steps
+// of stride K, chunks of a block) with its own accumulators, and the kg sums
+// are added in LDS in a fixed order at the end.  A wave loads its MFMA
+// fragments straight from the packed operands (their layout is the fragment
+// layout: 32 lanes read 512 contiguous bytes) into D register sets, D - 1
+// chunks ahead, so there is no LDS staging and no barrier in the loop.
+#include <hip/hip_ext.h>
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "hs_internal.h"
+#include "hs_mfma.h"
+
+namespace hs {
+
+bool take_timed_launch(hipEvent_t *start, hipEvent_t *stop);   // hs_kernels.hip
+
+// T x T MFMA tiles per wave.  D: register sets of fragments (chunks in
+// flight + 1); a set is 2 T NP LD x 4 registers.
+template <int FAM, int FORM, int T>
+struct WvCfg {
+    static const int NP = Pieces<FAM, FORM>::NP;
+    static const int MT = Mfma<FAM>::T;
+    static const int ROWS = T * MT;                              // tile rows and columns
+    static const int CB = FAM == FAM_FP8 || FAM == FAM_F64 ? 64 : 32;   // bytes per chunk row
+    static const int LD = FAM == FAM_FP8 ? 2 : 1;                // 16-byte loads per fragment
+    static const int SET = 2 * T * NP * LD * 4;                  // registers of one set
+    static const int D = SET <= 8 ? 8 : SET <= 16 ? 4 : SET <= 24 ? 3 : 2;
+    typedef typename Mfma<FAM>::Acc Acc;
+    static const int NE = (int)(sizeof(Acc) / (FAM == FAM_F64 ? 8 : 4));
+};
+
+template <int FAM, int FORM, int T>
+__global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
+    typedef WvCfg<FAM, FORM, T> C;
+    typedef typename C::Acc Acc;
+    typedef typename std::conditional<FAM == FAM_F64, double, float>::type E;
+    extern __shared__ __attribute__((aligned(16))) uint8_t red[];   // kg / 2 accumulator sets
+    constexpr int NP = C::NP, MT = C::MT, LD = C::LD;
+    const int lane = threadIdx.x & 63;
+    const int kgi = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+
+    // workgroup -> (split, class, group of the class, column tile): each XCD
+    // takes a contiguous range, in batches of grp_v groups x grp_t column tiles
+    int64_t bid = blockIdx.x;
+    {
+        const int64_t nwg = gridDim.x, xcd = bid % 8, per = nwg / 8, rem = nwg % 8;
+        bid = xcd * per + (xcd < rem ? xcd : rem) + bid / 8;
+    }
+    const int split = (int)(bid / (gridDim.x / a.nsplit));
+    bid %= gridDim.x / a.nsplit;
+    const int p = a.p, K = a.K, Kt = a.Kt;
+    int64_t ntile, gi;
+    int cls;
+    {
+        const int64_t t_lo = bid % a.grp_t;  bid /= a.grp_t;
+        const int64_t u_lo = bid % a.grp_v;  bid /= a.grp_v;
+        const int64_t tg = bid % a.n_tg;     bid /= a.n_tg;
+        const int64_t ug = bid % a.n_ug;
+        cls = (int)(bid / a.n_ug);
+        ntile = tg * a.grp_t + t_lo;
+        gi = ug * a.grp_v + u_lo;
+        if (ntile >= a.n_ntiles || gi >= a.GS) return;   // grid padding
+    }
+    const int rows = gi + 1 == a.GS ? a.a_last : a.a_rows;        // rows of this group
+    const uint32_t nch = (uint32_t)a.nch;
+    const uint32_t a_chunk = (uint32_t)(rows * C::CB), b_chunk = (uint32_t)(C::ROWS * C::CB);
+    const uint32_t a_piece = (uint32_t)p * nch * a_chunk, b_piece = (uint32_t)p * nch * b_chunk;
+    const __amdgpu_buffer_rsrc_t rsA = packed_rsrc(a.A + cls * a.a_class + gi * a.a_group, a_piece * NP);
+    const __amdgpu_buffer_rsrc_t rsB = packed_rsrc(a.B + ntile * a.b_group, b_piece * NP);
+
+    // Fragment addresses: lane group g = lane / MT holds plane g (FP8: planes
+    // 2g, 2g + 1) of row lane % MT.  Tile rows past the group's own re-read
+    // row 0; they are never stored.
+    const int r = lane & (MT - 1), g = lane / MT;
+    int a_off[T], a_pl;
+#pragma unroll
+    for (int mi = 0; mi < T; ++mi) {
+        const int row = mi * MT + r < rows ? mi * MT + r : 0;
+        a_off[mi] = (g * LD * rows + row) * 16;
+    }
+    a_pl = rows * 16;
+    const int b_off = (g * LD * C::ROWS + r) * 16;
+
+    // this wave's chunks of the workgroup's [split per, (split + 1) per)
+    const int total = p * (int)nch;
+    const int w0 = split * a.split_chunks;
+    const int wn = total - w0 < a.split_chunks ? total - w0 : a.split_chunks;
+    const int s0 = (int)((int64_t)wn * kgi / a.kg), s1 = (int)((int64_t)wn * (kgi + 1) / a.kg);
+    const int n = s1 - s0;
+    struct Pos { int kb, cs, j, t, n; };
+    Pos q;
+    {
+        const int s = n > 0 ? w0 + s0 : 0, per_t = Kt * (int)nch;
+        q.t = s / per_t;
+        q.j = (s % per_t) / (int)nch;
+        q.cs = s % (int)nch;
+        q.kb = (cls + K - 1 - q.t) % K + q.j * K;
+        q.n = 0;
+    }
+    Pos qc = q;                                          // FP8: the chunk being multiplied
+    auto advance = [&](Pos &x) {                         // past the last chunk the position stays put
+        if (++x.n >= n) return;
+        if (++x.cs < (int)nch) return;
+        x.cs = 0;
+        if (++x.j < Kt) { x.kb += K; return; }
+        x.j = 0;
+        ++x.t;
+        x.kb = (cls + K - 1 - x.t) % K;
+    };
+
+    struct Set { u32x4 a[NP][T][LD], b[NP][T][LD]; };
+    Set f[C::D];
+    auto load = [&](Set &x) {
+        const uint32_t ch = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)q.kb * nch + (uint32_t)q.cs));
+        advance(q);
+        const uint32_t sa = ch * a_chunk, sb = ch * b_chunk;
+#pragma unroll
+        for (int P = 0; P < NP; ++P)
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int h = 0; h < LD; ++h) {
+                    x.a[P][i][h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                        rsA, a_off[i] + h * a_pl, (int)(sa + P * a_piece), 0));
+                    x.b[P][i][h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                        rsB, b_off + (i * MT + h * C::ROWS) * 16, (int)(sb + P * b_piece), 0));
+                }
+    };
+
+    // FP8: scale tile of each row / column tile (uniform across the wave)
+    int tra[T], trb[T];
+    if constexpr (FAM == FAM_FP8) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int64_t at = gi * a.a_rows + i * MT;
+            int64_t row = (cls + at / a.S_r * K) * a.S_r + at % a.S_r;
+            row = row < a.M ? row : a.M - 1;             // rows past M are never stored
+            tra[i] = (int)(row / FP8_TILE);
+            int64_t col = ntile * C::ROWS + i * MT;
+            col = col < a.N ? col : a.N - 1;
+            trb[i] = (int)(col / FP8_TILE);
+        }
+    }
+
+    Acc acc[T][T];
+#pragma unroll
+    for (int mi = 0; mi < T; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < T; ++ni) acc[mi][ni] = Acc{};
+
+    auto multiply = [&](const Set &x) {
+        if constexpr (FAM == FAM_FP8) {
+            typedef const __attribute__((address_space(4))) int32_t cint;
+            cint *ea = (cint *)a.a_exps;
+            cint *eb = (cint *)a.b_exps;
+            int64_t kk = (int64_t)qc.kb * a.S_k + (int64_t)qc.cs * 64;
+            kk = kk < a.Kd ? kk : a.Kd - 1;              // padding chunks hold zeros
+            advance(qc);
+            const int tc = __builtin_amdgcn_readfirstlane((int)(kk / FP8_TILE));
+            int sa[NP][T], sb[NP][T];
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                const int ta = __builtin_amdgcn_readfirstlane((int)((tra[i] * a.a_tiles_k + tc) * 2));
+                const int tb = __builtin_amdgcn_readfirstlane((int)((trb[i] * a.b_tiles_k + tc) * 2));
+                sa[0][i] = 127 - ea[ta];
+                sb[0][i] = 127 - eb[tb];
+                if constexpr (NP == 2) {
+                    sa[1][i] = sa[0][i] - ea[ta + 1];
+                    sb[1][i] = sb[0][i] - eb[tb + 1];
+                }
+            }
+            auto frag = [](const u32x4 (&w)[LD]) {
+                const u32x4 lo = w[0], hi = w[LD - 1];
+                return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            };
+#pragma unroll
+            for (int mi = 0; mi < T; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < T; ++ni) {
+                    if constexpr (NP == 2) {             // q1 q0', q0 q1', q0 q0': smallest first
+                        acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                            frag(x.a[1][mi]), frag(x.b[0][ni]), acc[mi][ni], 0, 0, 0, sa[1][mi], 0, sb[0][ni]);
+                        acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                            frag(x.a[0][mi]), frag(x.b[1][ni]), acc[mi][ni], 0, 0, 0, sa[0][mi], 0, sb[1][ni]);
+                    }
+                    acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                        frag(x.a[0][mi]), frag(x.b[0][ni]), acc[mi][ni], 0, 0, 0, sa[0][mi], 0, sb[0][ni]);
+                }
+        } else if constexpr (FAM == FAM_F64) {
+            // a lane's 16 bytes are contraction elements 2g, 2g + 1 of the
+            // 8-deep chunk; MFMA t takes element t of A and B alike
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int mi = 0; mi < T; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < T; ++ni) {
+                        const u32x4 av = x.a[0][mi][0], bv = x.b[0][ni][0];
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            __hiloint2double((int)av[2 * t + 1], (int)av[2 * t]),
+                            __hiloint2double((int)bv[2 * t + 1], (int)bv[2 * t]), acc[mi][ni], 0, 0, 0);
+                    }
+        } else {
+            u32x4 bv[NP][T];
+#pragma unroll
+            for (int P = 0; P < NP; ++P)
+#pragma unroll
+                for (int ni = 0; ni < T; ++ni) bv[P][ni] = x.b[P][ni][0];
+#pragma unroll
+            for (int mi = 0; mi < T; ++mi) {
+                u32x4 av[NP];
+#pragma unroll
+                for (int P = 0; P < NP; ++P) av[P] = x.a[P][mi][0];
+                mfma_row<FAM, FORM, T>(acc[mi], av, bv);
+            }
+        }
+    };
+
+    if (n > 0) {
+#pragma unroll
+        for (int d = 0; d < C::D; ++d) load(f[d]);
+        for (int s = 0;;) {
+#pragma unroll
+            for (int d = 0; d < C::D; ++d) {
+                multiply(f[d]);
+                load(f[d]);
+                if (++s >= n) goto done;
+            }
+        }
+    }
+done:
+
+    // the kg sums, added pairwise: waves [h, 2h) hand theirs to waves [0, h)
+    E *buf = (E *)red;
+    for (int h = a.kg >> 1; h >= 1; h >>= 1) {
+        if (kgi >= h && kgi < 2 * h) {
+#pragma unroll
+            for (int mi = 0; mi < T; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < T; ++ni)
+#pragma unroll
+                    for (int e = 0; e < C::NE; ++e)
+                        buf[(((kgi - h) * T * T + mi * T + ni) * C::NE + e) * 64 + lane] = acc[mi][ni][e];
+        }
+        __syncthreads();
+        if (kgi < h) {
+#pragma unroll
+            for (int mi = 0; mi < T; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < T; ++ni)
+#pragma unroll
+                    for (int e = 0; e < C::NE; ++e)
+                        acc[mi][ni][e] += buf[((kgi * T * T + mi * T + ni) * C::NE + e) * 64 + lane];
+        }
+        __syncthreads();
+    }
+    if (kgi != 0) return;
+
+    // epilogue: tile row rho is position gi a_rows + rho of the class's list
+    constexpr bool ROWSCALE = FAM == FAM_F16 && FORM == 2;
+    const int64_t cbase = ntile * C::ROWS + r;
+    int ecol[T];
+#pragma unroll
+    for (int ni = 0; ni < T; ++ni) {
+        ecol[ni] = 0;
+        if constexpr (ROWSCALE)
+            if (cbase + ni * MT < a.N) ecol[ni] = row_scale_exp(((const uint32_t *)a.b_exps)[cbase + ni * MT]);
+    }
+    const bool to_part = a.nsplit > 1;
+    const uint32_t S = (uint32_t)a.S_r, base = (uint32_t)(gi * a.a_rows);
+#pragma unroll
+    for (int mi = 0; mi < T; ++mi)
+#pragma unroll
+        for (int e = 0; e < C::NE; ++e) {
+            const int rho = mi * MT + (FAM == FAM_F64 ? 4 * e + g : (e >> 2) * 8 + g * 4 + (e & 3));
+            const uint32_t at = base + rho, i = at / S;
+            const int64_t row = (int64_t)(cls + i * K) * S + (at - i * S);
+            if (rho >= rows || row >= a.M) continue;
+            int erow = 0;
+            if constexpr (ROWSCALE) erow = row_scale_exp(((const uint32_t *)a.a_exps)[row]);
+            const int64_t ob = to_part ? ((int64_t)split * a.M + row) * a.N + cbase : row * a.ldo + cbase;
+            E *dst = (E *)(to_part ? a.part : a.out) + ob;
+#pragma unroll
+            for (int ni = 0; ni < T; ++ni) {
+                if (cbase + ni * MT >= a.N) continue;
+                if constexpr (ROWSCALE) dst[ni * MT] = ldexpf(acc[mi][ni][e], -(erow + ecol[ni]));
+                else dst[ni * MT] = acc[mi][ni][e];
+            }
+        }
+}
+
+template <int FAM, int FORM, int T>
+static hipError_t launch_wave_t(const WaveArgs &a, hipStream_t st) {
+    typedef WvCfg<FAM, FORM, T> C;
+    const int64_t nwg = (int64_t)a.K * a.n_ug * a.n_tg * a.grp_v * a.grp_t * a.nsplit;
+    const unsigned lds = (unsigned)(a.kg / 2) * T * T * sizeof(typename C::Acc) * 64;   // <= 64 KiB
+    hipEvent_t ts, te;
+    if (take_timed_launch(&ts, &te))
+        hipExtLaunchKernelGGL((wave_kernel<FAM, FORM, T>), dim3((unsigned)nwg), dim3(64 * a.kg), lds, st, ts, te, 0, a);
+    else
+        hipLaunchKernelGGL((wave_kernel<FAM, FORM, T>), dim3((unsigned)nwg), dim3(64 * a.kg), lds, st, a);
+    return hipGetLastError();
+}
+
+// Bytes per chunk row of the packed operands of this kernel.
+int wave_chunk_bytes(int fam) { return fam == FAM_FP8 || fam == FAM_F64 ? 64 : 32; }
+// Tile rows (and columns) with t MFMA tiles per side.
+int wave_tile(int fam, int t) { return t * (fam == FAM_F64 ? 16 : 32); }
+
+hipError_t launch_wave(int fam, int form, int t, const WaveArgs &a, hipStream_t st) {
+#define HS_WV(F, O)                                            \
+    if (fam == F && form == O)                                 \
+        return t == 1 ? launch_wave_t<F, O, 1>(a, st) : launch_wave_t<F, O, 2>(a, st)
+    HS_WV(FAM_F64, 0);
+    HS_WV(FAM_F32, 0);
+    HS_WV(FAM_F16, 0);
+    HS_WV(FAM_F16, 2);
+    HS_WV(FAM_BF16, 0);
+    HS_WV(FAM_BF16, 1);
+    HS_WV(FAM_FP8, 0);
+    HS_WV(FAM_FP8, 1);
+#undef HS_WV
+    return hipErrorInvalidValue;
+}
+
+}  // namespace hs
