@@ -148,10 +148,10 @@ void layout_workspace(Plan *P) {
 // split-BF16 528 / 696 and 4154 / 6310, two-piece FP16 322 / 406 and
 // 2429 / 3427, BF16 124 / 179 and 866 / 1394, FP8 84 / 93 and 533 / 704,
 // refined FP8 161 / 181 and 1183 / 1571.  Left of the line: 1024^3 (16 tiles)
-// FP32 251 / 26, split-BF16 111 / 22, BF16 43 / 13; 5000^3 (400 tiles) FP32
+// FP32 251 / 23, split-BF16 111 / 19, BF16 43 / 11; 5000^3 (400 tiles) FP32
 // 3425 / 1877, refined FP8 507 / 383.  FP64 always takes it (an LDS-tiled
 // 64 x 64 kernel measured 3075 us at 4096^3 against 1852, 400 against 259 at
-// 2048^3, 18.6 against 6.4 at 256^3).
+// 2048^3, 18.6 against 5.8 at 256^3).
 int wave_percent(const FormInfo &f) {
     switch (f.fam) {
         case FAM_F64: return 101;
@@ -164,20 +164,22 @@ int wave_percent(const FormInfo &f) {
 // MFMA tiles per side of the wave kernel's tile, and waves per workgroup.
 // The forms with cheap fragments (FP32, FP64: an MFMA takes 64 cycles for two
 // fragments of 16 bytes a lane) keep small tiles until 900 large ones exist
-// and 4 waves a workgroup until 8192 (FP32 2048^3, 1024 large tiles: 143 us
-// with 4 waves, 195 with 2, 255 with 1, since workgroups of one wave share
-// SIMDs while others idle).  The 16-bit and FP8 forms are bound by fragment
-// reads, which a large tile halves: large from 256 tiles (split: 1024^3 22 us
-// against 24) or 400 (plain: BF16 1100x900x1000, 270 tiles, 14.5 us small
-// against 16.9), and only as many waves as fill the SIMDs.
+// (FP32 1500^3, 576 large tiles: 66 us small, 82 large; 2048^3, 1024: 149 and
+// 139) and 4 waves a workgroup until 8192 (2048^3: 139 us with 4 waves, 193
+// with 2, 250 with 1, since workgroups of one or two waves share SIMDs while
+// others idle).  The 16-bit and FP8 forms are bound by fragment reads, which a
+// large tile halves: large from 256 tiles (1024^3: split-BF16 19 us against
+// 22, FP8 8.9 against 9.1; below, 256 x 512 x 2048, 64 tiles, refined FP8 8.6
+// against 6.9), and only as many waves as fill the SIMDs (BF16 2500^3, 1600
+// tiles: 53 us with one wave, 64 with 4; 1500^3, 576: 25, 22 with 2, 24).
 void wave_shape(const FormInfo &f, int64_t small, int64_t large, int64_t chunks, int *t, int *kg) {
     const bool slow = f.fam == FAM_F64 || f.fam == FAM_F32;
-    *t = large >= (slow ? 900 : f.form ? 256 : 400) ? 2 : 1;
+    *t = large >= (slow ? 900 : 256) ? 2 : 1;
     const int64_t n = *t == 2 ? large : small;
     if (slow) *kg = n >= 8192 ? 1 : 4;
-    else if (*t == 2) *kg = n >= 1500 ? 1 : n >= 512 ? 2 : 4;
-    else *kg = n >= 768 ? 1 : n >= 384 ? 2 : 4;
-    if (n <= 128 && chunks >= 256) *kg = 8;     // long sums on few tiles: 300x320x6000 BF16 15 us against 17
+    else if (*t == 2) *kg = n >= 1024 ? 1 : n >= 512 ? 2 : 4;
+    else *kg = n >= 768 ? 2 : 4;
+    if (n <= 128 && chunks >= 256) *kg = 8;     // long sums on few tiles: 300x320x6000 BF16 13 us against 15
     while (*kg > 1 && chunks < 2 * *kg) *kg /= 2;
 }
 

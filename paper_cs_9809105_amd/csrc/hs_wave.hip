@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "hs_internal.h"
 #include "hs_mfma.h"
 
@@ -24,7 +26,10 @@ namespace hs {
 bool take_timed_launch(hipEvent_t *start, hipEvent_t *stop);   // hs_kernels.hip
 
 // T x T MFMA tiles per wave.  D: register sets of fragments (chunks in
-// flight + 1); a set is 2 T NP LD x 4 registers.
+// flight + 1); a set is 2 T NP LD x 4 registers.  One or two sets more changed
+// nothing beyond noise (split-BF16 1024^3 19.1 against 18.9 us, FP32 2500^3 287
+// against 289): the vector-memory path is the limit there, at about 28 bytes
+// per clock and CU with it busy three quarters of the time.
 template <int FAM, int FORM, int T>
 struct WvCfg {
     static const int NP = Pieces<FAM, FORM>::NP;
@@ -43,39 +48,41 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
     typedef WvCfg<FAM, FORM, T> C;
     typedef typename C::Acc Acc;
     typedef typename std::conditional<FAM == FAM_F64, double, float>::type E;
-    extern __shared__ __attribute__((aligned(16))) uint8_t red[];   // kg / 2 accumulator sets
+    extern __shared__ __attribute__((aligned(32))) uint8_t red[];   // kg > 1: kg accumulator sets
     constexpr int NP = C::NP, MT = C::MT, LD = C::LD;
     const int lane = threadIdx.x & 63;
     const int kgi = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
     // workgroup -> (split, class, group of the class, column tile): each XCD
     // takes a contiguous range, in batches of grp_v groups x grp_t column tiles
-    int64_t bid = blockIdx.x;
+    uint32_t bid = blockIdx.x;
     {
-        const int64_t nwg = gridDim.x, xcd = bid % 8, per = nwg / 8, rem = nwg % 8;
+        const uint32_t nwg = gridDim.x, xcd = bid % 8, per = nwg / 8, rem = nwg % 8;
         bid = xcd * per + (xcd < rem ? xcd : rem) + bid / 8;
     }
-    const int split = (int)(bid / (gridDim.x / a.nsplit));
-    bid %= gridDim.x / a.nsplit;
+    const uint32_t per_split = gridDim.x / (uint32_t)a.nsplit;
+    const int split = (int)(bid / per_split);
+    bid -= split * per_split;
     const int p = a.p, K = a.K, Kt = a.Kt;
-    int64_t ntile, gi;
+    uint32_t ntile, gi;
     int cls;
     {
-        const int64_t t_lo = bid % a.grp_t;  bid /= a.grp_t;
-        const int64_t u_lo = bid % a.grp_v;  bid /= a.grp_v;
-        const int64_t tg = bid % a.n_tg;     bid /= a.n_tg;
-        const int64_t ug = bid % a.n_ug;
-        cls = (int)(bid / a.n_ug);
-        ntile = tg * a.grp_t + t_lo;
-        gi = ug * a.grp_v + u_lo;
+        const uint32_t gt = a.grp_t, gv = a.grp_v, ntg = a.n_tg, nug = a.n_ug;
+        const uint32_t t_lo = bid % gt;  bid /= gt;
+        const uint32_t u_lo = bid % gv;  bid /= gv;
+        const uint32_t tg = bid % ntg;   bid /= ntg;
+        const uint32_t ug = bid % nug;
+        cls = (int)(bid / nug);
+        ntile = tg * gt + t_lo;
+        gi = ug * gv + u_lo;
         if (ntile >= a.n_ntiles || gi >= a.GS) return;   // grid padding
     }
     const int rows = gi + 1 == a.GS ? a.a_last : a.a_rows;        // rows of this group
     const uint32_t nch = (uint32_t)a.nch;
     const uint32_t a_chunk = (uint32_t)(rows * C::CB), b_chunk = (uint32_t)(C::ROWS * C::CB);
     const uint32_t a_piece = (uint32_t)p * nch * a_chunk, b_piece = (uint32_t)p * nch * b_chunk;
-    const __amdgpu_buffer_rsrc_t rsA = packed_rsrc(a.A + cls * a.a_class + gi * a.a_group, a_piece * NP);
-    const __amdgpu_buffer_rsrc_t rsB = packed_rsrc(a.B + ntile * a.b_group, b_piece * NP);
+    const __amdgpu_buffer_rsrc_t rsA = packed_rsrc(a.A + cls * a.a_class + (int64_t)gi * a.a_group, a_piece * NP);
+    const __amdgpu_buffer_rsrc_t rsB = packed_rsrc(a.B + (int64_t)ntile * a.b_group, b_piece * NP);
 
     // Fragment addresses: lane group g = lane / MT holds plane g (FP8: planes
     // 2g, 2g + 1) of row lane % MT.  Tile rows past the group's own re-read
@@ -94,16 +101,17 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
     const int total = p * (int)nch;
     const int w0 = split * a.split_chunks;
     const int wn = total - w0 < a.split_chunks ? total - w0 : a.split_chunks;
-    const int s0 = (int)((int64_t)wn * kgi / a.kg), s1 = (int)((int64_t)wn * (kgi + 1) / a.kg);
-    const int n = s1 - s0;
+    const int each = (wn + a.kg - 1) / a.kg;
+    const int s0 = kgi * each < wn ? kgi * each : wn;
+    const int n = wn - s0 < each ? wn - s0 : each;
     struct Pos { int kb, cs, j, t, n; };
     Pos q;
     {
-        const int s = n > 0 ? w0 + s0 : 0, per_t = Kt * (int)nch;
-        q.t = s / per_t;
-        q.j = (s % per_t) / (int)nch;
-        q.cs = s % (int)nch;
-        q.kb = (cls + K - 1 - q.t) % K + q.j * K;
+        const uint32_t s = n > 0 ? w0 + s0 : 0, blk = s / nch;
+        q.cs = (int)(s - blk * nch);
+        q.t = (int)(blk / (uint32_t)Kt);
+        q.j = (int)(blk - (uint32_t)q.t * Kt);
+        q.kb = (int)((uint32_t)(cls + K - 1 - q.t) % (uint32_t)K) + q.j * K;
         q.n = 0;
     }
     Pos qc = q;                                          // FP8: the chunk being multiplied
@@ -114,7 +122,7 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
         if (++x.j < Kt) { x.kb += K; return; }
         x.j = 0;
         ++x.t;
-        x.kb = (cls + K - 1 - x.t) % K;
+        x.kb = (int)((uint32_t)(cls + K - 1 - x.t) % (uint32_t)K);
     };
 
     struct Set { u32x4 a[NP][T][LD], b[NP][T][LD]; };
@@ -141,11 +149,11 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
     if constexpr (FAM == FAM_FP8) {
 #pragma unroll
         for (int i = 0; i < T; ++i) {
-            const int64_t at = gi * a.a_rows + i * MT;
+            const int64_t at = (int64_t)gi * a.a_rows + i * MT;
             int64_t row = (cls + at / a.S_r * K) * a.S_r + at % a.S_r;
             row = row < a.M ? row : a.M - 1;             // rows past M are never stored
             tra[i] = (int)(row / FP8_TILE);
-            int64_t col = ntile * C::ROWS + i * MT;
+            int64_t col = (int64_t)ntile * C::ROWS + i * MT;
             col = col < a.N ? col : a.N - 1;
             trb[i] = (int)(col / FP8_TILE);
         }
@@ -239,70 +247,72 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
     }
 done:
 
-    // the kg sums, added pairwise: waves [h, 2h) hand theirs to waves [0, h)
-    E *buf = (E *)red;
-    for (int h = a.kg >> 1; h >= 1; h >>= 1) {
-        if (kgi >= h && kgi < 2 * h) {
-#pragma unroll
-            for (int mi = 0; mi < T; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < T; ++ni)
-#pragma unroll
-                    for (int e = 0; e < C::NE; ++e)
-                        buf[(((kgi - h) * T * T + mi * T + ni) * C::NE + e) * 64 + lane] = acc[mi][ni][e];
-        }
-        __syncthreads();
-        if (kgi < h) {
-#pragma unroll
-            for (int mi = 0; mi < T; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < T; ++ni)
-#pragma unroll
-                    for (int e = 0; e < C::NE; ++e)
-                        acc[mi][ni][e] += buf[((kgi * T * T + mi * T + ni) * C::NE + e) * 64 + lane];
-        }
-        __syncthreads();
-    }
-    if (kgi != 0) return;
-
     // epilogue: tile row rho is position gi a_rows + rho of the class's list
     constexpr bool ROWSCALE = FAM == FAM_F16 && FORM == 2;
-    const int64_t cbase = ntile * C::ROWS + r;
-    int ecol[T];
-#pragma unroll
-    for (int ni = 0; ni < T; ++ni) {
-        ecol[ni] = 0;
-        if constexpr (ROWSCALE)
-            if (cbase + ni * MT < a.N) ecol[ni] = row_scale_exp(((const uint32_t *)a.b_exps)[cbase + ni * MT]);
-    }
     const bool to_part = a.nsplit > 1;
-    const uint32_t S = (uint32_t)a.S_r, base = (uint32_t)(gi * a.a_rows);
+    const uint32_t S = (uint32_t)a.S_r, base = (uint32_t)gi * (uint32_t)a.a_rows;
+    const uint32_t *eca = (const uint32_t *)a.a_exps, *ecb = (const uint32_t *)a.b_exps;
+    auto store = [&](int mi, int ni, int e, E v) {
+        const int rho = mi * MT + (FAM == FAM_F64 ? 4 * e + g : (e >> 2) * 8 + g * 4 + (e & 3));
+        const uint32_t at = base + rho, i = at / S;
+        const int64_t row = (int64_t)(cls + i * K) * S + (at - i * S);
+        const int64_t col = (int64_t)ntile * C::ROWS + ni * MT + r;
+        if (rho >= rows || row >= a.M || col >= a.N) return;
+        if constexpr (ROWSCALE) v = ldexpf(v, -(row_scale_exp(eca[row]) + row_scale_exp(ecb[col])));
+        if (to_part) ((E *)a.part)[((int64_t)split * a.M + row) * a.N + col] = v;
+        else ((E *)a.out)[row * a.ldo + col] = v;
+    };
+    if (a.kg == 1) {
+#pragma unroll
+        for (int mi = 0; mi < T; ++mi)
+#pragma unroll
+            for (int e = 0; e < C::NE; ++e)
+#pragma unroll
+                for (int ni = 0; ni < T; ++ni) store(mi, ni, e, acc[mi][ni][e]);
+        return;
+    }
+    // every wave leaves its sums in LDS; then wave w adds and stores quads
+    // w, w + kg, .. of accumulator elements, the waves' sums in their order.
+    // (A pairwise tree after which one wave stored the tile took longer:
+    // split-BF16 256^3 7.9 us against 5.8, 1024^3 22 against 19.)
+    typedef E E4 __attribute__((ext_vector_type(4)));
+    constexpr int NQ = T * T * C::NE / 4;                // quads per lane: (mi, ni, e / 4)
+    E4 *buf = (E4 *)red;
 #pragma unroll
     for (int mi = 0; mi < T; ++mi)
 #pragma unroll
-        for (int e = 0; e < C::NE; ++e) {
-            const int rho = mi * MT + (FAM == FAM_F64 ? 4 * e + g : (e >> 2) * 8 + g * 4 + (e & 3));
-            const uint32_t at = base + rho, i = at / S;
-            const int64_t row = (int64_t)(cls + i * K) * S + (at - i * S);
-            if (rho >= rows || row >= a.M) continue;
-            int erow = 0;
-            if constexpr (ROWSCALE) erow = row_scale_exp(((const uint32_t *)a.a_exps)[row]);
-            const int64_t ob = to_part ? ((int64_t)split * a.M + row) * a.N + cbase : row * a.ldo + cbase;
-            E *dst = (E *)(to_part ? a.part : a.out) + ob;
+        for (int ni = 0; ni < T; ++ni)
 #pragma unroll
-            for (int ni = 0; ni < T; ++ni) {
-                if (cbase + ni * MT >= a.N) continue;
-                if constexpr (ROWSCALE) dst[ni * MT] = ldexpf(acc[mi][ni][e], -(erow + ecol[ni]));
-                else dst[ni * MT] = acc[mi][ni][e];
-            }
-        }
+            for (int h = 0; h < C::NE / 4; ++h)
+                buf[(kgi * NQ + (mi * T + ni) * (C::NE / 4) + h) * 64 + lane] =
+                    E4{acc[mi][ni][4 * h], acc[mi][ni][4 * h + 1], acc[mi][ni][4 * h + 2], acc[mi][ni][4 * h + 3]};
+    __syncthreads();
+    for (int q4 = kgi; q4 < NQ; q4 += a.kg) {
+        E4 v = buf[q4 * 64 + lane];
+        for (int w = 1; w < a.kg; ++w) v += buf[(w * NQ + q4) * 64 + lane];
+        const int h = q4 % (C::NE / 4), tile = q4 / (C::NE / 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) store(tile / T, tile % T, 4 * h + e, v[e]);
+    }
 }
 
 template <int FAM, int FORM, int T>
 static hipError_t launch_wave_t(const WaveArgs &a, hipStream_t st) {
     typedef WvCfg<FAM, FORM, T> C;
     const int64_t nwg = (int64_t)a.K * a.n_ug * a.n_tg * a.grp_v * a.grp_t * a.nsplit;
-    const unsigned lds = (unsigned)(a.kg / 2) * T * T * sizeof(typename C::Acc) * 64;   // <= 64 KiB
+    const unsigned lds = a.kg == 1 ? 0 : (unsigned)a.kg * T * T * sizeof(typename C::Acc) * 64;   // <= 128 KiB
+    // LDS beyond 64 KiB has to be allowed per kernel and device, once
+    static std::atomic<uint64_t> allowed{0};
+    int dev = 0;
+    if (lds > 65536) {
+        if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
+        if (dev >= 64 || !(allowed.load() >> dev & 1)) {
+            hipError_t e = hipFuncSetAttribute((const void *)wave_kernel<FAM, FORM, T>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 131072);
+            if (e != hipSuccess) return e;
+            if (dev < 64) allowed.fetch_or((uint64_t)1 << dev);
+        }
+    }
     hipEvent_t ts, te;
     if (take_timed_launch(&ts, &te))
         hipExtLaunchKernelGGL((wave_kernel<FAM, FORM, T>), dim3((unsigned)nwg), dim3(64 * a.kg), lds, st, ts, te, 0, a);
