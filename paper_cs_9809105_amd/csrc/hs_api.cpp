@@ -16,8 +16,7 @@
 #include "hs_internal.h"
 
 namespace hs {
-hipError_t launch_pack(int kind, int kmajor, const PackArgs &a, hipStream_t st);
-hipError_t launch_pack_mn(int kind, const PackArgs &a, hipStream_t st);
+hipError_t launch_pack(int kind, const PackArgs &a, const PackArgs &b, hipStream_t st);
 hipError_t launch_mm(int fam, int form, const MainArgs &a, hipStream_t st);
 hipError_t launch_wave(int fam, int form, int t, const WaveArgs &a, hipStream_t st);
 int wave_chunk_bytes(int fam);
@@ -26,8 +25,8 @@ hipError_t launch_backshift(int f64, const void *W, int64_t plane, int K, int64_
                             void *Cout, int64_t ldc, hipStream_t st);
 hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t ldc, hipStream_t st);
 hipError_t launch_gemv(int f64, const GemvArgs &a, hipStream_t st);
-hipError_t launch_fp8_exps(const Fp8ExpArgs &a, int64_t tiles, hipStream_t st);
-hipError_t launch_row_amax(const RowAmaxArgs &a, hipStream_t st);
+hipError_t launch_fp8_exps(const Fp8ExpArgs &a, int64_t ta, const Fp8ExpArgs &b, int64_t tb, hipStream_t st);
+hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream_t st);
 void set_timed_launch(hipEvent_t start, hipEvent_t stop);
 bool timed_launch_done();
 hipError_t launch_nbody(int f64, const void *bodies, void *out, const NbodyArgs &a, int kr, hipStream_t st);
@@ -102,8 +101,26 @@ struct Plan {
 const int64_t kCUs = 256;
 
 // Bytes of a packed operand.
-int64_t operand_bytes(const OperandGeom &g) {
-    return g.striped == OPG_CLASSES ? g.K * g.class_bytes : g.n_groups * g.group_bytes;
+int64_t operand_bytes(const OperandGeom &g) { return g.n_groups / g.GS * g.list_bytes; }
+
+// The group geometry that follows from striped, S_r, grp_rows, GS and the
+// contraction: `lists` lists of `rows` rows each.
+void finish_geom(OperandGeom *g, int p, int K, int64_t lists, int64_t rows) {
+    g->n_groups = lists * g->GS;
+    g->row_bytes = (int64_t)p * g->nch * g->chunk_bytes;
+    g->piece_bytes = g->grp_rows * g->row_bytes;
+    g->group_bytes = g->pieces * g->piece_bytes;
+    g->last_rows = g->grp_rows;
+    g->list_bytes = g->GS * g->group_bytes;
+    g->run = g->striped == OPG_TILES ? 0x7fffffffu : (uint32_t)g->S_r;
+    g->runs = 1;
+    g->step = 0;
+    if (g->striped == OPG_CLASSES) {
+        g->last_rows = (int)(rows - (g->GS - 1) * g->grp_rows);
+        g->list_bytes = rows * g->pieces * g->row_bytes;
+        g->runs = (uint32_t)(p / K);
+        g->step = (uint32_t)K;
+    }
 }
 
 // Threads of the pack kernel: one per 16-byte unit; a K-major source is
@@ -205,17 +222,14 @@ void plan_wave(Plan *P) {
     if (wt * 4 > std::numeric_limits<int32_t>::max()) return;   // grid padded in both directions
     const int R = wave_tile(fam, W.wave);
     OperandGeom &a = W.ga, &b = W.gb;
-    a.striped = OPG_CLASSES; a.K = P->K;
+    a.striped = OPG_CLASSES;
     a.grp_rows = (int)std::min<int64_t>(R, L);
-    a.GS = ceil_div(L, a.grp_rows); a.n_groups = P->K * a.GS;
-    a.last_rows = (int)(L - (a.GS - 1) * a.grp_rows);
-    b.grp_rows = R; b.GS = ceil_div(P->N, R); b.n_groups = b.GS;
-    for (OperandGeom *g : {&a, &b}) {
-        g->nch = nch; g->chunk_bytes = CBY;
-        g->piece_bytes = chunks * g->grp_rows * CBY;
-        g->group_bytes = g->pieces * g->piece_bytes;
-    }
-    a.class_bytes = L * a.pieces * chunks * CBY;
+    a.GS = ceil_div(L, a.grp_rows);
+    b.grp_rows = R; b.GS = ceil_div(P->N, R);
+    a.nch = b.nch = nch;
+    a.chunk_bytes = b.chunk_bytes = CBY;
+    finish_geom(&a, P->p, P->K, P->K, L);
+    finish_geom(&b, P->p, P->K, 1, P->N);
     const int64_t kMaxUnits = ((int64_t)1 << 32) - 512;   // 32-bit unit numbers
     if (pack_units(a, 1) > kMaxUnits || pack_units(b, 1) > kMaxUnits) return;
     int64_t ns = std::min<int64_t>({(int64_t)P->nsplit, kCUs / wt, chunks / (16 * W.kg)});
@@ -262,17 +276,15 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
 
     OperandGeom &a = P->ga;
     a.R = M; a.Kd = Kd; a.striped = OPG_STRIPES; a.S_r = S_r; a.grp_rows = MS;
-    a.GS = ceil_div(S_r, MS); a.n_groups = (int64_t)p * a.GS; a.p = p;
+    a.GS = ceil_div(S_r, MS); a.p = p;
     a.S_k = S_k; a.nch = nch; a.chunk_bytes = CBY; a.pieces = NP;
-    a.piece_bytes = (int64_t)p * nch * MS * CBY;
-    a.group_bytes = NP * a.piece_bytes;
+    finish_geom(&a, p, P->K, p, S_r);
 
     OperandGeom &b = P->gb;
     b.R = N; b.Kd = Kd; b.striped = OPG_TILES; b.S_r = 0; b.grp_rows = BNT;
-    b.GS = ceil_div(N, BNT); b.n_groups = b.GS; b.p = p;
+    b.GS = std::max<int64_t>(1, ceil_div(N, BNT)); b.p = p;
     b.S_k = S_k; b.nch = nch; b.chunk_bytes = CBY; b.pieces = NP;
-    b.piece_bytes = (int64_t)p * nch * BNT * CBY;
-    b.group_bytes = NP * b.piece_bytes;
+    finish_geom(&b, p, P->K, 1, N);
 
     // grid (with padding to whole workgroup groups) must fit in 32 bits
     const int64_t nwg = (int64_t)p * a.GS * b.GS * 2 + 64;
@@ -366,19 +378,26 @@ int pack_vec_ok(const Plan &P, const Operand &X) {
     return (X.ld * in % 16 == 0 && aligned(X.ptr, 16) && P.ga.S_k % ue == 0 && P.Kd % ue == 0) ? 1 : 0;
 }
 
-// An MN-major FP32 source goes through pack_mn_kernel (16-byte loads of 4
-// rows, transposed in LDS) when its rows are 16-byte aligned and every
-// 4-row run of a group lies in one stripe.
-bool pack_mn_ok(const Plan &P, const Operand &X, const OperandGeom &g) {
-    if (X.kmajor || X.embed != EMB_NONE) return false;
-    if (P.f.pack != PK_F32 && P.f.pack != PK_SPLIT3 && P.f.pack != PK_FP8 && P.f.pack != PK_SPLIT2F16)
-        return false;
-    return X.ld % 4 == 0 && aligned(X.ptr, 16) && g.grp_rows % 4 == 0 && (g.striped == OPG_TILES || g.S_r % 4 == 0);
+// How an operand's source is read.  An MN-major one goes through LDS (16-byte
+// runs of 4 FP32 or 8 16-bit rows) when its rows are 16-byte aligned and every
+// run of a group lies in one stripe.
+int pack_mode(const Plan &P, const Operand &X, const OperandGeom &g) {
+    if (X.kmajor) return PACK_K;
+    if (X.embed != EMB_NONE || P.f.pack == PK_F64) return PACK_MN;
+    const int rw = 16 / P.f.in_esz;
+    return X.ld % rw == 0 && aligned(X.ptr, 16) && g.grp_rows % rw == 0 && (g.striped == OPG_TILES || g.S_r % rw == 0)
+               ? PACK_MN_LDS : PACK_MN;
 }
 
-hipError_t pack_operand(const Plan &P, const Operand &X, const PackArgs &pa, const OperandGeom &g, hipStream_t st) {
-    if (pack_mn_ok(P, X, g)) return launch_pack_mn(P.f.pack, pa, st);
-    return launch_pack(P.f.pack, X.kmajor, pa, st);
+PackArgs pack_args(const Plan &P, const Operand &X, const OperandGeom &g, void *dst, const int32_t *exps) {
+    PackArgs a{};
+    a.src = X.ptr; a.ld = X.ld; a.g = g; a.dst = dst;
+    a.total_units = pack_units(g, X.kmajor);
+    a.mode = pack_mode(P, X, g);
+    a.vec = pack_vec_ok(P, X);
+    a.exps = exps; a.exp_tiles_k = P.tiles_k; a.refine = P.f.form;
+    a.embed = X.embed;
+    return a;
 }
 
 // 32 workgroups per XCD batch: grp_v class members x grp_t column tiles.
@@ -405,38 +424,23 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
     if (fp8) {   // per-tile exponents of both operands (operand preparation)
         Fp8ExpArgs xa{(const float *)X.ptr, X.ld, X.kmajor, P.M, P.Kd, P.tiles_k, P.f.form, ea};
         Fp8ExpArgs xb{(const float *)Y.ptr, Y.ld, Y.kmajor, P.N, P.Kd, P.tiles_k, P.f.form, eb};
-        if (launch_fp8_exps(xa, P.tiles_ra * P.tiles_k, stream) != hipSuccess ||
-            launch_fp8_exps(xb, P.tiles_rb * P.tiles_k, stream) != hipSuccess)
+        if (launch_fp8_exps(xa, P.tiles_ra * P.tiles_k, xb, P.tiles_rb * P.tiles_k, stream) != hipSuccess)
             return HS_ERR_LAUNCH_FAILED;
     }
     if (P.f.pack == PK_SPLIT2F16) {   // row amaxes of both operands (their scales)
         RowAmaxArgs xa{(const float *)X.ptr, X.ld, X.kmajor, P.M, P.Kd, (uint32_t *)ea, X.embed};
         RowAmaxArgs xb{(const float *)Y.ptr, Y.ld, Y.kmajor, P.N, P.Kd, (uint32_t *)eb, Y.embed};
-        if (launch_row_amax(xa, stream) != hipSuccess || launch_row_amax(xb, stream) != hipSuccess)
-            return HS_ERR_LAUNCH_FAILED;
+        if (launch_row_amax(xa, xb, stream) != hipSuccess) return HS_ERR_LAUNCH_FAILED;
     }
 
-    PackArgs pa{};
-    pa.src = X.ptr; pa.ld = X.ld; pa.g = P.ga; pa.dst = w + P.off_a;
-    pa.total_units = pack_units(P.ga, X.kmajor);
-    pa.vec = pack_vec_ok(P, X);
-    pa.exps = ea; pa.exp_tiles_k = P.tiles_k; pa.refine = P.f.form;
-    pa.embed = X.embed;
-    hipError_t e = pack_operand(P, X, pa, P.ga, stream);
-    if (e != hipSuccess) return HS_ERR_LAUNCH_FAILED;
-    PackArgs pb{};
-    pb.src = Y.ptr; pb.ld = Y.ld; pb.g = P.gb; pb.dst = w + P.off_b;
-    pb.total_units = pack_units(P.gb, Y.kmajor);
-    pb.vec = pack_vec_ok(P, Y);
-    pb.exps = eb; pb.exp_tiles_k = P.tiles_k; pb.refine = P.f.form;
-    pb.embed = Y.embed;
-    e = pack_operand(P, Y, pb, P.gb, stream);
+    hipError_t e = launch_pack(P.f.pack, pack_args(P, X, P.ga, w + P.off_a, ea),
+                               pack_args(P, Y, P.gb, w + P.off_b, eb), stream);
     if (e != hipSuccess) return HS_ERR_LAUNCH_FAILED;
 
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (P.wave) {
         WaveArgs v{};
-        v.A = w + P.off_a; v.a_group = P.ga.group_bytes; v.a_class = P.ga.class_bytes;
+        v.A = w + P.off_a; v.a_group = P.ga.group_bytes; v.a_class = P.ga.list_bytes;
         v.B = w + P.off_b; v.b_group = P.gb.group_bytes;
         v.a_rows = P.ga.grp_rows; v.a_last = P.ga.last_rows; v.GS = P.ga.GS;
         v.a_exps = ea; v.b_exps = eb; v.a_tiles_k = P.tiles_k; v.b_tiles_k = P.tiles_k;

@@ -50,6 +50,7 @@ struct RowAmaxArgs {
     int64_t R, Kd;
     uint32_t *amax;           // [R] float bits of max |x| over the row
     int embed;
+    int vec;                  // 16-byte loads are legal (set by launch_row_amax)
 };
 
 // FP8 scale tiles: 128 x 128 blocks of the logical operand (rows x
@@ -65,45 +66,53 @@ struct Fp8ExpArgs {
     int64_t tiles_k;          // tiles along the contraction
     int refine;
     int32_t *exps;            // [tile_r][tile_k][2]
+    int vec;                  // 16-byte loads are legal (set by launch_fp8_exps)
 };
 
-// How an operand's rows are cut into groups.
-enum OperandGroups : int {
-    OPG_TILES = 0,    // runs of grp_rows rows
-    OPG_STRIPES = 1,  // p stripes of S_r rows, each in GS groups of MS = grp_rows rows
-    OPG_CLASSES = 2   // the stripes of each residue class mod K, one after the other, as one
-                      // list of K~ S_r rows cut into groups of grp_rows (the last one shorter,
-                      // nothing padded): position q of class c is row q mod S_r of stripe
-                      // c + (q / S_r) K.  Group gi of class c starts at c class_bytes +
-                      // gi group_bytes, and its own row count is the stride of its planes.
-};
+// How an operand's rows are cut into groups.  Each kind is a number of lists
+// (one; p stripes; K classes) of GS groups; position q of list c is row
+// (c + (q / run) step) run + q mod run, while q / run < runs:
+//   OPG_TILES    one list of all rows (run past the operand, runs 1)
+//   OPG_STRIPES  stripe c: rows c S_r .. of one stripe (run S_r, runs 1)
+//   OPG_CLASSES  residue class c mod K: its K~ stripes one after the other
+//                (run S_r, runs K~, step K); its last group may be shorter,
+//                nothing is padded
+// Group gi of list c starts at c list_bytes + gi group_bytes, and its own row
+// count is the stride of its planes.
+enum OperandGroups : int { OPG_TILES = 0, OPG_STRIPES = 1, OPG_CLASSES = 2 };
 
 struct OperandGeom {
     int64_t R;        // logical rows
     int64_t Kd;       // contraction length
-    int striped;      // OPG_TILES, OPG_STRIPES or OPG_CLASSES
+    int striped;      // OperandGroups
     int64_t S_r;      // stripe height (striped) -- ceil(R / p)
-    int grp_rows;     // rows per group (MS or BN)
-    int64_t GS;       // groups per stripe, per class, or total groups (tiles)
-    int64_t n_groups; // logical groups (p GS, K GS or GS)
-    int K;            // OPG_CLASSES: residue classes
-    int last_rows;    // OPG_CLASSES: rows of a class's last group (the others have grp_rows)
-    int64_t class_bytes;  // OPG_CLASSES: one class, all its groups
+    int grp_rows;     // rows per group
+    int last_rows;    // rows of a list's last group
+    int64_t GS;       // groups per list
+    int64_t n_groups; // all groups
+    uint32_t run, runs, step;   // the list formula above
+    int64_t list_bytes;
     int p;
     int64_t S_k;      // contraction block length -- ceil(Kd / p)
     int64_t nch;      // chunks per block (padded)
     int chunk_bytes;  // 32 (f64, f32, 16-bit) or 64 (fp8)
     int pieces;       // planes written
-    int64_t piece_bytes;  // one piece of one group: p blocks x nch chunks x grp_rows x chunk_bytes
-    int64_t group_bytes;  // one group, all pieces
+    int64_t row_bytes;    // one piece of one row: p blocks x nch chunks x chunk_bytes
+    int64_t piece_bytes;  // one piece of one group of grp_rows rows
+    int64_t group_bytes;  // that group, all pieces
 };
+
+// How a source is read: along the contraction, across it element by element,
+// or across it in 16-byte runs transposed through LDS.
+enum PackMode : int { PACK_K = 0, PACK_MN = 1, PACK_MN_LDS = 2 };
 
 struct PackArgs {
     const void *src;
     int64_t ld;
     OperandGeom g;
     void *dst;
-    int64_t total_units;     // < 2^31
+    int64_t total_units;     // < 2^32
+    int mode;                // PackMode
     int vec;                 // K-major source: 16-byte vector loads are legal
     const int32_t *exps;     // fp8: tile exponents (Fp8ExpArgs); two-piece FP16:
                              // the rows' amax bits (RowAmaxArgs), as uint32

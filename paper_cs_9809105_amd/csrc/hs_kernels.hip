@@ -3,11 +3,6 @@
 // GPU, with p virtual processors realised as groups of workgroups.
 //
 // Kernels
-//   pack_kernel      operand preparation: copies (or splits, or quantises) a
-//                    row-major operand into the packed tile layout described
-//                    in hs_internal.h; HBM bound.
-//   pack_mn_kernel   the same for an MN-major FP32 source, read as 16-byte
-//                    runs of 4 rows and transposed through LDS.
 //   mm_kernel        the hot loop: one workgroup holds an output tile of
 //                    G stripes of one residue class mod K and is the
 //                    collector of the back-shift (base C = (0,1,..,1)): it
@@ -33,519 +28,6 @@
 #include "hs_mfma.h"
 
 namespace hs {
-
-// ---------------------------------------------------------------------------
-// number formats
-// ---------------------------------------------------------------------------
-// Eight floats -> the 16-byte units of their three BF16 pieces,
-// x = a0 + a1 + a2 with a0 = bf16(x), a1 = bf16(x - a0), a2 = bf16(x - a0 - a1):
-// round to nearest even, two values per conversion instruction
-// (v_cvt_pk_bf16_f32), residuals exact in FP32.  Word j of a unit holds
-// elements 2j (low half) and 2j + 1.  The instruction was compared with a
-// software round-to-nearest-even on 24 million values (random bit patterns,
-// every exponent, exact ties, denormals): no difference.
-DEVI void split3_units(const float (&x)[8], u32x4 &p0, u32x4 &p1, u32x4 &p2) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const f32x2 v = {x[2 * j], x[2 * j + 1]};
-        const uint32_t w0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-        const f32x2 r1 = v - f32x2{__uint_as_float(w0 << 16), __uint_as_float(w0 & 0xffff0000u)};
-        const uint32_t w1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(r1, bf16x2));
-        const f32x2 r2 = r1 - f32x2{__uint_as_float(w1 << 16), __uint_as_float(w1 & 0xffff0000u)};
-        p0[j] = w0;
-        p1[j] = w1;
-        p2[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r2, bf16x2));
-    }
-}
-
-// float -> e4m3 (OCP FP8: 1 sign, 4 exponent bits with bias 7, 3 mantissa
-// bits; largest finite 448, no infinities), round to nearest, ties to even,
-// saturating at 448 (subnormals m * 2^-9, m = 1..7), four values at a time:
-// gfx950's conversion instruction on values clamped to [-448, 448].  The
-// instruction's rounding was compared with a software round-to-nearest-even
-// encoder on every e4m3 value, every midpoint between neighbours and the
-// floats next to each midpoint, both signs, values below the smallest
-// subnormal and 8 million random ones: no difference.  The tests compare
-// the quantisation bit for bit with the oracle's encoder.
-DEVI uint32_t e4m3x4(float x0, float x1, float x2, float x3) {
-    auto c = [](float x) { return fminf(fmaxf(x, -448.0f), 448.0f); };
-    int w = __builtin_amdgcn_cvt_pk_fp8_f32(c(x0), c(x1), 0, false);     // bytes 0, 1
-    w = __builtin_amdgcn_cvt_pk_fp8_f32(c(x2), c(x3), w, true);          // bytes 2, 3
-    return (uint32_t)w;
-}
-// byte B of a word of four e4m3 codes -> float (exact)
-template <int B> DEVI float e4m3_byte_to_f32(uint32_t w) { return __builtin_amdgcn_cvt_f32_fp8((int)w, B); }
-
-// Largest e with amax * 2^e <= 448 (0 for an all-zero tile), clamped so that
-// the block-scale byte 127 - e stays a finite E8M0 value.
-DEVI int fp8_exponent(float amax) {
-    if (!(amax > 0.0f) || !(amax < 3.0e38f)) return 0;
-    int E;
-    const float m = frexpf(amax, &E);                      // amax = m 2^E, m in [0.5, 1)
-    int e = (m <= 0.875f ? 9 : 8) - E;                     // 448 = 0.875 * 2^9
-    return e < -126 ? -126 : (e > 126 ? 126 : e);
-}
-
-// ---------------------------------------------------------------------------
-// pack
-// ---------------------------------------------------------------------------
-// One workgroup per 128 x 128 scale tile: amax of the tile, then (with
-// refinement) amax of the residuals a 2^e - q0, both turned into exponents.
-// The tile is 128 lines of 128 contiguous floats in memory (rows of a
-// K-major source, contraction rows of an MN-major one); each of the 512
-// threads holds 8 float4 of it in registers (one read of the tile), line
-// t * 16 + tid / 32, float4 tid % 32, so a wave reads two 512-byte lines per
-// load.  VEC: rows are 16-byte aligned (ld % 4 == 0, 16-byte aligned base).
-DEVI float wave_max(float m) {
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
-    return m;
-}
-
-template <int VEC>
-__global__ __launch_bounds__(512) void fp8_tile_exp_kernel(Fp8ExpArgs a) {
-    __shared__ float red[2][8];
-    const int64_t tr = blockIdx.x / a.tiles_k, tc = blockIdx.x % a.tiles_k;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    // memory lines (outer index) and contiguous positions (inner index)
-    const int64_t o0 = (a.kmajor ? tr : tc) * FP8_TILE, i0 = (a.kmajor ? tc : tr) * FP8_TILE;
-    const int64_t olim = a.kmajor ? a.R : a.Kd, ilim = a.kmajor ? a.Kd : a.R;
-    const int64_t ib = i0 + (tid & 31) * 4;
-    float4 v[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const int64_t o = o0 + t * 16 + (tid >> 5);
-        const float *q = a.src + o * a.ld + ib;
-        if (VEC && o < olim && ib + 3 < ilim) {
-            v[t] = *(const float4 *)q;
-        } else {
-            const bool ol = o < olim;
-            v[t].x = ol && ib < ilim ? q[0] : 0.f;
-            v[t].y = ol && ib + 1 < ilim ? q[1] : 0.f;
-            v[t].z = ol && ib + 2 < ilim ? q[2] : 0.f;
-            v[t].w = ol && ib + 3 < ilim ? q[3] : 0.f;
-        }
-    }
-    auto block_max = [&](float m, float (&r)[8]) {
-        m = wave_max(m);
-        if ((tid & 63) == 0) r[wave] = m;
-        __syncthreads();
-        float x = r[0];
-#pragma unroll
-        for (int w = 1; w < 8; ++w) x = fmaxf(x, r[w]);
-        return x;
-    };
-    float m = 0.f;
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(v[t].x), fabsf(v[t].y)), fmaxf(fabsf(v[t].z), fabsf(v[t].w))));
-    const float amax = block_max(m, red[0]);
-    const int e = fp8_exponent(amax);
-    int e1 = 0;
-    if (a.refine) {
-        float mr = 0.f;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            // a 2^e is exact; its residual after rounding to e4m3 is exact too
-            const float x0 = ldexpf(v[t].x, e), x1 = ldexpf(v[t].y, e), x2 = ldexpf(v[t].z, e),
-                        x3 = ldexpf(v[t].w, e);
-            const uint32_t q = e4m3x4(x0, x1, x2, x3);
-            mr = fmaxf(mr, fmaxf(fmaxf(fabsf(x0 - e4m3_byte_to_f32<0>(q)), fabsf(x1 - e4m3_byte_to_f32<1>(q))),
-                                 fmaxf(fabsf(x2 - e4m3_byte_to_f32<2>(q)), fabsf(x3 - e4m3_byte_to_f32<3>(q)))));
-        }
-        const float rmax = block_max(mr, red[1]);
-        e1 = rmax > 0.0f ? fp8_exponent(rmax) : 0;
-        if (e1 > 127 - e) e1 = 127 - e;                    // keep 127 - e - e1 >= 0
-        if (e1 < -127 - e) e1 = -127 - e;
-    }
-    if (tid == 0) {
-        a.exps[blockIdx.x * 2] = e;
-        a.exps[blockIdx.x * 2 + 1] = e1;
-    }
-}
-
-// Eight floats of one row -> the 16-byte units of their two FP16 pieces,
-// x' = x 2^e, a0 = f16(x'), a1 = f16(x' - a0): round to nearest even, the
-// residual exact in FP32 (a0 is within a factor 2 of x', or both lie below
-// 2^-14 on the 2^-24 grid).  Word j holds elements 2j (low half), 2j + 1.
-DEVI void split2_f16_units(const float (&x)[8], int e, u32x4 &p0, u32x4 &p1) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const f32x2 v = {ldexpf(x[2 * j], e), ldexpf(x[2 * j + 1], e)};   // exact
-        const f16x2 h0 = __builtin_convertvector(v, f16x2);
-        const f32x2 r = v - __builtin_convertvector(h0, f32x2);
-        p0[j] = __builtin_bit_cast(uint32_t, h0);
-        p1[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
-    }
-}
-
-template <int KIND> struct PackTraits;
-template <> struct PackTraits<PK_F64> { typedef double S; static const int UE = 2; static const int ESZ = 8; static const int NP = 1; };
-template <> struct PackTraits<PK_F32> { typedef float S; static const int UE = 4; static const int ESZ = 4; static const int NP = 1; };
-template <> struct PackTraits<PK_B16> { typedef uint16_t S; static const int UE = 8; static const int ESZ = 2; static const int NP = 1; };
-template <> struct PackTraits<PK_SPLIT3> { typedef float S; static const int UE = 8; static const int ESZ = 2; static const int NP = 3; };
-template <> struct PackTraits<PK_FP8> { typedef float S; static const int UE = 16; static const int ESZ = 1; static const int NP = 2; };
-template <> struct PackTraits<PK_SPLIT2F16> { typedef float S; static const int UE = 8; static const int ESZ = 2; static const int NP = 2; };
-
-// The operand row at position rr of group grp, and whether it exists (rows
-// past a stripe, a class's list or the operand are padding).
-DEVI void group_row(const OperandGeom &g, uint32_t grp, uint32_t rr, int64_t &row, bool &valid) {
-    const int64_t at = (int64_t)(g.striped == OPG_TILES ? grp : grp % (uint32_t)g.GS) * g.grp_rows + rr;
-    if (g.striped == OPG_TILES) {
-        row = at;
-        valid = row < g.R;
-    } else if (g.striped == OPG_STRIPES) {
-        row = (int64_t)(grp / (uint32_t)g.GS) * g.S_r + at;
-        valid = at < g.S_r && row < g.R;
-    } else {
-        const uint32_t S = (uint32_t)g.S_r, i = (uint32_t)at / S;   // at < R + grp_rows
-        row = (int64_t)(grp / (uint32_t)g.GS + i * (uint32_t)g.K) * g.S_r + ((uint32_t)at - i * S);
-        valid = i < (uint32_t)(g.p / g.K) && row < g.R;
-    }
-}
-
-// Write one 16-byte unit (of each piece) of the packed image: row rr of
-// group grp, block kb, chunk ch, plane half, from the unit's values.
-template <int KIND>
-DEVI void pack_emit(const PackArgs &a, uint32_t grp, uint32_t kb, uint32_t ch, uint32_t half, uint32_t rr,
-                    int64_t row, bool rvalid, int64_t kk0, const float *vals_f, const double *vals_d,
-                    const uint16_t *vals_h) {
-    const OperandGeom &g = a.g;
-    const uint32_t nch = (uint32_t)g.nch;
-    int64_t base = (int64_t)grp * g.group_bytes, piece = g.piece_bytes;
-    uint32_t gr = (uint32_t)g.grp_rows;
-    if (g.striped == OPG_CLASSES) {             // the last group of a class has its own row count
-        const uint32_t cls = grp / (uint32_t)g.GS, gi = grp % (uint32_t)g.GS;
-        base = cls * g.class_bytes + gi * g.group_bytes;
-        if (gi + 1 == (uint32_t)g.GS) {
-            gr = (uint32_t)g.last_rows;
-            if (rr >= gr) return;
-            piece = (int64_t)g.p * nch * gr * g.chunk_bytes;
-        }
-    }
-    // chunk = UPR planes of 16 bytes per row: [plane][row][16 bytes]
-    // [group][piece][block][chunk][plane][row][16 bytes]
-    const int64_t inner = ((int64_t)kb * nch + ch) * gr * g.chunk_bytes + ((int64_t)half * gr + rr) * 16;
-    uint8_t *dst = (uint8_t *)a.dst + base + inner;
-    auto put = [&](int64_t at, const u32x4 &w) { *(u32x4 *)(dst + at) = w; };
-    if constexpr (KIND == PK_F64) {
-        put(0, __builtin_bit_cast(u32x4, make_double2(vals_d[0], vals_d[1])));
-    } else if constexpr (KIND == PK_F32) {
-        put(0, u32x4{__float_as_uint(vals_f[0]), __float_as_uint(vals_f[1]), __float_as_uint(vals_f[2]),
-                     __float_as_uint(vals_f[3])});
-    } else if constexpr (KIND == PK_B16) {
-        u32x4 w;
-        w[0] = vals_h[0] | ((uint32_t)vals_h[1] << 16);
-        w[1] = vals_h[2] | ((uint32_t)vals_h[3] << 16);
-        w[2] = vals_h[4] | ((uint32_t)vals_h[5] << 16);
-        w[3] = vals_h[6] | ((uint32_t)vals_h[7] << 16);
-        put(0, w);
-    } else if constexpr (KIND == PK_FP8) {
-        // all 16 elements of the unit lie in one 128 x 128 scale tile
-        int e = 0, e1 = 0;
-        if (rvalid && kk0 < g.Kd) {
-            const int64_t t2 = ((row / FP8_TILE) * a.exp_tiles_k + kk0 / FP8_TILE) * 2;
-            e = a.exps[t2];
-            e1 = a.exps[t2 + 1];
-        }
-        u32x4 w0, w1 = {0, 0, 0, 0};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            float xs[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) xs[i] = ldexpf(vals_f[4 * d + i], e);   // exact
-            w0[d] = e4m3x4(xs[0], xs[1], xs[2], xs[3]);
-            if (a.refine) {
-                // the residual a 2^e - q0 is exact; scaled by 2^e1, rounded again
-                const uint32_t q = w0[d];
-                w1[d] = e4m3x4(ldexpf(xs[0] - e4m3_byte_to_f32<0>(q), e1), ldexpf(xs[1] - e4m3_byte_to_f32<1>(q), e1),
-                               ldexpf(xs[2] - e4m3_byte_to_f32<2>(q), e1), ldexpf(xs[3] - e4m3_byte_to_f32<3>(q), e1));
-            }
-        }
-        put(0, w0);
-        if (a.refine) put(piece, w1);
-    } else if constexpr (KIND == PK_SPLIT2F16) {
-        const int e = rvalid ? row_scale_exp(((const uint32_t *)a.exps)[row]) : 0;
-        u32x4 w0, w1;
-        split2_f16_units(*(const float(*)[8])vals_f, e, w0, w1);
-        put(0, w0);
-        put(piece, w1);
-    } else {   // PK_SPLIT3: a0 = bf16(a), a1 = bf16(a - a0), a2 = bf16(a - a0 - a1)
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = vals_f[e];
-        u32x4 w0, w1, w2;
-        split3_units(x, w0, w1, w2);
-        put(0, w0);
-        put(piece, w1);
-        put(2 * piece, w2);
-    }
-}
-
-// Row amax of the two-piece FP16 split, K-major source: one wave per row,
-// 16-byte loads when VEC (ld % 4 == 0, 16-byte aligned base).  NaNs are
-// skipped (fmaxf); they reach the product through the values themselves.
-template <int VEC>
-__global__ __launch_bounds__(256) void row_amax_k_kernel(RowAmaxArgs a) {
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (row >= a.R) return;
-    const float *q = a.src + (a.embed == EMB_BLOCKS_H ? row >> 1 : row) * a.ld;
-    float m = 0.f;
-    int64_t k = 0;
-    if (VEC) {
-        const int64_t k4 = a.Kd / 4 * 4;
-#pragma unroll 4
-        for (k = lane * 4; k < k4; k += 256) {
-            const float4 v = *(const float4 *)(q + k);
-            m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-        }
-        k = k4;
-    }
-    for (int64_t kk = k + lane; kk < a.Kd; kk += 64) m = fmaxf(m, fabsf(q[kk]));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (lane == 0) a.amax[row] = __float_as_uint(m);
-}
-
-// Row amax, MN-major source (element (kk, c) of the float view at
-// src[kk ld + c]): thread columns (4 per thread when VEC) over a slab of
-// 256 contraction rows, then one atomic max per column into its row (two
-// for EMB_BLOCKS); the host zero-fills amax first.  Workgroup b takes column
-// block b % ncb of slab b / ncb.
-DEVI void amax_into_rows(const RowAmaxArgs &a, int64_t c, float m) {
-    const uint32_t bits = __float_as_uint(m);
-    if (a.embed == EMB_BLOCKS) {
-        atomicMax(a.amax + (c & ~(int64_t)1), bits);
-        atomicMax(a.amax + (c | 1), bits);
-    } else if (a.embed == EMB_TRANS || a.embed == EMB_CONJ) {
-        atomicMax(a.amax + (c >> 1), bits);
-    } else {
-        atomicMax(a.amax + c, bits);
-    }
-}
-
-template <int VEC>
-__global__ __launch_bounds__(256) void row_amax_mn_kernel(RowAmaxArgs a) {
-    constexpr int CW = VEC ? 4 : 1;
-    // the float view's columns and contraction rows
-    const int64_t ncol = (a.embed == EMB_TRANS || a.embed == EMB_CONJ) ? 2 * a.R : a.R;
-    const int64_t nk = a.embed == EMB_NONE ? a.Kd : a.Kd / 2;
-    const int64_t ncb = (ncol + 256 * CW - 1) / (256 * CW);
-    const int64_t r0 = ((int64_t)(blockIdx.x % ncb) * 256 + threadIdx.x) * CW;
-    if (r0 >= ncol) return;
-    const int64_t k0 = (int64_t)(blockIdx.x / ncb) * 256;
-    const int64_t k1 = k0 + 256 < nk ? k0 + 256 : nk;
-    float m[CW];
-#pragma unroll
-    for (int j = 0; j < CW; ++j) m[j] = 0.f;
-    bool done = false;
-    if constexpr (VEC) {
-        if (r0 + 3 < ncol) {
-#pragma unroll 4
-            for (int64_t kk = k0; kk < k1; ++kk) {
-                const float4 v = *(const float4 *)(a.src + kk * a.ld + r0);
-                m[0] = fmaxf(m[0], fabsf(v.x));
-                m[1] = fmaxf(m[1], fabsf(v.y));
-                m[2] = fmaxf(m[2], fabsf(v.z));
-                m[3] = fmaxf(m[3], fabsf(v.w));
-            }
-            done = true;
-        }
-    }
-    if (!done) {
-        for (int64_t kk = k0; kk < k1; ++kk)
-#pragma unroll
-            for (int j = 0; j < CW; ++j)
-                if (r0 + j < ncol) m[j] = fmaxf(m[j], fabsf(a.src[kk * a.ld + r0 + j]));
-    }
-#pragma unroll
-    for (int j = 0; j < CW; ++j)
-        if (r0 + j < ncol) amax_into_rows(a, r0 + j, m[j]);
-}
-
-// An MN-major unit of pack_kernel's numbering: row rr of group grp, block
-// kb, chunk ch, plane half, and where its elements lie in the source.
-struct MnUnit {
-    uint32_t rr, half, ch, kb, grp;
-    int64_t row, kin0, kk0;
-    bool rvalid;
-};
-
-template <int KIND>
-DEVI MnUnit mn_decode(uint32_t u, const OperandGeom &g) {
-    typedef PackTraits<KIND> T;
-    const int KC = g.chunk_bytes / T::ESZ;
-    const uint32_t UPR = (uint32_t)(g.chunk_bytes / 16), nch = (uint32_t)g.nch, p = (uint32_t)g.p;
-    const uint32_t gr = (uint32_t)g.grp_rows;
-    MnUnit d;
-    uint32_t t = u;
-    d.rr = t % gr;    t /= gr;
-    d.half = t % UPR; t /= UPR;
-    d.ch = t % nch;   t /= nch;
-    d.kb = t % p;
-    d.grp = t / p;
-    group_row(g, d.grp, d.rr, d.row, d.rvalid);
-    d.kin0 = (int64_t)d.ch * KC + d.half * T::UE;
-    d.kk0 = (int64_t)d.kb * g.S_k + d.kin0;
-    return d;
-}
-
-// MN-major FP32 source (copy, split and FP8 kinds), transposed through LDS:
-// the workgroup's 256 units (pack_kernel's numbering: rows fastest) are read
-// as 16-byte runs of 4 rows per contraction index -- 64 lanes read 64 runs,
-// one contiguous stretch per group -- into an [element][unit] tile, then each
-// thread packs and writes its own unit as pack_kernel does, so consecutive
-// threads still write consecutive 16-byte rows.  Host: ld % 4 == 0, source
-// 16-byte aligned, grp_rows % 4 == 0, S_r % 4 == 0 for a striped operand;
-// total_units is a multiple of 4.
-template <int KIND>
-__global__ __launch_bounds__(256) void pack_mn_kernel(PackArgs a) {
-    typedef PackTraits<KIND> T;
-    constexpr int UE = T::UE;                   // 4, 8 or 16 elements per unit
-    __shared__ float tile[UE][256];
-    const OperandGeom &g = a.g;
-    const float *src = (const float *)a.src;
-    const uint32_t base = blockIdx.x * 256u;    // host: total_units < 2^31
-#pragma unroll
-    for (int i = 0; i < UE / 4; ++i) {
-        const uint32_t q = threadIdx.x + 256u * i;
-        const uint32_t quad = q % 64, e = q / 64;
-        const uint32_t u = base + quad * 4;     // units u .. u+3: rows rr .. rr+3 of one group
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (u < (uint32_t)a.total_units) {
-            const MnUnit d = mn_decode<KIND>(u, g);
-            const int64_t kk = d.kk0 + e;
-            if (d.kin0 + e < g.S_k && kk < g.Kd) {
-                bool rv[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) rv[r] = d.rvalid && d.row + r < g.R;   // one stripe: S_r % 4 == 0
-                const float *q4 = src + kk * a.ld + d.row;
-                if (rv[0] && rv[1] && rv[2] && rv[3]) {
-                    v = *(const float4 *)q4;
-                } else {
-                    v.x = rv[0] ? q4[0] : 0.f;
-                    v.y = rv[1] ? q4[1] : 0.f;
-                    v.z = rv[2] ? q4[2] : 0.f;
-                    v.w = rv[3] ? q4[3] : 0.f;
-                }
-            }
-        }
-        *(float4 *)&tile[e][quad * 4] = v;
-    }
-    __syncthreads();
-    const uint32_t u = base + threadIdx.x;
-    if (u >= (uint32_t)a.total_units) return;
-    const MnUnit d = mn_decode<KIND>(u, g);
-    float vals_f[UE];
-    double vals_d[1] = {0.0};
-    uint16_t vals_h[1] = {0};
-#pragma unroll
-    for (int e = 0; e < UE; ++e) vals_f[e] = tile[e][threadIdx.x];
-    pack_emit<KIND>(a, d.grp, d.kb, d.ch, d.half, d.rr, d.row, d.rvalid, d.kk0, vals_f, vals_d, vals_h);
-}
-
-// One thread makes one 16-byte unit of the packed image (for the split form,
-// the same unit of each of the three pieces).  Consecutive threads take
-// consecutive rows of one (group, block, chunk, plane), so the packed writes
-// are contiguous; for a row-major (MN-major) source the reads are contiguous
-// too, for a K-major source each thread reads its own 16-32 bytes of a row.
-template <int KIND, int KMAJOR>
-__global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
-    typedef PackTraits<KIND> T;
-    typedef typename T::S S;
-    const OperandGeom &g = a.g;
-    const uint32_t u = blockIdx.x * 256u + threadIdx.x;     // host: total_units < 2^31
-    if (u >= (uint32_t)a.total_units) return;
-    const int KC = g.chunk_bytes / T::ESZ;      // elements per chunk row
-    const uint32_t UPR = (uint32_t)(g.chunk_bytes / 16);  // 16-byte planes per chunk row
-    const uint32_t nch = (uint32_t)g.nch, p = (uint32_t)g.p, gr = (uint32_t)g.grp_rows;
-    uint32_t t = u, rr, half, ch, kb, grp;
-    if (KMAJOR) {
-        // 8 x 8 blocks of (row, unit along the contraction): a wave reads 8
-        // rows x 8 consecutive units (128-256 contiguous bytes per row) and
-        // writes, per (chunk, plane), 8 consecutive rows (128 bytes).
-        const uint32_t nu = nch * UPR;                  // units along one block row
-        const uint32_t nkg = (nu + 7) / 8, nrg = (gr + 7) / 8;
-        const uint32_t uu = t % 8;  t /= 8;
-        const uint32_t rlo = t % 8; t /= 8;
-        const uint32_t kg = t % nkg; t /= nkg;
-        const uint32_t rhi = t % nrg; t /= nrg;
-        kb = t % p;
-        grp = t / p;
-        const uint32_t ku = kg * 8 + uu;
-        rr = rhi * 8 + rlo;
-        if (ku >= nu || rr >= gr) return;
-        ch = ku / UPR;
-        half = ku % UPR;
-    } else {
-        rr = t % gr;    t /= gr;
-        half = t % UPR; t /= UPR;
-        ch = t % nch;   t /= nch;
-        kb = t % p;
-        grp = t / p;
-    }
-    int64_t row;
-    bool rvalid;
-    group_row(g, grp, rr, row, rvalid);
-    const int64_t kin0 = (int64_t)ch * KC + half * T::UE;
-    const int64_t kk0 = (int64_t)kb * g.S_k + kin0;
-    const S *src = (const S *)a.src;
-    float vals_f[T::UE];
-    double vals_d[T::UE];
-    uint16_t vals_h[T::UE];
-    if (KMAJOR && a.vec) {
-        // the unit's elements are contiguous, 16-byte aligned, all valid or all padding
-        const bool ok = rvalid && kin0 < g.S_k && kk0 < g.Kd;
-        const S *q = src + row * a.ld + kk0;
-        constexpr int SB = (int)sizeof(S);             // source element bytes
-        constexpr int NV = T::UE * SB / 16;            // 16-byte loads per unit
-        u32x4 w[NV];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) w[i] = ok ? *(const u32x4 *)(q + i * (16 / SB)) : u32x4{0, 0, 0, 0};
-#pragma unroll
-        for (int e = 0; e < T::UE; ++e) {
-            const int byte = e * SB;
-            const uint32_t word = w[byte / 16][(byte % 16) / 4];
-            if constexpr (KIND == PK_F64) {
-                vals_d[e] = __hiloint2double((int)w[byte / 16][(byte % 16) / 4 + 1], (int)word);
-            } else if constexpr (KIND == PK_B16) {
-                vals_h[e] = (uint16_t)(word >> ((byte % 4) * 8));
-            } else {
-                vals_f[e] = __uint_as_float(word);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < T::UE; ++e) {
-            const int64_t kin = kin0 + e;
-            const int64_t kk = kk0 + e;
-            const bool ok = rvalid && kin < g.S_k && kk < g.Kd;
-            int64_t idx = KMAJOR ? row * a.ld + kk : kk * a.ld + row;
-            bool neg = false;
-            if constexpr (KIND == PK_F32 || KIND == PK_SPLIT3 || KIND == PK_SPLIT2F16) {
-                // complex sources: sr = kk % 2 and c = row % 2 pick the entry
-                // of the 2 x 2 block [[re, im], [-im, re]]
-                const int64_t sr = kk & 1, c = row & 1;
-                if (!KMAJOR && a.embed == EMB_BLOCKS) {
-                    idx = (kk >> 1) * a.ld + (row - c) + (sr ^ c);
-                    neg = sr == 1 && c == 0;
-                } else if (KMAJOR && a.embed == EMB_BLOCKS_H) {
-                    // conj(x): the im entries change sign
-                    idx = (row >> 1) * a.ld + 2 * (kk >> 1) + (sr ^ c);
-                    neg = sr == 0 && c == 1;
-                } else if (!KMAJOR && (a.embed == EMB_CONJ || a.embed == EMB_TRANS)) {
-                    idx = (kk >> 1) * a.ld + 2 * row + sr;
-                    neg = a.embed == EMB_CONJ && sr == 1;
-                }
-            }
-            if constexpr (KIND == PK_F64) vals_d[e] = ok ? (double)src[idx] : 0.0;
-            else if constexpr (KIND == PK_B16) vals_h[e] = ok ? (uint16_t)src[idx] : (uint16_t)0;
-            else vals_f[e] = ok ? (neg ? -(float)src[idx] : (float)src[idx]) : 0.0f;
-        }
-    }
-    pack_emit<KIND>(a, grp, kb, ch, half, rr, row, rvalid, kk0, vals_f, vals_d, vals_h);
-}
 
 // ---------------------------------------------------------------------------
 // the hyper-systolic main loop on MFMA
@@ -1342,29 +824,6 @@ bool timed_launch_done() {
             hipLaunchKernelGGL(KERNEL, GRID, BLOCK, SHM, ST, __VA_ARGS__);                   \
     } while (0)
 
-hipError_t launch_pack(int kind, int kmajor, const PackArgs &a, hipStream_t st) {
-    if (a.total_units == 0) return hipSuccess;
-    const unsigned nb = nblocks(a.total_units);
-#define HS_PACK(K_, M_) hipLaunchKernelGGL((pack_kernel<K_, M_>), dim3(nb), dim3(256), 0, st, a)
-    switch (kind * 2 + (kmajor ? 1 : 0)) {
-        case PK_F64 * 2: HS_PACK(PK_F64, 0); break;
-        case PK_F64 * 2 + 1: HS_PACK(PK_F64, 1); break;
-        case PK_F32 * 2: HS_PACK(PK_F32, 0); break;
-        case PK_F32 * 2 + 1: HS_PACK(PK_F32, 1); break;
-        case PK_B16 * 2: HS_PACK(PK_B16, 0); break;
-        case PK_B16 * 2 + 1: HS_PACK(PK_B16, 1); break;
-        case PK_SPLIT3 * 2: HS_PACK(PK_SPLIT3, 0); break;
-        case PK_SPLIT3 * 2 + 1: HS_PACK(PK_SPLIT3, 1); break;
-        case PK_FP8 * 2: HS_PACK(PK_FP8, 0); break;
-        case PK_FP8 * 2 + 1: HS_PACK(PK_FP8, 1); break;
-        case PK_SPLIT2F16 * 2: HS_PACK(PK_SPLIT2F16, 0); break;
-        case PK_SPLIT2F16 * 2 + 1: HS_PACK(PK_SPLIT2F16, 1); break;
-        default: return hipErrorInvalidValue;
-    }
-#undef HS_PACK
-    return hipGetLastError();
-}
-
 template <int FAM, int FORM, int BM, int BN, int CPS, int WAVES>
 static hipError_t launch_mm_t(const MainArgs &a, hipStream_t st) {
     typedef MmCfg<FAM, FORM, BM, BN, CPS, WAVES> C;
@@ -1413,49 +872,6 @@ hipError_t launch_mm(int fam, int form, const MainArgs &a, hipStream_t st) {
     if (fam == FAM_FP8 && form == 0) return launch_mm_t<FAM_FP8, 0, 256, 256, 2, 8>(a, st);
     if (fam == FAM_FP8 && form == 1) return launch_mm_t<FAM_FP8, 1, 256, 256, 1, 8>(a, st);
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_pack_mn(int kind, const PackArgs &a, hipStream_t st) {
-    if (a.total_units == 0) return hipSuccess;
-    const unsigned nb = nblocks(a.total_units);
-    switch (kind) {
-        case PK_F32: hipLaunchKernelGGL((pack_mn_kernel<PK_F32>), dim3(nb), dim3(256), 0, st, a); break;
-        case PK_SPLIT3: hipLaunchKernelGGL((pack_mn_kernel<PK_SPLIT3>), dim3(nb), dim3(256), 0, st, a); break;
-        case PK_FP8: hipLaunchKernelGGL((pack_mn_kernel<PK_FP8>), dim3(nb), dim3(256), 0, st, a); break;
-        case PK_SPLIT2F16: hipLaunchKernelGGL((pack_mn_kernel<PK_SPLIT2F16>), dim3(nb), dim3(256), 0, st, a); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t ldc, hipStream_t st);
-
-hipError_t launch_row_amax(const RowAmaxArgs &a, hipStream_t st) {
-    if (a.R == 0) return hipSuccess;
-    const bool vec = a.ld % 4 == 0 && ((uintptr_t)a.src % 16) == 0;
-    if (a.kmajor) {
-        const dim3 grid((unsigned)((a.R + 3) / 4));
-        if (vec) hipLaunchKernelGGL(row_amax_k_kernel<1>, grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(row_amax_k_kernel<0>, grid, dim3(256), 0, st, a);
-        return hipGetLastError();
-    }
-    hipError_t e = launch_fill_zero(0, a.amax, 1, a.R, a.R, st);   // zero bits = 0.0f
-    if (e != hipSuccess || a.Kd == 0) return e;
-    // the float view (see RowAmaxArgs); R Kd < 2^34 (the packing limit), so blocks < 2^19
-    const int64_t ncol = (a.embed == EMB_TRANS || a.embed == EMB_CONJ) ? 2 * a.R : a.R;
-    const int64_t nk = a.embed == EMB_NONE ? a.Kd : a.Kd / 2;
-    const int64_t slabs = (nk + 255) / 256;
-    if (vec) hipLaunchKernelGGL(row_amax_mn_kernel<1>, dim3((unsigned)((ncol + 1023) / 1024 * slabs)), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(row_amax_mn_kernel<0>, dim3((unsigned)((ncol + 255) / 256 * slabs)), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_fp8_exps(const Fp8ExpArgs &a, int64_t tiles, hipStream_t st) {
-    if (tiles == 0) return hipSuccess;
-    const bool vec = a.ld % 4 == 0 && ((uintptr_t)a.src % 16) == 0;
-    if (vec) hipLaunchKernelGGL(fp8_tile_exp_kernel<1>, dim3((unsigned)tiles), dim3(512), 0, st, a);
-    else hipLaunchKernelGGL(fp8_tile_exp_kernel<0>, dim3((unsigned)tiles), dim3(512), 0, st, a);
-    return hipGetLastError();
 }
 
 hipError_t launch_backshift(int f64, const void *W, int64_t plane, int K, int64_t M, int64_t N,
