@@ -29,7 +29,7 @@ hipError_t launch_fp8_exps(const Fp8ExpArgs &a, int64_t ta, const Fp8ExpArgs &b,
 hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream_t st);
 void set_timed_launch(hipEvent_t start, hipEvent_t stop);
 bool timed_launch_done();
-hipError_t launch_nbody(int f64, const void *bodies, void *out, const NbodyArgs &a, int kr, hipStream_t st);
+hipError_t launch_nbody(int f64, const void *bodies, void *out, const NbodyArgs &a, hipStream_t st);
 int mm_tile_rows(int fam);
 int mm_tile_cols(int fam);
 int mm_chunks_per_stage(int fam, int form);
@@ -507,13 +507,12 @@ hs_status check_ws(const Plan &P, const void *ws, size_t ws_bytes) {
 
 }  // namespace
 
-// The n-body call's launch shape and workspace.  Replicas per thread (KR):
-// the largest power of two up to 2 that divides K.  Two replicas per thread
-// (56 VGPRs, 8 waves per SIMD) measured fastest at n = 2^18, K = 8:
-// 3.48 T pairs/s against 3.34 (4) and 3.17 (8).
-const int kNbodyKR = 2;
-hs_status nbody_plan(int64_t n, int dtype, hs_schedule s, double eps2, NbodyArgs *a, int *kr,
-                     size_t *ws) {
+// The n-body call's launch shape and workspace.  A workgroup's ss waves split
+// the travelling bodies: 8 (n = 262144, p = 64, K = 8: 18.1 ms; 18.7 with 16),
+// or 16 where there are fewer than 1024 workgroups (n = 10000, p = 8, K = 1,
+// 160 workgroups: 68 us; 79 with 8), and fewer where a wave would get under 16
+// bodies.
+hs_status nbody_plan(int64_t n, int dtype, hs_schedule s, double eps2, NbodyArgs *a, size_t *ws) {
     if (dtype != HS_F32 && dtype != HS_F64) return HS_ERR_NOT_SUPPORTED;
     hs_schedule r;
     HS_TRY(hs_schedule_resolve(s, &r));
@@ -528,12 +527,10 @@ hs_status nbody_plan(int64_t n, int dtype, hs_schedule s, double eps2, NbodyArgs
     a->K = r.K;
     a->Kt = r.p / r.K;
     a->S = (int)std::max<int64_t>(1, ceil_div(n, r.p));
-    a->sub = (int)ceil_div(a->S, 256);
-    int k = kNbodyKR;
-    while (r.K % k != 0) k /= 2;
-    *kr = k;
-    a->tgroups = r.K / k;
-    if ((int64_t)a->p * a->sub * a->tgroups > std::numeric_limits<int32_t>::max()) return HS_ERR_NOT_SUPPORTED;
+    a->sub = (int)ceil_div(a->S, 64);
+    const int64_t gx = (int64_t)a->sub * r.K;         // times 64: at most n + 64 K, below 2^32 threads
+    a->ss = gx * r.p < 1024 ? 16 : 8;
+    while (a->ss > 1 && ((int64_t)a->Kt * a->S < 16 * a->ss || gx * 64 * a->ss >> 32)) a->ss /= 2;
     const size_t esz = f64 ? 8 : 4;
     *ws = r.K > 1 ? align_up((size_t)r.K * (size_t)n * 4 * esz) : 0;
     return HS_OK;
@@ -609,9 +606,8 @@ size_t hs_workspace_size(int op, int64_t m, int64_t n, int64_t k, int dtype, hs_
         }
         case HS_OP_NBODY: {
             NbodyArgs a;
-            int kr;
             size_t ws;
-            if (nbody_plan(m, dtype, s, 0.0, &a, &kr, &ws) != HS_OK) return bad;
+            if (nbody_plan(m, dtype, s, 0.0, &a, &ws) != HS_OK) return bad;
             return ws;
         }
         case HS_OP_BACKWARD: {
@@ -771,9 +767,8 @@ hs_status hs_gemm_backward(int64_t m, int64_t n, int64_t k, int dtype, hs_schedu
 hs_status hs_nbody(int64_t n, int dtype, hs_schedule s, const void *bodies, double eps2, void *out,
                    void *ws, size_t ws_bytes, void *stream) {
     NbodyArgs a;
-    int kr;
     size_t need;
-    HS_TRY(nbody_plan(n, dtype, s, eps2, &a, &kr, &need));
+    HS_TRY(nbody_plan(n, dtype, s, eps2, &a, &need));
     if (n == 0) return HS_OK;
     const int f64 = dtype == HS_F64;
     const size_t row = f64 ? 32 : 16;             // one body: 4 values
@@ -789,7 +784,7 @@ hs_status hs_nbody(int64_t n, int dtype, hs_schedule s, const void *bodies, doub
     void *dst = a.K > 1 ? ws : out;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
-    hipError_t e = launch_nbody(f64, bodies, dst, a, kr, st);
+    hipError_t e = launch_nbody(f64, bodies, dst, a, st);
     if (g_prof) keep_timing(ev0, ev1);
     if (e != hipSuccess) return HS_ERR_LAUNCH_FAILED;
     if (a.K > 1) return launch_status(launch_backshift(f64, ws, 4 * n, a.K, n, 4, out, 4, st));

@@ -222,8 +222,8 @@ struct NbodyArgs {
     double eps2;             // softening, >= 0 (rounded to float for FP32)
     int p, K, Kt;            // ring of p virtual processors, K * Kt == p
     int S;                   // bodies per block, ceil(n / p)
-    int sub;                 // workgroups along one block: ceil(S / 256)
-    int tgroups;             // thread groups per position: K / KR
+    int sub;                 // workgroups along one block: ceil(S / 64)
+    int ss;                  // waves per workgroup: runs of the travelling bodies
 };
 
 }  // namespace hs

@@ -192,3 +192,25 @@ def test_profile_counts_interaction_launches():
     hs.hs_nbody(Xd, 1e-4, p=8, K=1)
     ms, launches = hs.hs_profile_end()
     assert launches == 2 and ms > 0
+
+
+# (n, p, K): blocks one body short of, at and past a slice of 64 and of 128,
+# and travelling runs of 15, 16, 17 (one and two waves), 127 and 128 bodies
+# (four and eight) and many (sixteen; over 1024 workgroups, eight)
+SLICE_CASES = [(63 * 5, 5, 1), (64 * 4, 4, 2), (65 * 3, 3, 3), (127, 1, 1), (128 * 2, 2, 1), (129 * 2, 2, 2),
+               (15, 1, 1), (16 * 2, 2, 2), (17 * 3, 3, 3), (32 * 4, 4, 4), (127 * 3, 3, 3), (9000, 64, 8)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("n,p,K", SLICE_CASES)
+def test_nbody_slices_and_runs(dt, n, p, K):
+    _skip_no_gpu()
+    note("hs_nbody slices", dt, n, p, K)
+    X = inputs.plummer(n, seed=inputs.BASE_SEED + 3 * n + p, unequal=True)
+    Xd, X64 = _stored(X, dt)
+    got = _run(Xd, 0.0, dt, p, K)
+    ref, scale = oracle.nbody(X64, 0.0, with_scale=True)
+    assert np.isfinite(got).all()
+    ea, ep = _errors(got, ref, scale)
+    ta, tp = _bounds(n, K, dt)
+    assert ea <= ta and ep <= tp, (ea, ta, ep, tp)
