@@ -79,6 +79,31 @@ def lib():
     return L
 
 
+_native_mod = None
+
+
+def _native():
+    """The native call path (csrc/hs_torch.cpp), connected to libhs.so.  It
+    makes the ordinary call of each device entry point and returns None for any
+    other, which the functions below then marshal themselves."""
+    global _native_mod
+    if _native_mod is None:
+        L = lib()
+        from . import _hs_torch
+        _hs_torch.connect(*[ctypes.cast(f, ctypes.c_void_p).value for f in
+                            (L.hs_workspace_size, L.hs_gemm, L.hs_gemm_tn, L.hs_gemm_noalloc, L.hs_gemv,
+                             L.hs_gemm_backward, L.hs_nbody)])
+        _native_mod = _hs_torch
+    return _native_mod
+
+
+def _result(r, where):
+    """A native call's answer: the outputs, or the status that it refused with."""
+    if type(r) is int:
+        raise HsError(r, where)
+    return r
+
+
 def _check(status, where):
     if status != HS_OK:
         raise HsError(status, where)
@@ -210,6 +235,10 @@ def _new_out(shape, dt, device, out, name):
 def hs_gemm(A, B, dtype="f32", p=1, K=0, out=None, stream=None):
     """C = A . B on the hyper-systolic schedule (p, K)."""
     dt = _dt(dtype)
+    if stream is None:
+        r = (_native_mod or _native()).product(0, A, B, out, dt, p, K)
+        if r is not None:
+            return _result(r, "hs_gemm")
     a, lda = _mat(A, "A", dt)
     b, ldb = _mat(B, "B", dt)
     m, k = A.shape
@@ -230,6 +259,10 @@ def hs_gemm_noalloc(A, B, out, dtype="f32", p=1, K=0, stream=None):
     """C = A . B into ``out`` without any device allocation (the library's
     static scratch array is the workspace)."""
     dt = _dt(dtype)
+    if stream is None:
+        r = (_native_mod or _native()).product(2, A, B, out, dt, p, K)
+        if r is not None:
+            return _result(r, "hs_gemm_noalloc")
     a, lda = _mat(A, "A", dt)
     b, ldb = _mat(B, "B", dt)
     m, k = A.shape
@@ -246,6 +279,10 @@ def hs_gemm_noalloc(A, B, out, dtype="f32", p=1, K=0, stream=None):
 def hs_gemm_tn(A, B, dtype="f32", p=1, K=0, out=None, stream=None):
     """C = A^T . B with A stored k x m."""
     dt = _dt(dtype)
+    if stream is None:
+        r = (_native_mod or _native()).product(1, A, B, out, dt, p, K)
+        if r is not None:
+            return _result(r, "hs_gemm_tn")
     a, lda = _mat(A, "A", dt)
     b, ldb = _mat(B, "B", dt)
     k, m = A.shape
@@ -264,8 +301,12 @@ def hs_gemm_tn(A, B, dtype="f32", p=1, K=0, out=None, stream=None):
 
 def hs_gemv(A, x, dtype="f32", p=1, K=0, out=None, stream=None):
     """y = A . x."""
-    torch = _torch()
     dt = _dt(dtype)
+    if stream is None:
+        r = (_native_mod or _native()).gemv(A, x, out, dt, p, K)
+        if r is not None:
+            return _result(r, "hs_gemv")
+    torch = _torch()
     a, lda = _mat(A, "A", dt)
     m, n = A.shape
     if x.dim() != 1 or x.shape[0] != n or x.dtype != A.dtype or x.device != A.device:
@@ -283,8 +324,12 @@ def hs_gemv(A, x, dtype="f32", p=1, K=0, out=None, stream=None):
 
 def hs_gemm_backward(A, B, G, dtype="f32", p=1, K=0, need_a=True, need_b=True, stream=None):
     """dA = G . B^T and dB = A^T . G (either may be skipped)."""
-    torch = _torch()
     dt = _dt(dtype)
+    if stream is None:
+        r = (_native_mod or _native()).backward(A, B, G, dt, p, K, bool(need_a), bool(need_b))
+        if r is not None:
+            return _result(r, "hs_gemm_backward")
+    torch = _torch()
     a, lda = _mat(A, "A", dt)
     b, ldb = _mat(B, "B", dt)
     g, ldg = _mat(G, "G", dt)
@@ -319,6 +364,10 @@ def hs_nbody(bodies, eps2=0.0, dtype=None, p=1, K=0, out=None, stream=None):
         if dtype is None:
             raise TypeError("bodies must be float32 or float64")
     dt = _dt(dtype)
+    if stream is None:
+        r = (_native_mod or _native()).nbody(bodies, float(eps2), out, dt, p, K)
+        if r is not None:
+            return _result(r, "hs_nbody")
     if bodies.dtype != getattr(torch, IN_TYPES[dt]) or dt not in (HS_F32, HS_F64):
         raise TypeError("bodies must be float32 (f32) or float64 (f64)")
     n = bodies.shape[0]
