@@ -204,11 +204,12 @@ hs_status hs_gemm_tn(int64_t m, int64_t n, int64_t k, int dtype, hs_schedule s,
                      void *C, int64_t ldc, void *ws, size_t ws_bytes, void *stream);
 
 /* y[m] = A[m, n] . x[n]  (the matrix-vector product of the Abstract and
- * Sec. 8).  Virtual processor v owns row stripe v of A and y; x stripes
- * travel in the order of base A; the K partial vectors are combined in the
- * back-shift order, in FP64 for HS_F32.  dtype: HS_F32, HS_F64 or HS_C32
- * (complex64 A, x, y; lda in complex elements; pointers 8-byte aligned; the
- * real and imaginary partial sums combined in FP64).  lda >= n.
+ * Sec. 8).  Virtual processor v owns row stripe v of A and y.  A block product
+ * of the schedule belongs to one row, and the collector sums a row's K partials
+ * in place: its blocks are visited in storage order, groups of FP32 products
+ * summed in FP64 (HS_F32, HS_C32).  dtype: HS_F32, HS_F64 or HS_C32
+ * (complex64 A, x, y; lda in complex elements; pointers 8-byte aligned).
+ * lda >= n.
  * Needs no workspace (ws may be NULL). */
 hs_status hs_gemv(int64_t m, int64_t n, int dtype, hs_schedule s,
                   const void *A, int64_t lda, const void *x, void *y,

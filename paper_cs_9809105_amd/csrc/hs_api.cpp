@@ -698,12 +698,13 @@ hs_status hs_gemv(int64_t m, int64_t n, int dtype, hs_schedule s,
     GemvArgs g{};
     g.cplx = cplx;
     g.A = A; g.lda = lda; g.x = x; g.y = y; g.m = m; g.n = n;
-    g.p = r.p; g.K = r.K; g.Kt = r.p / r.K;
-    g.S_r = std::max<int64_t>(1, ceil_div(m, r.p));
-    g.S_k = std::max<int64_t>(1, ceil_div(n, r.p));
-    if (g.S_k * r.p >= ((int64_t)1 << 31)) return HS_ERR_NOT_SUPPORTED;   // 32-bit positions
-    const int VE = (f64 || cplx) ? 2 : 4;         // elements per 16-byte load
-    g.vec = (g.S_k % VE == 0 && lda % VE == 0 && n % VE == 0 && aligned(A, 16) && aligned(x, 16)) ? 1 : 0;
+    if (std::max<int64_t>(1, ceil_div(n, r.p)) * r.p >= ((int64_t)1 << 31)) return HS_ERR_NOT_SUPPORTED;   // 32-bit positions
+    // waves per row: one, two for long rows (FP32 2500 x 16384 30 us against 34,
+    // 16384 x 16384 166 against 170; but 3500 x 5000 12.0 against 11.5), four for
+    // few rows that are not short (100 x 10000 4.0 us against 4.4, 250 x 16384
+    // 5.3 against 7.6; but 2500 x 5000 10.2 against 8.9)
+    const int64_t row_bytes = n * (int64_t)esz;
+    g.waves = m < 400 && row_bytes >= 24 * 1024 ? 4 : row_bytes >= 48 * 1024 ? 2 : 1;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
     hipError_t e = launch_gemv(f64, g, st);

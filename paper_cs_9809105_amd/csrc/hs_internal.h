@@ -210,10 +210,8 @@ struct GemvArgs {
     const void *x;
     void *y;
     int64_t m, n;
-    int p, K, Kt;
-    int64_t S_r, S_k;
-    int vec;                 // 1: 16-byte loads are legal
     int cplx;                // 1: complex64 A, x, y (lda in complex elements)
+    int waves;               // waves per row: 1 (4 rows per workgroup) or 4
 };
 
 // All-pairs n-body interaction on the two-array recipe (hs_nbody.hip).

@@ -16,9 +16,8 @@
 //                    accumulator that never leaves the registers.
 //   backshift_kernel the collector of the all-pairs interaction (hs_nbody):
 //                    sums K partial planes in FP64, fixed order.
-//   gemv_kernel      y = A x with the same index map, collector form: one
-//                    wave owns a row and combines the K partial dot products
-//                    in the back-shift order (gemv_c32_kernel: complex64).
+//   gemv_kernel      y = A x, collector form: one wave (or two, four) owns a
+//                    row and sums its K partial dot products in FP64.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -645,143 +644,123 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(OT *Cout, int64_t M, int
 // ---------------------------------------------------------------------------
 // matrix-vector product
 // ---------------------------------------------------------------------------
-template <typename T, int VE>
+// y = A x.  Every block product of the schedule belongs to one row, and the
+// collector adds all K partials of a row in the wave (or the W = 2, 4 waves) that
+// owns it, so the blocks are visited in storage order: one contiguous sweep over
+// the row, VE elements per lane and load (16 bytes, at any element alignment), U
+// loads in flight while the U before them are multiplied.  Each group's FP32 sum
+// (16 products) goes into an FP64 sum, and the lanes' FP64 sums are added at the
+// end.  Bound by reading A once: FP32 8192 x 8192 42.5 us (6.3 TB/s), 3001 x 2999
+// (rows at any alignment) 7.0, 500 x 500 3.9.  Walking the blocks partial by
+// partial in the order of base A, with a cross-lane sum after each, took 46.0, 11.0
+// and (p = 64, K = 8) 45 us; the same walk as one pipelined sequence 42.5, 10.7
+// and 4.4, but 5000 x 10000 44.5 against 35.5 here, for its index arithmetic.
+// CX: complex64 (VE complex elements per load).  NT: A is read past the caches
+// (it is larger than they are, see launch_gemv_t).
+template <typename T, int CX, int NT>
 __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs a) {
-    typedef typename std::conditional<VE == 4, float4, typename std::conditional<VE == 2, double2, T>::type>::type V;
-    constexpr int U = 4;                       // loads in flight per lane
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= a.m) return;
-    const T *Ar = (const T *)a.A + row * a.lda;
+    constexpr int VE = 16 / (int)(sizeof(T) * (1 + CX)), U = 4, NT4 = VE * (1 + CX);
+    typedef T V __attribute__((ext_vector_type(VE * (1 + CX))));
+    typedef V VU __attribute__((aligned(sizeof(T) * (1 + CX))));
+    __shared__ double red[4][2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int W = a.waves, part = wave & (W - 1);   // W a power of two: 4 / W rows per workgroup
+    const int64_t row = ((int64_t)blockIdx.x * 4 + wave) / W;
+    const int64_t n = row < a.m ? a.n : 0;
+    const int start = (part * 64 + lane) * VE, stride = 64 * W * VE;
+    const T *Ar = (const T *)a.A + row * a.lda * (1 + CX);
     const T *x = (const T *)a.x;
-    const int p = a.p, K = a.K;
-    const int rs = (int)(row / a.S_r);
-    const int S_k = (int)a.S_k;                // host: S_k * p fits in 32 bits
-    const int total = a.Kt * S_k;
-    double S = 0.0;
-    for (int l = K - 1; l >= 0; --l) {         // collector: c^{K-1} first
-        const int v = (rs + l) % p;            // the virtual processor holding partial l
-        // lane position: element e of the partial's sequence lies in step
-        // j = e / S_k (block kb = (v + j K) mod p) at offset e mod S_k
-        int e = lane * VE, j = e / S_k, off = e % S_k;
-        int kb = (int)(((int64_t)v + (int64_t)j * K) % p);
-        auto advance = [&]() {
-            e += 64 * VE;
-            off += 64 * VE;
-            while (off >= S_k) {
-                off -= S_k;
-                kb += K;
-                if (kb >= p) kb -= p;
-            }
-        };
-        T acc = 0;
-        while (e < total) {
-            V av[U], xv[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t col = (int64_t)kb * S_k + off;
-                const bool ok = e < total && col < a.n;
-                if (ok) {
-                    av[u] = *(const V *)(Ar + col);
-                    xv[u] = *(const V *)(x + col);
-                } else {
-                    av[u] = V{};
-                    xv[u] = V{};
-                }
-                advance();
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if constexpr (VE == 4) {
-                    acc += av[u].x * xv[u].x;
-                    acc += av[u].y * xv[u].y;
-                    acc += av[u].z * xv[u].z;
-                    acc += av[u].w * xv[u].w;
-                } else if constexpr (VE == 2) {
-                    acc += av[u].x * xv[u].x;
-                    acc += av[u].y * xv[u].y;
-                } else {
-                    acc += av[u] * xv[u];
-                }
-            }
-        }
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-        S = (double)acc + S;
-    }
-    if (lane == 0) ((T *)a.y)[row] = (T)S;
-}
-
-// Complex y = A x (complex64, interleaved re/im): the map and collector
-// order of gemv_kernel, positions in complex elements; each lane keeps the
-// real and imaginary partial sums, combined in FP64 in the back-shift order.
-// VE complex elements per load: 2 (16 bytes) or 1.
-template <int VE>
-__global__ __launch_bounds__(256) void gemv_c32_kernel(GemvArgs a) {
-    typedef typename std::conditional<VE == 2, float4, float2>::type V;
-    constexpr int U = 4;                       // loads in flight per lane
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= a.m) return;
-    const float *Ar = (const float *)a.A + row * a.lda * 2;
-    const float *x = (const float *)a.x;
-    const int p = a.p, K = a.K;
-    const int rs = (int)(row / a.S_r);
-    const int S_k = (int)a.S_k;                // host: S_k * p fits in 32 bits
-    const int total = a.Kt * S_k;
     double Sr = 0.0, Si = 0.0;
-    for (int l = K - 1; l >= 0; --l) {         // collector: c^{K-1} first
-        const int v = (rs + l) % p;
-        int e = lane * VE, j = e / S_k, off = e % S_k;
-        int kb = (int)(((int64_t)v + (int64_t)j * K) % p);
-        auto advance = [&]() {
-            e += 64 * VE;
-            off += 64 * VE;
-            while (off >= S_k) {
-                off -= S_k;
-                kb += K;
-                if (kb >= p) kb -= p;
-            }
-        };
-        float re = 0.f, im = 0.f;
-        while (e < total) {
-            V av[U], xv[U];
+    auto multiply = [&](const V (&av)[U], const V (&xv)[U]) {
+        T re = 0, im = 0;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t col = (int64_t)kb * S_k + off;
-                const bool ok = e < total && col < a.n;
-                if (ok) {
-                    av[u] = *(const V *)(Ar + 2 * col);
-                    xv[u] = *(const V *)(x + 2 * col);
-                } else {
-                    av[u] = V{};
-                    xv[u] = V{};
-                }
-                advance();
-            }
+        for (int u = 0; u < U; ++u) {
+            if constexpr (CX) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                re = __builtin_fmaf(av[u].x, xv[u].x, re);
-                re = __builtin_fmaf(-av[u].y, xv[u].y, re);
-                im = __builtin_fmaf(av[u].x, xv[u].y, im);
-                im = __builtin_fmaf(av[u].y, xv[u].x, im);
-                if constexpr (VE == 2) {
-                    re = __builtin_fmaf(av[u].z, xv[u].z, re);
-                    re = __builtin_fmaf(-av[u].w, xv[u].w, re);
-                    im = __builtin_fmaf(av[u].z, xv[u].w, im);
-                    im = __builtin_fmaf(av[u].w, xv[u].z, im);
+                for (int c = 0; c < VE; ++c) {
+                    const T ar = av[u][2 * c], ai = av[u][2 * c + 1], xr = xv[u][2 * c], xi = xv[u][2 * c + 1];
+                    re = __builtin_fmaf(ar, xr, re);
+                    re = __builtin_fmaf(-ai, xi, re);
+                    im = __builtin_fmaf(ar, xi, im);
+                    im = __builtin_fmaf(ai, xr, im);
                 }
+            } else {
+#pragma unroll
+                for (int c = 0; c < VE; ++c) re += av[u][c] * xv[u][c];
             }
         }
+        Sr += (double)re;
+        if constexpr (CX) Si += (double)im;
+    };
+    // whole groups: every lane's U loads lie inside the row
+    const int groups = (int)(n / ((int64_t)stride * U));
+    auto load = [&](V (&av)[U], V (&xv)[U], int g) {
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            re += __shfl_xor(re, m, 64);
-            im += __shfl_xor(im, m, 64);
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = ((int64_t)(g * U + u) * stride + start) * (1 + CX);
+            if constexpr (NT) av[u] = __builtin_nontemporal_load((const VU *)(Ar + at));
+            else av[u] = *(const VU *)(Ar + at);
+            xv[u] = *(const VU *)(x + at);
         }
-        Sr = (double)re + Sr;
-        Si = (double)im + Si;
+    };
+    V a0[U], x0[U], a1[U], x1[U];
+    if (groups > 0) {
+        load(a0, x0, 0);
+        for (int g = 1;; g += 2) {
+            if (g >= groups) {
+                multiply(a0, x0);
+                break;
+            }
+            load(a1, x1, g);
+            multiply(a0, x0);
+            if (g + 1 >= groups) {
+                multiply(a1, x1);
+                break;
+            }
+            load(a0, x0, g + 1);
+            multiply(a1, x1);
+        }
     }
-    if (lane == 0) ((float2 *)a.y)[row] = make_float2((float)Sr, (float)Si);
+    // the rest of the row: a load may end inside it
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t col = (int64_t)(groups * U + u) * stride + start;
+        a0[u] = V{};
+        x0[u] = V{};
+        if (col + VE <= n) {
+            a0[u] = *(const VU *)(Ar + col * (1 + CX));
+            x0[u] = *(const VU *)(x + col * (1 + CX));
+        } else {
+#pragma unroll
+            for (int c = 0; c < NT4 - (1 + CX); ++c)
+                if (col + c / (1 + CX) < n) {
+                    a0[u][c] = Ar[col * (1 + CX) + c];
+                    x0[u][c] = x[col * (1 + CX) + c];
+                }
+        }
+    }
+    multiply(a0, x0);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        Sr += __shfl_xor(Sr, m, 64);
+        if constexpr (CX) Si += __shfl_xor(Si, m, 64);
+    }
+    if (W > 1) {                               // the row's waves
+        if (lane == 0) {
+            red[wave][0] = Sr;
+            red[wave][1] = Si;
+        }
+        __syncthreads();
+        if (part != 0) return;
+        for (int w = 1; w < W; ++w) {
+            Sr += red[wave + w][0];
+            Si += red[wave + w][1];
+        }
+    }
+    if (lane != 0 || row >= a.m) return;
+    T *y = (T *)a.y + row * (1 + CX);
+    y[0] = (T)Sr;
+    if constexpr (CX) y[1] = (T)Si;
 }
 
 // ---------------------------------------------------------------------------
@@ -906,20 +885,24 @@ hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t l
     return hipGetLastError();
 }
 
-hipError_t launch_gemv(int f64, const GemvArgs &a, hipStream_t st) {
-    const unsigned nb = (unsigned)((a.m + 3) / 4);
-    if (nb == 0) return hipSuccess;
-    if (a.cplx) {
-        if (a.vec) HS_LAUNCH_TIMED((gemv_c32_kernel<2>), dim3(nb), dim3(256), 0, st, a);
-        else HS_LAUNCH_TIMED((gemv_c32_kernel<1>), dim3(nb), dim3(256), 0, st, a);
-    } else if (f64) {
-        if (a.vec) HS_LAUNCH_TIMED((gemv_kernel<double, 2>), dim3(nb), dim3(256), 0, st, a);
-        else HS_LAUNCH_TIMED((gemv_kernel<double, 1>), dim3(nb), dim3(256), 0, st, a);
-    } else {
-        if (a.vec) HS_LAUNCH_TIMED((gemv_kernel<float, 4>), dim3(nb), dim3(256), 0, st, a);
-        else HS_LAUNCH_TIMED((gemv_kernel<float, 1>), dim3(nb), dim3(256), 0, st, a);
-    }
+template <typename T, int CX>
+static hipError_t launch_gemv_t(const GemvArgs &a, hipStream_t st) {
+    const dim3 grid((unsigned)((a.m * a.waves + 3) / 4));
+    // A of 256 MiB or more does not stay in the memory-side cache between
+    // calls; reading it past the caches is then faster (FP32 8192 x 8192, the
+    // kernel before this one: 44.9 us against 48.2; 8192 x 2048, which stays in
+    // that cache: 13.8 against 12.6)
+    if (a.m * a.n * (int64_t)(sizeof(T) * (1 + CX)) >= (int64_t)256 << 20)
+        HS_LAUNCH_TIMED((gemv_kernel<T, CX, 1>), grid, dim3(256), 0, st, a);
+    else
+        HS_LAUNCH_TIMED((gemv_kernel<T, CX, 0>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
+}
+
+hipError_t launch_gemv(int f64, const GemvArgs &a, hipStream_t st) {
+    if (a.m == 0) return hipSuccess;
+    if (a.cplx) return launch_gemv_t<float, 1>(a, st);
+    return f64 ? launch_gemv_t<double, 0>(a, st) : launch_gemv_t<float, 0>(a, st);
 }
 
 }  // namespace hs
