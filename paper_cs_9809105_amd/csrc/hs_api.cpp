@@ -158,25 +158,17 @@ void layout_workspace(Plan *P) {
 // Whether the wave kernel takes the product that *P plans for mm_kernel, and
 // with which tile.  mm_kernel needs its 256 x 256 tiles to fill the chip: a
 // launch of `tiles` of them keeps u = tiles / (256 rounds) of the CUs busy.
-// The wave kernel's 64 x 64 tiles fill it from about a thousand waves on, but
-// every wave reads its own fragments, so at u = 1 it reaches a fraction r of
-// mm_kernel's rate; below u = r it is the faster one.  r, measured at 4096^3
-// to 8192^3 (main kernel, us, mm / wave): FP32 932 / 963 and 7305 / 7389,
-// split-BF16 528 / 696 and 4154 / 6310, two-piece FP16 322 / 406 and
-// 2429 / 3427, BF16 124 / 179 and 866 / 1394, FP8 84 / 93 and 533 / 704,
-// refined FP8 161 / 181 and 1183 / 1571.  Left of the line: 1024^3 (16 tiles)
-// FP32 251 / 23, split-BF16 111 / 19, BF16 43 / 11; 5000^3 (400 tiles) FP32
-// 3425 / 1877, refined FP8 507 / 383.  FP64 always takes it (an LDS-tiled
-// 64 x 64 kernel measured 3075 us at 4096^3 against 1852, 400 against 259 at
-// 2048^3, 18.6 against 5.8 at 256^3).
-int wave_percent(const FormInfo &f) {
-    switch (f.fam) {
-        case FAM_F64: return 101;
-        case FAM_F32: return 95;
-        case FAM_FP8: return f.form ? 78 : 80;
-        default: return f.form == 1 ? 70 : f.form == 2 ? 75 : 65;
-    }
-}
+// The wave kernel's small tiles fill it sooner, but every wave reads its own
+// fragments; below u = r it is the faster one.  Whole calls, n x n x k, us
+// (wave / mm): u = 0.39 (n = 2560, k = 1024): BF16 36 / 43, two-piece FP16
+// 75 / 88, split-BF16 93 / 120, FP8 34 / 43, refined FP8 46 / 57; u = 0.56
+// (n = 3072, k = 1024): 44 / 40, 95 / 90, 125 / 116, 39 / 38, 61 / 54, so r is
+// one half; for FP32, whose fragments are cheap, u = 0.77 (n = 3584): 837 / 955
+// at k = 4096, u = 0.88 (n = 3840): 956 / 961, and 277 / 254 at k = 1024.
+// Far left of the line: 1024^3 FP32 35 / 240, split-BF16 30 / 105.  FP64
+// always takes it (an LDS-tiled 64 x 64 kernel measured 3075 us at 4096^3
+// against 1852, 400 against 259 at 2048^3, 18.6 against 5.8 at 256^3).
+int wave_percent(const FormInfo &f) { return f.fam == FAM_F64 ? 101 : f.fam == FAM_F32 ? 88 : 50; }
 
 // MFMA tiles per side of the wave kernel's tile, and waves per workgroup.
 // The forms with cheap fragments (FP32, FP64: an MFMA takes 64 cycles for two
@@ -219,7 +211,7 @@ void plan_wave(Plan *P) {
     };
     wave_shape(P->f, count(1), count(2), chunks, &W.wave, &W.kg);
     const int64_t wt = count(W.wave);
-    if (wt * 4 > std::numeric_limits<int32_t>::max()) return;   // grid padded in both directions
+    if (wt > (int64_t)1 << 26) return;                    // 32-bit grid in threads
     const int R = wave_tile(fam, W.wave);
     OperandGeom &a = W.ga, &b = W.gb;
     a.striped = OPG_CLASSES;
@@ -303,13 +295,15 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
     if ((int64_t)p * nch >= (int64_t)1 << 31) return HS_ERR_NOT_SUPPORTED;
 
     // Output tiles under the CU count: split each tile's step order over
-    // nsplit workgroups (at most 4, at least 64 stages each), whose sums a
-    // fixed-order FP64 pass adds (the planes below)
+    // nsplit workgroups (at most 4, at least 64 stages each; 128 of the plain
+    // 16-bit and FP8 forms' short ones), whose sums a fixed-order FP64 pass adds
+    // (the planes below)
     {
         const int64_t nstages = (int64_t)p * (nch / CPS);
         const int64_t tiles = (int64_t)P->K * ceil_div(P->Kt, P->G) * a.GS * b.GS;
+        const int64_t least = P->f.form == 0 && (fp8 || P->f.packed_esz == 2) ? 128 : 64;
         int64_t ns = 1;
-        if (tiles > 0 && tiles < kCUs) ns = std::min<int64_t>({4, kCUs / tiles, nstages / 64});
+        if (tiles > 0 && tiles < kCUs) ns = std::min<int64_t>({4, kCUs / tiles, nstages / least});
         if (ns < 2) ns = 1;
         P->split_stages = (int)ceil_div(nstages, ns);
         P->nsplit = (int)ceil_div(nstages, P->split_stages);
@@ -401,14 +395,12 @@ PackArgs pack_args(const Plan &P, const Operand &X, const OperandGeom &g, void *
 }
 
 // 32 workgroups per XCD batch: grp_v class members x grp_t column tiles.
-void batch_shape(int64_t nt, int64_t members, int64_t *grp_v, int64_t *grp_t, int64_t *n_ug, int64_t *n_tg) {
+void batch_shape(int64_t nt, int64_t members, int64_t *grp_v, int64_t *grp_t) {
     int64_t gt = 1;
     while (gt * 2 <= 8 && gt * 2 <= nt) gt *= 2;
     int64_t gv = 32 / gt;
     while (gv > 1 && gv / 2 >= members) gv /= 2;
     *grp_t = gt; *grp_v = gv;
-    *n_tg = ceil_div(nt, gt);
-    *n_ug = ceil_div(members, gv);
 }
 
 // One product through the hyper-systolic path.  The plan must come from
@@ -448,7 +440,7 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
         v.out = out; v.ldo = ldo;
         v.p = P.p; v.K = P.K; v.Kt = P.Kt; v.nch = P.ga.nch; v.S_r = P.ga.S_r;
         v.M = P.M; v.N = P.N; v.n_ntiles = P.gb.GS;
-        batch_shape(P.gb.GS, P.ga.GS, &v.grp_v, &v.grp_t, &v.n_ug, &v.n_tg);
+        batch_shape(P.gb.GS, P.ga.GS, &v.grp_v, &v.grp_t);
         v.kg = P.kg; v.nsplit = P.nsplit; v.split_chunks = P.split_stages; v.part = w + P.off_part;
         if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
         e = launch_wave(P.f.fam, P.f.form, P.wave, v, stream);
@@ -472,7 +464,7 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
     m.nsplit = P.nsplit;
     m.split_stages = P.split_stages;
     m.part = w + P.off_part;
-    batch_shape(P.gb.GS, ceil_div(P.Kt, P.G) * P.ga.GS, &m.grp_v, &m.grp_t, &m.n_ug, &m.n_tg);
+    batch_shape(P.gb.GS, ceil_div(P.Kt, P.G) * P.ga.GS, &m.grp_v, &m.grp_t);
     if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
     e = launch_mm(P.f.fam, P.f.form, m, stream);
     if (g_prof) keep_timing(ev0, ev1);

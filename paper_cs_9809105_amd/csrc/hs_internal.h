@@ -166,7 +166,7 @@ struct MainArgs {
     int64_t M, N;
     int64_t n_ntiles;        // column tiles
     // workgroup groups: grp_v class members x grp_t column tiles run together
-    int64_t grp_v, grp_t, n_ug, n_tg;
+    int64_t grp_v, grp_t;
     // launches with fewer output tiles than CUs: nsplit workgroups per tile,
     // each over split_stages consecutive stages of the step order, their sums
     // in planes [nsplit][M][N] of part (element type as out), summed after
@@ -197,7 +197,7 @@ struct WaveArgs {
     int64_t S_r;
     int64_t M, N;
     int64_t n_ntiles;
-    int64_t grp_v, grp_t, n_ug, n_tg;
+    int64_t grp_v, grp_t;          // members x column tiles that run together
     int kg;                        // waves per workgroup, a power of two
     int nsplit;                    // workgroups per tile (planes of part if > 1)
     int split_chunks;              // chunks each of them walks

@@ -10,8 +10,8 @@
 //                    arrays C^l of Sec. 5.2.2) and forms each on the spot as
 //                    the virtual processor that owns it: K~ steps over the
 //                    travelling blocks kb = (v + jK) mod p (base
-//                    A = (0,K,..,K)), fetched through registers and a
-//                    double-buffered LDS ring, times the pre-shifted static
+//                    A = (0,K,..,K)), loaded straight into a ring of LDS
+//                    stages, times the pre-shifted static
 //                    block (base B = (0,-1,..,-1)), on MFMA, into one
 //                    accumulator that never leaves the registers.
 //   backshift_kernel the collector of the all-pairs interaction (hs_nbody):
@@ -47,13 +47,11 @@ struct MmCfg {
     static const int TM = WM / MT, TN = WN / MT;
     static const int STAGE = A_STAGE + B_STAGE;         // one slot of the LDS ring
     static const int LPS = UA + UB;                     // DMA loads per thread per stage
-    // One wave per SIMD (4 waves of 128 x 128 on the 256 x 256 tile): both
-    // operands through LDS, two slots of static LDS, the stage interleaved
-    // by hand (FP32, plain BF16 and FP16)
-    static const bool W1 = WAVES == 4 && BM == 256;
-    // B fragments straight from memory into registers (32x32 families)
-    static const bool BD = FAM != FAM_FP8 && !W1;
-    static const int LDS_BYTES = W1 ? 0 : 2 * (BD ? A_STAGE : STAGE);   // dynamic LDS: two slots
+    // One wave per SIMD (4 waves of 128 x 128): SLOTS stages in LDS; otherwise
+    // (refined FP8) two waves per SIMD and two slots
+    static const bool W1 = WAVES == 4;
+    static const int SLOTS = W1 ? 3 : 2;
+    static const int LDS_BYTES = SLOTS * STAGE;         // dynamic LDS
 };
 
 // One FP8 pipeline stage from LDS: for every chunk of the stage, the wave's
@@ -103,70 +101,26 @@ DEVI void mm_compute(AccArr &acc, const uint8_t *Ab, const uint8_t *Bb, int lane
     }
 }
 
-// Fragment reads and MFMA tile products of the 32x32 families (FP32,
-// BF16, FP16, split-BF16) for the B-direct stage below.  Lane group g
-// = lane / 32 holds plane g of a chunk row (16 bytes); lane & 31 the row.
-template <int FAM, int FORM, int BM, int BN, int CPS, int WAVES, typename AV>
-DEVI void read_a_frags(AV &av, const uint8_t *Ab, int c, int mi, int lane, int wm) {
-    typedef MmCfg<FAM, FORM, BM, BN, CPS, WAVES> C;
-    const int r32 = lane & 31, g = lane >> 5;
-#pragma unroll
-    for (int P = 0; P < C::NP; ++P)
-        av[P] = *(const u32x4 *)(Ab + (P * CPS + c) * BM * C::CB + g * BM * 16 + (wm * C::WM + mi * 32 + r32) * 16);
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// A packed operand's buffer resource as four scalar registers.
+DEVI i32x4 packed_rsrc_s(const uint8_t *base, uint32_t bytes) {
+    const uint64_t p = (uint64_t)base;
+    return i32x4{__builtin_amdgcn_readfirstlane((int)(uint32_t)p), __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)),
+                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
 }
 
-// One stage of a 32x32 family whose B fragments are already in registers
-// (bq[chunk][piece][column tile]); A fragments come from the LDS slot.
-template <int FAM, int FORM, int BM, int BN, int CPS, int WAVES, typename AccArr, typename BQ>
-DEVI void mm_compute_bd(AccArr &acc, const uint8_t *Ab, const BQ &bq, int lane, int wm) {
-    typedef MmCfg<FAM, FORM, BM, BN, CPS, WAVES> C;
-#pragma unroll
-    for (int c = 0; c < CPS; ++c)
-#pragma unroll
-        for (int mi = 0; mi < C::TM; ++mi) {
-            u32x4 av[C::NP];
-            read_a_frags<FAM, FORM, BM, BN, CPS, WAVES>(av, Ab, c, mi, lane, wm);
-            mfma_row<FAM, FORM, C::TN>(acc[mi], av, bq[c]);
-        }
-}
-
-// Global -> registers for one stage: 16-byte buffer loads of the K static
-// blocks and of the travelling block.  The per-thread part of each address
-// is a constant 32-bit offset; the stage part is wave-uniform (SGPR).
-template <int UA, int UB>
-DEVI void stage_load(u32x4 (&r)[UA + UB], __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb,
-                     const uint32_t (&a_off)[UA], const uint32_t (&b_off)[UB], uint32_t ach, uint32_t bch) {
-#pragma unroll
-    for (int q = 0; q < UA; ++q)
-        r[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_off[q], (int)ach, 0));
-#pragma unroll
-    for (int q = 0; q < UB; ++q)
-        r[UA + q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)b_off[q], (int)bch, 0));
-}
-
-// Registers -> LDS slot.  The LDS image of a stage is
-// [slab = (piece, chunk)][plane][row][16 bytes]: unit ui = tid + NT q lands
-// at ui * 16, so consecutive lanes write consecutive 16 bytes, and the 32
-// lanes of an MFMA lane group later read 512 contiguous bytes of one plane.
-template <int UA, int UB, int A_STAGE, int NT>
-DEVI void stage_store(const u32x4 (&r)[UA + UB], uint8_t *slot, int tid) {
-#pragma unroll
-    for (int q = 0; q < UA; ++q) *(u32x4 *)(slot + (tid + NT * q) * 16) = r[q];
-#pragma unroll
-    for (int q = 0; q < UB; ++q) *(u32x4 *)(slot + A_STAGE + (tid + NT * q) * 16) = r[UA + q];
-}
-
-template <int UA>
-DEVI void stage_load_a(u32x4 (&r)[UA], __amdgpu_buffer_rsrc_t ra, const uint32_t (&a_off)[UA], uint32_t ach) {
-#pragma unroll
-    for (int q = 0; q < UA; ++q)
-        r[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_off[q], (int)ach, 0));
-}
-
-template <int UA, int NT>
-DEVI void stage_store_a(const u32x4 (&r)[UA], uint8_t *slot, int tid) {
-#pragma unroll
-    for (int q = 0; q < UA; ++q) *(u32x4 *)(slot + (tid + NT * q) * 16) = r[q];
+// 64 lanes x 16 bytes from memory straight to LDS bytes lds .. lds + 1023 (one
+// 16-byte unit per lane, in lane order).  As an asm statement, so that the
+// compiler's wait counts do not include it: with the builtin every LDS read
+// that follows waits for all such loads in flight.  The caller waits (vmcnt)
+// before the barrier that publishes the stage, and before the wave ends.  The
+// statement has no register outputs.
+DEVI void load_to_lds(uint32_t lds, int voff, i32x4 rsrc, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory");
 }
 
 template <int FAM, int FORM, int BM, int BN, int CPS, int WAVES>
@@ -185,40 +139,19 @@ void mm_kernel(MainArgs a) {
     // tile).  The tile's rows are sub-group msub of the G stripes
     // r0 + i K (i < ng), r0 = c + sg G K: all of residue class c mod K, so
     // they need the same travelling block at every step (see the step order
-    // below).  Workgroups are dealt to the 8 XCDs round robin; renumber them
-    // so each XCD runs a contiguous range.  Inside it, 32 consecutive
-    // workgroups (one per CU of the XCD) take G_V members of one class times
-    // G_T column tiles, so the XCD's L2 serves each travelling tile to G_V
-    // workgroups and each static tile to G_T of them.
+    // below).
     // With a.nsplit > 1 (launches with fewer output tiles than CUs) the grid
     // holds nsplit copies of the tile grid; copy q walks only stages
     // [q per, (q + 1) per) of the step order and leaves its sums in plane q
     // of a.part (a fixed-order FP64 sum of the planes follows).
-    int64_t bid = blockIdx.x;
-    {
-        const int64_t nwg = gridDim.x, xcd = bid % 8, per = nwg / 8, rem = nwg % 8;
-        bid = xcd * per + (xcd < rem ? xcd : rem) + bid / 8;
-    }
-    const int split = (int)(bid / (gridDim.x / a.nsplit));
-    bid %= gridDim.x / a.nsplit;
     const int p = a.p, K = a.K, Kt = a.Kt, MS = a.MS, G = a.G;
-    int64_t ntile, msub;
-    int c_class, r0, ng;
-    {
-        const int64_t t_lo = bid % a.grp_t;  bid /= a.grp_t;
-        const int64_t u_lo = bid % a.grp_v;  bid /= a.grp_v;
-        const int64_t tg = bid % a.n_tg;     bid /= a.n_tg;
-        const int64_t ug = bid % a.n_ug;
-        c_class = (int)(bid / a.n_ug);
-        ntile = tg * a.grp_t + t_lo;
-        const int64_t u = ug * a.grp_v + u_lo;        // member of the class: (sg, msub)
-        const int nsg = (Kt + G - 1) / G;              // stripe groups per class
-        if (ntile >= a.n_ntiles || u >= (int64_t)nsg * a.GS) return;   // grid padding
-        msub = u % a.GS;
-        const int sg = (int)(u / a.GS);
-        r0 = c_class + sg * G * K;
-        ng = Kt - sg * G < G ? Kt - sg * G : G;        // stripes of this tile
-    }
+    const uint32_t GS = (uint32_t)a.GS;
+    const TileAt at = tile_at(blockIdx.x, gridDim.x, (uint32_t)a.nsplit, (uint32_t)((Kt + G - 1) / G) * GS,
+                              (uint32_t)a.n_ntiles, (uint32_t)a.grp_v, (uint32_t)a.grp_t);
+    const int split = at.split, c_class = at.cls, sg = (int)(at.member / GS);
+    const int64_t ntile = at.col, msub = at.member % GS;
+    const int r0 = c_class + sg * G * K;
+    const int ng = Kt - sg * G < G ? Kt - sg * G : G;      // stripes of this tile
 
     const int64_t nch = a.nch;
     const int spb = (int)(nch / CPS);                   // stages per contraction block
@@ -256,8 +189,11 @@ void mm_kernel(MainArgs a) {
         const int P = slab / CPS, c = slab % CPS;
         b_off[q] = (uint32_t)((int64_t)P * a.b_piece + (int64_t)c * BN * C::CB + (int64_t)within * 16);
     }
-    const __amdgpu_buffer_rsrc_t rsA = packed_rsrc(a.A + ((int64_t)r0 * a.GS + msub) * a.a_group, (uint32_t)a.a_span);
-    const __amdgpu_buffer_rsrc_t rsB = packed_rsrc(a.B + ntile * a.b_group, (uint32_t)a.b_group);
+    const i32x4 rA = packed_rsrc_s(a.A + ((int64_t)r0 * a.GS + msub) * a.a_group, (uint32_t)a.a_span);
+    const i32x4 rB = packed_rsrc_s(a.B + ntile * a.b_group, (uint32_t)a.b_group);
+    // LDS address of this wave's first unit of a stage: unit ui lands at ui * 16
+    const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)ring + wave * 1024);
 
     // The step order.  The collector visits the partials l = K-1, .., 0
     // (t = K-1-l).  Partial l of stripe s is virtual processor v = s + l's
@@ -313,7 +249,7 @@ void mm_kernel(MainArgs a) {
     // across the wave: 127 - e for q0, 127 - e - e1 for q1.
     int sa[CPS][C::NP][C::TM], sb[CPS][C::NP][C::TN];
     Pos pc = start;                                     // stage being multiplied
-    int tra[C::TM], trb[C::TN];
+    uint32_t tra[C::TM], trb[C::TN];                    // index of each tile's scale at contraction tile 0
     if constexpr (FAM == FAM_FP8) {
 #pragma unroll
         for (int mi = 0; mi < C::TM; ++mi) {
@@ -322,41 +258,63 @@ void mm_kernel(MainArgs a) {
             // rows of the groups past ng are never stored: any valid scale
             int64_t row0 = (int64_t)(r0 + (i < ng ? i : 0) * K) * a.S_r + msub * MS + i0;
             row0 = row0 < a.M ? row0 : a.M - 1;
-            tra[mi] = (int)(row0 / FP8_TILE);
+            tra[mi] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(row0 / FP8_TILE * a.a_tiles_k * 2));
         }
 #pragma unroll
         for (int ni = 0; ni < C::TN; ++ni) {
             int64_t col0 = ntile * BN + wn * C::WN + ni * 32;
             col0 = col0 < a.N ? col0 : a.N - 1;
-            trb[ni] = (int)(col0 / FP8_TILE);
+            trb[ni] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(col0 / FP8_TILE * a.b_tiles_k * 2));
         }
     }
+    // a wave's columns lie in one scale tile (128-column waves, or 64 of a 128);
+    // its rows do too where stripes are whole scale tiles
+    static_assert(FAM != FAM_FP8 || (FP8_TILE % C::WN == 0 && BN % FP8_TILE == 0), "one column scale tile per wave");
+    bool one_row_tile = true;
+    if constexpr (FAM == FAM_FP8) {
+#pragma unroll
+        for (int mi = 1; mi < C::TM; ++mi) one_row_tile = one_row_tile && tra[mi] == tra[0];
+    }
+    // index of the stage's scale tile along the contraction, then to the next stage
+    auto scale_col = [&]() -> uint32_t {
+        // positions below p S_k < 2^31 (host); padding chunks hold zeros
+        uint32_t kk = (uint32_t)pc.kb * (uint32_t)a.S_k + (uint32_t)pc.cs * 64u;
+        kk = kk < (uint32_t)a.Kd ? kk : (uint32_t)a.Kd - 1;
+        advance(pc);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(kk / FP8_TILE * 2));
+    };
     auto stage_scales = [&]() {
         if constexpr (FAM == FAM_FP8) {
+            static_assert(CPS == 1, "one 64-deep chunk per stage");
             typedef const __attribute__((address_space(4))) int32_t cint;
             cint *ea = (cint *)a.a_exps;
             cint *eb = (cint *)a.b_exps;
+            const uint32_t tc = scale_col();
+            auto scale = [&](cint *e, int (&s0), int &s1) {
+                s0 = 127 - e[0];
+                if constexpr (C::NP == 2) s1 = s0 - e[1];
+            };
+            int s0 = 0, s1 = 0;
+            scale(eb + trb[0] + tc, s0, s1);
 #pragma unroll
-            for (int c = 0; c < CPS; ++c) {
-                int64_t kk = (int64_t)pc.kb * a.S_k + (int64_t)(pc.cs * CPS + c) * 64;
-                kk = kk < a.Kd ? kk : a.Kd - 1;         // padding chunks hold zeros
-                const int tc = __builtin_amdgcn_readfirstlane((int)(kk / FP8_TILE));
+            for (int ni = 0; ni < C::TN; ++ni) {
+                sb[0][0][ni] = s0;
+                if constexpr (C::NP == 2) sb[0][1][ni] = s1;
+            }
+            scale(ea + tra[0] + tc, s0, s1);
 #pragma unroll
-                for (int mi = 0; mi < C::TM; ++mi) {
-                    const int t = __builtin_amdgcn_readfirstlane((int)((tra[mi] * a.a_tiles_k + tc) * 2));
-                    const int e = ea[t], e1 = ea[t + 1];
-                    sa[c][0][mi] = 127 - e;
-                    if constexpr (C::NP == 2) sa[c][1][mi] = 127 - e - e1;
-                }
+            for (int mi = 0; mi < C::TM; ++mi) {
+                sa[0][0][mi] = s0;
+                if constexpr (C::NP == 2) sa[0][1][mi] = s1;
+            }
+            if (!one_row_tile) {
 #pragma unroll
-                for (int ni = 0; ni < C::TN; ++ni) {
-                    const int t = __builtin_amdgcn_readfirstlane((int)((trb[ni] * a.b_tiles_k + tc) * 2));
-                    const int e = eb[t], e1 = eb[t + 1];
-                    sb[c][0][ni] = 127 - e;
-                    if constexpr (C::NP == 2) sb[c][1][ni] = 127 - e - e1;
+                for (int mi = 1; mi < C::TM; ++mi) {
+                    scale(ea + tra[mi] + tc, s0, s1);
+                    sa[0][0][mi] = s0;
+                    if constexpr (C::NP == 2) sa[0][1][mi] = s1;
                 }
             }
-            advance(pc);
         }
     };
 
@@ -367,230 +325,213 @@ void mm_kernel(MainArgs a) {
         for (int ni = 0; ni < C::TN; ++ni) acc[mi][ni] = Acc{};
 
     uint32_t ach, bch;
-    if constexpr (C::BD) {
-        // The travelling operand skips LDS: each wave loads its own MFMA
-        // fragments of B (the packed layout already is the fragment layout:
-        // 32 lanes read 512 contiguous bytes of one plane) one stage ahead,
-        // into one of two register sets.  Only the static blocks go
-        // through LDS (two slots, loaded two stages ahead, written one
-        // stage ahead, one barrier per stage), which halves the LDS writes
-        // and cuts the LDS reads by a third.
+    if constexpr (C::W1) {
+        // One wave per SIMD; the loads of a stage write LDS themselves, so
+        // neither staging registers nor LDS write instructions exist, and
+        // SLOTS stages fit.  A stage's one barrier sits before its last chunk:
+        // there every wave has read the whole stage s (its slot is free for
+        // stage s + SLOTS) and has waited for its own loads of stage s + 1;
+        // stages s + 2 .. s + SLOTS - 1 stay in flight.  Between MFMA tiles the
+        // wave reads the next chunk's fragments into the other register set and
+        // issues the loads, in an order pinned by sched_barrier.
+        constexpr int NP = C::NP, S = C::SLOTS, LD = C::NPL / 2;   // LD: 16-byte reads per fragment
+        constexpr int RD = (C::TM + C::TN) * NP * LD, TILES = C::TM * C::TN;
+        constexpr int UNR = (S * CPS) % 2 ? 2 * S : S;      // stages per turn of the loop
         const int r32 = lane & 31, g = lane >> 5;
-        const uint32_t b_lane = (uint32_t)((int64_t)g * BN * 16 + (int64_t)(wn * C::WN + r32) * 16);
-        const uint32_t b_piece = (uint32_t)a.b_piece;
-        typedef u32x4 BQ[CPS][C::NP][C::TN];
-        auto load_b = [&](BQ &bq, uint32_t ch) {
-            const uint32_t bst = ch * b_stage;
-#pragma unroll
-            for (int c = 0; c < CPS; ++c)
-#pragma unroll
-                for (int P = 0; P < C::NP; ++P)
-#pragma unroll
-                    for (int ni = 0; ni < C::TN; ++ni)
-                        bq[c][P][ni] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                            rsB, (int)(b_lane + ni * 32 * 16), (int)(bst + P * b_piece + c * BN * C::CB), 0));
+        const int a_rd = g * LD * BM * 16 + (wm * C::WM + r32) * 16;
+        const int b_rd = C::A_STAGE + g * LD * BN * 16 + (wn * C::WN + r32) * 16;
+        u32x4 fa[2][C::TM][NP][LD], fb[2][C::TN][NP][LD];
+        // read i of a chunk: A tile 0, the B tiles, the other A tiles
+        auto rd = [&](int set, const uint8_t *sl, int c, int i) {
+            const int h = i % LD, P = i / LD % NP, k = i / LD / NP;
+            if (k >= 1 && k <= C::TN)
+                fb[set][k - 1][P][h] =
+                    *(const u32x4 *)(sl + b_rd + (P * CPS + c) * BN * C::CB + h * BN * 16 + (k - 1) * 32 * 16);
+            else {
+                const int mi = k == 0 ? 0 : k - C::TN;
+                fa[set][mi][P][h] = *(const u32x4 *)(sl + a_rd + (P * CPS + c) * BM * C::CB + h * BM * 16 + mi * 32 * 16);
+            }
         };
-        u32x4 r0s[C::UA], r1s[C::UA];
-        BQ q0, q1;
-        Pos pb = start;
-        fetch_offsets(ach, bch);
-        stage_load_a<C::UA>(r0s, rsA, a_off, ach);
-        fetch_offsets(ach, bch);
-        stage_load_a<C::UA>(r1s, rsA, a_off, ach);
-        load_b(q0, next_chunk(pb));
-        stage_store_a<C::UA, C::NT>(r0s, ring, tid);
-        __syncthreads();
-#define HS_PIPE_STEP(RLOAD, RSTORE, QUSE, QLOAD)                                               \
-    {                                                                                          \
-        const int slot = (int)(s & 1);                                                         \
-        fetch_offsets(ach, bch);                                                               \
-        stage_load_a<C::UA>(RLOAD, rsA, a_off, ach);                                           \
-        load_b(QLOAD, next_chunk(pb));                                                         \
-        stage_store_a<C::UA, C::NT>(RSTORE, ring + (slot ^ 1) * C::A_STAGE, tid);              \
-        __builtin_amdgcn_sched_barrier(0);                                                     \
-        mm_compute_bd<FAM, FORM, BM, BN, CPS, WAVES>(acc, ring + slot * C::A_STAGE, QUSE, lane, wm); \
-        __syncthreads();                                                                       \
-        if (++s >= nstages) break;                                                             \
-    }
-        for (int s = 0; s < nstages;) {
-            HS_PIPE_STEP(r0s, r1s, q0, q1)
-            HS_PIPE_STEP(r1s, r0s, q1, q0)
+        // FP8: exponents of the next stage's scale tiles (na, nb) and block scales
+        // of the stage being multiplied (ca, cb).  The scalar loads are issued
+        // among one stage's MFMAs and first used right after the next barrier,
+        // where no LDS read is in flight that would have to be waited for too.
+        int na[C::TM], nb = 0, ca[C::TM] = {}, cb = 0;
+        auto next_scales = [&]() {
+            if constexpr (FAM == FAM_FP8) {
+                typedef const __attribute__((address_space(4))) int32_t cint;
+                const uint32_t tc = scale_col();
+                nb = ((cint *)a.b_exps)[trb[0] + tc];
+                na[0] = ((cint *)a.a_exps)[tra[0] + tc];
+                if (!one_row_tile) {
+#pragma unroll
+                    for (int i = 1; i < C::TM; ++i) na[i] = ((cint *)a.a_exps)[tra[i] + tc];
+                }
+            }
+        };
+        auto use_scales = [&]() {
+            if constexpr (FAM == FAM_FP8) {
+                static_assert(FORM == 0 && CPS == 1, "one scale per tile and stage");
+                cb = 127 - nb;
+#pragma unroll
+                for (int i = 0; i < C::TM; ++i) ca[i] = 127 - na[0];
+                if (!one_row_tile) {
+#pragma unroll
+                    for (int i = 1; i < C::TM; ++i) ca[i] = 127 - na[i];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto ld = [&](int slot, int i) {                    // load i of a stage: LPS of 4 KiB, 1 KiB per wave
+            const uint32_t at = lds0 + (uint32_t)(slot * C::STAGE + (i < C::UA ? i : i - C::UA) * C::NT * 16 +
+                                                  (i < C::UA ? 0 : C::A_STAGE));
+            if (i < C::UA) load_to_lds(at, (int)a_off[i < C::UA ? i : 0], rA, ach);
+            else load_to_lds(at, (int)b_off[i < C::UA ? 0 : i - C::UA], rB, bch);
+        };
+        constexpr int FIRST = 2;                            // MFMA tile after which a chunk's loads start
+        // one chunk from register set `set`; meanwhile read chunk c of slot sl
+        // into the other set and issue loads [l0, l1) of a stage into `slot`
+        auto chunk = [&](int set, const uint8_t *sl, int c, int slot, int l0, int l1, bool last) {
+#pragma unroll
+            for (int t = 0; t < TILES; ++t) {
+                const int mi = t / C::TN, ni = t % C::TN;
+                if constexpr (FAM == FAM_FP8) {
+                    auto frag = [](const u32x4 (&w)[LD]) {
+                        const u32x4 lo = w[0], hi = w[LD - 1];
+                        return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
+                                     (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+                    };
+                    acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                        frag(fa[set][mi][0]), frag(fb[set][ni][0]), acc[mi][ni], 0, 0, 0, ca[mi], 0, cb);
+                } else {
+                    u32x4 av[NP], bv[NP][1];
+#pragma unroll
+                    for (int P = 0; P < NP; ++P) {
+                        av[P] = fa[set][mi][P][0];
+                        bv[P][0] = fb[set][ni][P][0];
+                    }
+                    Acc row[1] = {acc[mi][ni]};
+                    mfma_row<FAM, FORM, 1>(row, av, bv);
+                    acc[mi][ni] = row[0];
+                }
+#pragma unroll
+                for (int i = 0; i < RD; ++i)
+                    if (i * TILES / RD == t) rd(set ^ 1, sl, c, i);
+#pragma unroll
+                for (int i = 0; i < C::LPS; ++i)
+                    if (i >= l0 && i < l1 && FIRST + (i - l0) * (TILES - FIRST) / (l1 - l0) == t) ld(slot, i);
+                __builtin_amdgcn_sched_barrier(0);
+                // scalar work of the next stage, while MFMAs run
+                if (last && t == 0) fetch_offsets(ach, bch);
+                if (last && t == 2) next_scales();
+            }
+        };
+        // a stage's loads: an equal share in its predecessor's last chunk (right
+        // after the slot is free) and in each chunk before the next barrier
+        constexpr int SH = C::LPS / CPS;
+        static_assert(SH * CPS == C::LPS && (S - 2) * C::LPS < 64, "load shares, vmcnt range");
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            fetch_offsets(ach, bch);
+#pragma unroll
+            for (int i = 0; i < (q + 1 < S ? C::LPS : SH); ++i) ld(q, i);
         }
-#undef HS_PIPE_STEP
-    } else if constexpr (C::W1) {
-        // One wave per SIMD, so nothing else on the SIMD hides a wait: the
-        // stage is laid out by hand.  Each LDS slot is a static array of
-        // its own, which lets the compiler place the reads of one slot
-        // between the writes to the other.  The one barrier per stage sits
-        // before its last chunk: until then the wave multiplies chunk c
-        // (fragments already in registers) while it reads chunk c + 1,
-        // issues the loads of stage s + 2 and writes stage s + 1 (loaded a
-        // stage earlier) into the other slot; after it the wave multiplies
-        // the last chunk while it reads chunk 0 of stage s + 1 from the other
-        // slot.  A slot is rewritten only after the barrier that follows its
-        // last read.
-        static_assert(CPS >= 2, "at least two chunks per stage");
-        __shared__ __attribute__((aligned(16))) uint8_t slot0[C::STAGE];
-        __shared__ __attribute__((aligned(16))) uint8_t slot1[C::STAGE];
-        u32x4 r0s[C::LPS], r1s[C::LPS];
-        const int r32 = lane & 31, g = lane >> 5;
-        const int a_rd = g * BM * 16 + (wm * C::WM + r32) * 16;
-        const int b_rd = C::A_STAGE + g * BN * 16 + (wn * C::WN + r32) * 16;
-        u32x4 fa0[C::TM], fb0[C::TN], fa1[C::TM], fb1[C::TN];
-        auto read_chunk = [&](const uint8_t *sl, int c, u32x4 (&fa)[C::TM], u32x4 (&fb)[C::TN]) {
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"((S - 2) * C::LPS + SH) : "memory");
 #pragma unroll
-            for (int ni = 0; ni < C::TN; ++ni) fb[ni] = *(const u32x4 *)(sl + b_rd + c * BN * C::CB + ni * 32 * 16);
+        for (int i = 0; i < RD; ++i) rd(0, ring, 0, i);
+        next_scales();
+        for (int s = 0;;) {
 #pragma unroll
-            for (int mi = 0; mi < C::TM; ++mi) fa[mi] = *(const u32x4 *)(sl + a_rd + c * BM * C::CB + mi * 32 * 16);
-        };
-        auto mfma_chunk = [&](const u32x4 (&fa)[C::TM], const u32x4 (&fb)[C::TN]) {
+            for (int u = 0; u < UNR; ++u) {
+                const uint8_t *cur = ring + (u % S) * C::STAGE, *nxt = ring + ((u + 1) % S) * C::STAGE;
 #pragma unroll
-            for (int mi = 0; mi < C::TM; ++mi) {
-                u32x4 av[1] = {fa[mi]};
-                u32x4 bv[1][C::TN];
-#pragma unroll
-                for (int ni = 0; ni < C::TN; ++ni) bv[0][ni] = fb[ni];
-                mfma_row<FAM, FORM, C::TN>(acc[mi], av, bv);
+                for (int c = 0; c + 1 < CPS; ++c)
+                    chunk((u * CPS + c) & 1, cur, c + 1, (u + S - 1) % S, (c + 1) * SH, (c + 2) * SH, false);
+                // this wave has read all of stage s and its share of stage s + 1 has landed
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((S - 2) * C::LPS) : "memory");
+                use_scales();
+                chunk((u * CPS + CPS - 1) & 1, nxt, 0, u % S, 0, SH, true);
+                if (++s >= nstages) goto dma_done;
             }
-        };
-        fetch_offsets(ach, bch);
-        stage_load<C::UA, C::UB>(r0s, rsA, rsB, a_off, b_off, ach, bch);
-        fetch_offsets(ach, bch);
-        stage_load<C::UA, C::UB>(r1s, rsA, rsB, a_off, b_off, ach, bch);
-        stage_store<C::UA, C::UB, C::A_STAGE, C::NT>(r0s, slot0, tid);
-        __syncthreads();
-        read_chunk(slot0, 0, fa0, fb0);
-        // sched_group_barrier masks: 0x008 MFMA, 0x020 global load, 0x100
-        // LDS read, 0x200 LDS write.  A chunk has W1_RD fragment reads and
-        // W1_PER MFMAs per read (2 for BF16/FP16, 8 for FP32's 32x32x2).
-        // Before the barrier, W1_SLOTS times: MFMA, read, (write), W1_PER - 1
-        // MFMAs, (load), the LPS loads and writes on the first slots; after
-        // it, W1_RD times: MFMA, read, W1_PER - 1 MFMAs.
-        constexpr int W1_RD = C::TM + C::TN;
-        constexpr int W1_PER = C::TM * C::TN * (FAM == FAM_F32 ? 4 : 1) / W1_RD;
-        constexpr int W1_SLOTS = (CPS - 1) * W1_RD;          // reads before the barrier
-        static_assert(C::LPS <= W1_SLOTS && W1_PER >= 2, "interleave pattern");
-        // Before the barrier: chunks 0 .. CPS-2 (each while reading the next
-        // chunk of this slot), the loads of stage s + 2 and the LDS writes of
-        // stage s + 1 into the other slot.  After it: the last chunk, while
-        // reading chunk 0 of stage s + 1 from the other slot.  Every read of
-        // this slot precedes the barrier, so the next stage may rewrite it.
-        auto first_part = [&](const uint8_t *X, uint8_t *Y, u32x4 (&RLOAD)[C::LPS], const u32x4 (&RSTORE)[C::LPS]) {
-#pragma unroll
-            for (int c = 0; c + 1 < CPS; ++c) {
-                if (c % 2 == 0) { mfma_chunk(fa0, fb0); read_chunk(X, c + 1, fa1, fb1); }
-                else { mfma_chunk(fa1, fb1); read_chunk(X, c + 1, fa0, fb0); }
-            }
-            stage_load<C::UA, C::UB>(RLOAD, rsA, rsB, a_off, b_off, ach, bch);
-            stage_store<C::UA, C::UB, C::A_STAGE, C::NT>(RSTORE, Y, tid);
-#pragma unroll
-            for (int i = 0; i < W1_SLOTS; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                if (i < C::LPS) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, W1_PER - 1, 0);
-                if (i < C::LPS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            }
-        };
-        auto last_part = [&](const uint8_t *Y) {
-            if constexpr ((CPS - 1) % 2 == 0) { mfma_chunk(fa0, fb0); read_chunk(Y, 0, fa0, fb0); }
-            else { mfma_chunk(fa1, fb1); read_chunk(Y, 0, fa0, fb0); }
-#pragma unroll
-            for (int i = 0; i < W1_RD; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, W1_PER - 1, 0);
-            }
-        };
-#define HS_W1_STEP(X, Y, RLOAD, RSTORE)                                                        \
-    {                                                                                          \
-        fetch_offsets(ach, bch);                                                               \
-        first_part(X, Y, RLOAD, RSTORE);                                                       \
-        __syncthreads();                                                                       \
-        last_part(Y);                                                                          \
-        if (++s >= nstages) break;                                                             \
-    }
-        for (int s = 0; s < nstages;) {
-            HS_W1_STEP(slot0, slot1, r0s, r1s)
-            HS_W1_STEP(slot1, slot0, r1s, r0s)
         }
-#undef HS_W1_STEP
+    dma_done:
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // no load may outlive the workgroup's LDS
     } else {
-        // Both operands through LDS, two slots: the global loads for stage
-        // s + 2 are issued at the top of stage s into one of two register
-        // sets; the LDS image of stage s + 1 is written into the other slot
-        // at the top of stage s, and one barrier closes each stage.
-        u32x4 r0s[C::LPS], r1s[C::LPS];
-        fetch_offsets(ach, bch);
-        stage_load<C::UA, C::UB>(r0s, rsA, rsB, a_off, b_off, ach, bch);
-        fetch_offsets(ach, bch);
-        stage_load<C::UA, C::UB>(r1s, rsA, rsB, a_off, b_off, ach, bch);
-        stage_store<C::UA, C::UB, C::A_STAGE, C::NT>(r0s, ring, tid);
-        __syncthreads();
-#define HS_PIPE_STEP(RLOAD, RSTORE)                                                            \
-    {                                                                                          \
-        const int slot = (int)(s & 1);                                                         \
-        fetch_offsets(ach, bch);                                                               \
-        stage_load<C::UA, C::UB>(RLOAD, rsA, rsB, a_off, b_off, ach, bch);                     \
-        stage_store<C::UA, C::UB, C::A_STAGE, C::NT>(RSTORE, ring + (slot ^ 1) * C::STAGE, tid); \
-        stage_scales();                                                                        \
-        __builtin_amdgcn_sched_barrier(0);                                                     \
-        mm_compute<FAM, FORM, BM, BN, CPS, WAVES>(acc, ring + slot * C::STAGE,                 \
-                                           ring + slot * C::STAGE + C::A_STAGE, lane, wm, wn,  \
-                                           sa, sb);                                            \
-        __syncthreads();                                                                       \
-        if (++s >= nstages) break;                                                             \
-    }
-        for (int s = 0; s < nstages;) {
-            HS_PIPE_STEP(r0s, r1s)
-            HS_PIPE_STEP(r1s, r0s)
+        // FP8: two waves per SIMD, two slots.  The loads of stage s + 1 write
+        // the other slot themselves while stage s is multiplied; the barrier
+        // that ends a stage follows each wave's wait for them.
+        auto ld_stage = [&](int slot) {
+            fetch_offsets(ach, bch);
+#pragma unroll
+            for (int i = 0; i < C::UA; ++i)
+                load_to_lds(lds0 + (uint32_t)(slot * C::STAGE + i * C::NT * 16), (int)a_off[i], rA, ach);
+#pragma unroll
+            for (int i = 0; i < C::UB; ++i)
+                load_to_lds(lds0 + (uint32_t)(slot * C::STAGE + C::A_STAGE + i * C::NT * 16), (int)b_off[i], rB, bch);
+        };
+        ld_stage(0);
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" : : : "memory");
+        for (int s = 0; s < nstages; ++s) {
+            const int slot = s & 1;
+            ld_stage(slot ^ 1);
+            stage_scales();
+            __builtin_amdgcn_sched_barrier(0);
+            mm_compute<FAM, FORM, BM, BN, CPS, WAVES>(acc, ring + slot * C::STAGE, ring + slot * C::STAGE + C::A_STAGE,
+                                                      lane, wm, wn, sa, sb);
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");
         }
-#undef HS_PIPE_STEP
     }
 
     // epilogue: the collector has absorbed every partial; tile row rho is
-    // row msub MS + (rho mod MS) of stripe r0 + (rho / MS) K.  One tile row
-    // at a time (row index computed once, then its columns).
-    const int64_t S_r = a.S_r;
+    // row msub MS + (rho mod MS) of stripe r0 + (rho / MS) K.  A tile that lies
+    // inside the matrix (all but the last ones of ragged sizes) stores without
+    // checks: with them and a division per row, the 64 rows of each lane cost
+    // 6 % of a BF16 4096^3 launch (110 us against 118) and 13 % of an FP8 one (66
+    // against 75).
     constexpr int NE = (int)(sizeof(Acc) / sizeof(acc[0][0][0]));
     // two-piece FP16: the tile holds C' = sum a' b' of the scaled operands;
     // C = C' 2^-(e_row + e_col) (exact unless the result is subnormal)
     constexpr bool ROWSCALE = FAM == FAM_F16 && FORM == 2;
-    int ecol[C::TN];
+    const int64_t cbase = ntile * BN + wn * C::WN + (lane & 31);
+    const uint32_t inv = (65536u + (uint32_t)MS - 1) / (uint32_t)MS;   // rho / MS = rho inv >> 16 for rho < 256
+    const bool to_part = a.nsplit > 1;
+    const int64_t ld = to_part ? a.N : a.ldo;
+    float *dst = to_part ? (float *)a.part + (int64_t)split * a.M * a.N : (float *)a.out;
+    auto store_tile = [&](auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        int ecol[C::TN];
 #pragma unroll
-    for (int ni = 0; ni < C::TN; ++ni) {
-        ecol[ni] = 0;
-        if constexpr (ROWSCALE) {
-            const int64_t col = ntile * BN + wn * C::WN + ni * C::MT + (lane & 31);
-            if (col < a.N) ecol[ni] = row_scale_exp(((const uint32_t *)a.b_exps)[col]);
+        for (int ni = 0; ni < C::TN; ++ni) {
+            ecol[ni] = 0;
+            if constexpr (ROWSCALE)
+                if (WHOLE || cbase + ni * C::MT < a.N)
+                    ecol[ni] = row_scale_exp(((const uint32_t *)a.b_exps)[cbase + ni * C::MT]);
         }
-    }
 #pragma unroll
-    for (int mi = 0; mi < C::TM; ++mi) {
+        for (int mi = 0; mi < C::TM; ++mi) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const int rho = wm * C::WM + mi * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-            const int i = rho / MS, ir = rho % MS;
-            const int64_t within = msub * MS + ir;
-            const int64_t row = (int64_t)(r0 + i * K) * S_r + within;
-            const bool rok = i < ng && within < S_r && row < a.M;
-            const int64_t cbase = ntile * BN + wn * C::WN + (lane & 31);
-            int erow = 0;
-            if constexpr (ROWSCALE) erow = rok ? row_scale_exp(((const uint32_t *)a.a_exps)[row]) : 0;
-            // the element's destination: C, or plane `split` of a.part (rows of N)
-            const bool to_part = a.nsplit > 1;
-            const int64_t obase = to_part ? ((int64_t)split * a.M + row) * a.N + cbase : row * a.ldo + cbase;
-            float *dst = (float *)(to_part ? a.part : a.out);
+            for (int e = 0; e < NE; ++e) {
+                const uint32_t rho = wm * C::WM + mi * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                const uint32_t i = rho * inv >> 16, ir = rho - i * (uint32_t)MS;
+                const uint32_t within = (uint32_t)msub * (uint32_t)MS + ir;
+                const int64_t row = (int64_t)(r0 + i * (uint32_t)K) * a.S_r + within;
+                if (!WHOLE && ((int)i >= ng || within >= a.S_r || row >= a.M)) continue;
+                int erow = 0;
+                if constexpr (ROWSCALE) erow = row_scale_exp(((const uint32_t *)a.a_exps)[row]);
+                float *d = dst + row * ld + cbase;
 #pragma unroll
-            for (int ni = 0; ni < C::TN; ++ni) {
-                const bool ok = rok && cbase + ni * C::MT < a.N;
-                if (ok) {
-                    if constexpr (ROWSCALE) dst[obase + ni * C::MT] = ldexpf(acc[mi][ni][e], -(erow + ecol[ni]));
-                    else dst[obase + ni * C::MT] = acc[mi][ni][e];
+                for (int ni = 0; ni < C::TN; ++ni) {
+                    if (!WHOLE && cbase + ni * C::MT >= a.N) continue;
+                    if constexpr (ROWSCALE) d[ni * C::MT] = ldexpf(acc[mi][ni][e], -(erow + ecol[ni]));
+                    else d[ni * C::MT] = acc[mi][ni][e];
                 }
             }
         }
-    }
+    };
+    const bool inside = ng * MS == BM && (msub + 1) * MS <= a.S_r && (ntile + 1) * BN <= a.N &&
+                        (int64_t)(r0 + (ng - 1) * K) * a.S_r + (msub + 1) * MS <= a.M;
+    if (inside) store_tile(std::true_type{});
+    else store_tile(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------
@@ -817,7 +758,7 @@ static hipError_t launch_mm_t(const MainArgs &a, hipStream_t st) {
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) attr_set[dev] = true;
     }
-    const int64_t nwg = (int64_t)a.K * a.n_ug * a.n_tg * a.grp_v * a.grp_t * a.nsplit;
+    const int64_t nwg = (int64_t)a.K * ((a.Kt + a.G - 1) / a.G) * a.GS * a.n_ntiles * a.nsplit;
     HS_LAUNCH_TIMED((mm_kernel<FAM, FORM, BM, BN, CPS, WAVES>), dim3((unsigned)nwg), dim3(C::NT), C::LDS_BYTES, st, a);
     return hipGetLastError();
 }
@@ -829,26 +770,28 @@ int mm_tile_rows(int fam) { return fam == FAM_F64 ? 64 : 256; }
 int mm_tile_cols(int fam) { return fam == FAM_F64 ? 64 : 256; }
 int mm_chunks_per_stage(int fam, int form) {
     if (fam == FAM_F64) return 4;
-    if (fam == FAM_FP8) return form == 1 ? 1 : 2;
+    if (fam == FAM_FP8) return 1;
     if (fam == FAM_F32) return 2;
-    // split forms one 16-deep chunk per stage (split-BF16: 48 MFMAs per wave;
-    // two-piece FP16: 24, measured 2.45 ms against 2.60 with two chunks at
-    // n = 8192), BF16 and FP16 four (64 per wave; 0.915 against 0.934 ms for
-    // BF16 with two at n = 8192)
-    return form == 1 || form == 2 ? 1 : 4;
+    // split forms one 16-deep chunk per stage (96 and 48 MFMAs per wave), BF16
+    // and FP16 two (32; with four, and two slots, BF16 n = 8192 takes 0.888 ms
+    // against 0.860)
+    return form == 1 || form == 2 ? 1 : 2;
 }
 
-// 8 waves (2 per SIMD) for the split forms' and FP8's 256 x 256 tiles, 4
-// (one per SIMD) for FP32, plain BF16 and FP16 (measured at n = 8192 on
-// one box against 8 waves: FP32 7.33 against 7.61 ms, BF16 0.930 against
-// 0.970 ms, FP16 0.970 against 1.008 ms, with two chunks per stage).
+// 4 waves (one per SIMD) of 128 x 128, but 8 of 128 x 64 for refined FP8, whose
+// fragments (two pieces of 32 bytes) do not fit in registers twice at 128 x 128.
+// Same box, same run, against the layouts before (tiles through registers into
+// two LDS slots; split forms and FP8 with 8 waves, the travelling operand of
+// the split forms straight into registers), n = 8192, ms: BF16 0.806 / 0.883,
+// FP16 0.863 / 0.951, two-piece FP16 2.35 / 2.50, split-BF16 4.11 / 4.23, FP32
+// 7.20 / 7.28, FP8 0.427 / 0.551, refined FP8 1.09 / 1.21.
 hipError_t launch_mm(int fam, int form, const MainArgs &a, hipStream_t st) {
     if (fam == FAM_F32) return launch_mm_t<FAM_F32, 0, 256, 256, 2, 4>(a, st);
-    if (fam == FAM_F16 && form == 0) return launch_mm_t<FAM_F16, 0, 256, 256, 4, 4>(a, st);
-    if (fam == FAM_F16 && form == 2) return launch_mm_t<FAM_F16, 2, 256, 256, 1, 8>(a, st);
-    if (fam == FAM_BF16 && form == 0) return launch_mm_t<FAM_BF16, 0, 256, 256, 4, 4>(a, st);
-    if (fam == FAM_BF16 && form == 1) return launch_mm_t<FAM_BF16, 1, 256, 256, 1, 8>(a, st);
-    if (fam == FAM_FP8 && form == 0) return launch_mm_t<FAM_FP8, 0, 256, 256, 2, 8>(a, st);
+    if (fam == FAM_F16 && form == 0) return launch_mm_t<FAM_F16, 0, 256, 256, 2, 4>(a, st);
+    if (fam == FAM_F16 && form == 2) return launch_mm_t<FAM_F16, 2, 256, 256, 1, 4>(a, st);
+    if (fam == FAM_BF16 && form == 0) return launch_mm_t<FAM_BF16, 0, 256, 256, 2, 4>(a, st);
+    if (fam == FAM_BF16 && form == 1) return launch_mm_t<FAM_BF16, 1, 256, 256, 1, 4>(a, st);
+    if (fam == FAM_FP8 && form == 0) return launch_mm_t<FAM_FP8, 0, 256, 256, 1, 4>(a, st);
     if (fam == FAM_FP8 && form == 1) return launch_mm_t<FAM_FP8, 1, 256, 256, 1, 8>(a, st);
     return hipErrorInvalidValue;
 }

@@ -53,30 +53,11 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
     const int lane = threadIdx.x & 63;
     const int kgi = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
-    // workgroup -> (split, class, group of the class, column tile): each XCD
-    // takes a contiguous range, in batches of grp_v groups x grp_t column tiles
-    uint32_t bid = blockIdx.x;
-    {
-        const uint32_t nwg = gridDim.x, xcd = bid % 8, per = nwg / 8, rem = nwg % 8;
-        bid = xcd * per + (xcd < rem ? xcd : rem) + bid / 8;
-    }
-    const uint32_t per_split = gridDim.x / (uint32_t)a.nsplit;
-    const int split = (int)(bid / per_split);
-    bid -= split * per_split;
     const int p = a.p, K = a.K, Kt = a.Kt;
-    uint32_t ntile, gi;
-    int cls;
-    {
-        const uint32_t gt = a.grp_t, gv = a.grp_v, ntg = a.n_tg, nug = a.n_ug;
-        const uint32_t t_lo = bid % gt;  bid /= gt;
-        const uint32_t u_lo = bid % gv;  bid /= gv;
-        const uint32_t tg = bid % ntg;   bid /= ntg;
-        const uint32_t ug = bid % nug;
-        cls = (int)(bid / nug);
-        ntile = tg * gt + t_lo;
-        gi = ug * gv + u_lo;
-        if (ntile >= a.n_ntiles || gi >= a.GS) return;   // grid padding
-    }
+    const TileAt wg = tile_at(blockIdx.x, gridDim.x, (uint32_t)a.nsplit, (uint32_t)a.GS, (uint32_t)a.n_ntiles,
+                              (uint32_t)a.grp_v, (uint32_t)a.grp_t);
+    const int split = wg.split, cls = wg.cls;
+    const uint32_t ntile = wg.col, gi = wg.member;        // column tile, group of the class
     const int rows = gi + 1 == a.GS ? a.a_last : a.a_rows;        // rows of this group
     const uint32_t nch = (uint32_t)a.nch;
     const uint32_t a_chunk = (uint32_t)(rows * C::CB), b_chunk = (uint32_t)(C::ROWS * C::CB);
@@ -299,7 +280,7 @@ done:
 template <int FAM, int FORM, int T>
 static hipError_t launch_wave_t(const WaveArgs &a, hipStream_t st) {
     typedef WvCfg<FAM, FORM, T> C;
-    const int64_t nwg = (int64_t)a.K * a.n_ug * a.n_tg * a.grp_v * a.grp_t * a.nsplit;
+    const int64_t nwg = (int64_t)a.K * a.GS * a.n_ntiles * a.nsplit;
     const unsigned lds = a.kg == 1 ? 0 : (unsigned)a.kg * T * T * sizeof(typename C::Acc) * 64;   // <= 128 KiB
     // LDS beyond 64 KiB has to be allowed per kernel and device, once
     static std::atomic<uint64_t> allowed{0};
