@@ -18,7 +18,7 @@
 namespace hs {
 hipError_t launch_pack(int kind, const PackArgs &a, const PackArgs &b, hipStream_t st);
 hipError_t launch_mm(int fam, int form, const MainArgs &a, hipStream_t st);
-hipError_t launch_wave(int fam, int form, int t, const WaveArgs &a, hipStream_t st);
+hipError_t launch_wave(int fam, int form, int tr, int tc, const WaveArgs &a, hipStream_t st);
 int wave_chunk_bytes(int fam);
 int wave_tile(int fam, int t);
 hipError_t launch_backshift(int f64, const void *W, int64_t plane, int K, int64_t M, int64_t N,
@@ -92,7 +92,7 @@ struct Plan {
     int64_t tiles_k, tiles_ra, tiles_rb;
     int nsplit, split_stages;         // workgroups per output tile, stages each
     size_t off_part;                  // their partial planes (nsplit > 1)
-    int wave;                         // MFMA tiles per side of the wave kernel's tile; 0: mm_kernel
+    int tr, tc;                       // MFMA tiles down and across the wave kernel's tile; 0: mm_kernel
     int kg;                           // its waves per workgroup
 };
 
@@ -168,27 +168,70 @@ void layout_workspace(Plan *P) {
 // Far left of the line: 1024^3 FP32 35 / 240, split-BF16 30 / 105.  FP64
 // always takes it (an LDS-tiled 64 x 64 kernel measured 3075 us at 4096^3
 // against 1852, 400 against 259 at 2048^3, 18.6 against 5.8 at 256^3).
-int wave_percent(const FormInfo &f) { return f.fam == FAM_F64 ? 101 : f.fam == FAM_F32 ? 88 : 50; }
+// 4 x 2 tiles (wave_shape: only where they fill the chip) move the line to u =
+// 0.97, split-BF16 and two-piece FP16: u = 1/2 (2048^3) 93 / 103 and 61 / 67;
+// u = 0.78 (2500^3) 167 / 252 and 117 / 140; u = 0.95 (2816^3) 207 / 274 and 142 / 155;
+// u = 1 (4096 x 2048 x 2048) 157 / 142 and 110 / 91.
+int wave_percent(const FormInfo &f, int tr) {
+    return f.fam == FAM_F64 ? 101 : f.fam == FAM_F32 ? 88 : tr == 4 ? 97 : 50;
+}
 
-// MFMA tiles per side of the wave kernel's tile, and waves per workgroup.
-// The forms with cheap fragments (FP32, FP64: an MFMA takes 64 cycles for two
-// fragments of 16 bytes a lane) keep small tiles until 900 large ones exist
-// (FP32 1500^3, 576 large tiles: 66 us small, 82 large; 2048^3, 1024: 149 and
-// 139) and 4 waves a workgroup until 8192 (2048^3: 139 us with 4 waves, 193
-// with 2, 250 with 1, since workgroups of one or two waves share SIMDs while
-// others idle).  The 16-bit and FP8 forms are bound by fragment reads, which a
-// large tile halves: large from 256 tiles (1024^3: split-BF16 19 us against
-// 22, FP8 8.9 against 9.1; below, 256 x 512 x 2048, 64 tiles, refined FP8 8.6
-// against 6.9), and only as many waves as fill the SIMDs (BF16 2500^3, 1600
-// tiles: 53 us with one wave, 64 with 4; 1500^3, 576: 25, 22 with 2, 24).
-void wave_shape(const FormInfo &f, int64_t small, int64_t large, int64_t chunks, int *t, int *kg) {
-    const bool slow = f.fam == FAM_F64 || f.fam == FAM_F32;
-    *t = large >= (slow ? 900 : 256) ? 2 : 1;
-    const int64_t n = *t == 2 ? large : small;
-    if (slow) *kg = n >= 8192 ? 1 : 4;
-    else if (*t == 2) *kg = n >= 1024 ? 1 : n >= 512 ? 2 : 4;
-    else *kg = n >= 768 ? 2 : 4;
-    if (n <= 128 && chunks >= 256) *kg = 8;     // long sums on few tiles: 300x320x6000 BF16 13 us against 15
+// MFMA tiles down and across the wave kernel's tile, and waves per workgroup;
+// n(tr, tc) counts the output tiles.  Times in us, n x n x k products.
+//
+// A wave of the FP32 and FP64 forms spends 64 cycles on the MFMA of two cheap
+// fragments: small tiles, 4 waves (FP32 2048^3: 139 with 4 waves, 193 with 2,
+// 250 with 1, since workgroups of one or two waves share SIMDs while others
+// idle), one wave from 8192 tiles on.  Of these 2 x 2 tiles two workgroups
+// fit a CU (LDS): taken from 900 tiles, and for FP32, where they gain little
+// (2048^3, 1024 tiles: 134 against 140) only if 512 at a time fill nine tenths
+// of the rounds (1800 x 2200 x 1000, 1050 tiles: 91 against 72).
+//
+// The 16-bit and FP8 forms are bound by fragment reads, which larger tiles
+// save: 2 x 2 from 256 tiles (1024^3: split-BF16 19 against 22, FP8 8.9 against
+// 9.1; below, 256 x 512 x 2048, 64 tiles, refined FP8 8.6 against 6.9) with only
+// as many waves as fill the SIMDs (BF16 2500^3, 1600 tiles: 53 with one wave,
+// 64 with 4; 1500^3, 576: 25, 22 with 2, 24; the split forms with their longer
+// chunks take 4 until 1024: split-BF16 1500^3 54 against 66 with 2).
+// Just past 256 tiles of 2 x 2 a few CUs would run two rounds: where 3 x 2 ones
+// are at most 256, the 16-bit forms take these with 8 waves (1100 x 900 x 1000,
+// 270 tiles against 180: split-BF16 28.4 to 23.0, two-piece FP16 20.4 to 17.4,
+// BF16 13.9 to 12.8; 800 x 1100 x 3000: 62 to 43, 43 to 31, 24 to 19; FP8 gains
+// nothing, 11.3 and 11.4, nor do fewer than 8 chunks).  4 x 2 tiles need all
+// registers of a SIMD for one wave; for the split forms they win where such
+// waves are on nearly every SIMD, 512 tiles of two waves or 1024 of one (2048^3:
+// 99 to 93 and 65 to 61; 2500^3, 800 tiles: 193 to 167 and 134 to 117; 1800 x
+// 2200 x 1000, 560: 64, 73 here), from 64 chunks (split-BF16 2048 x 2048 x 512: 32, 35
+// here) or 128 (two-piece FP16 2560 x 2560 x 1024: 60, 65 here).
+template <class Count>
+void wave_shape(const FormInfo &f, Count n, int64_t chunks, int *tr, int *tc, int *kg) {
+    const bool slow = f.fam == FAM_F64 || f.fam == FAM_F32, b16 = f.fam == FAM_BF16 || f.fam == FAM_F16;
+    const bool split = b16 && f.form != 0;
+    auto fills = [](int64_t tiles, int64_t slots, int percent) {
+        return tiles * 100 >= ceil_div(tiles, slots) * slots * percent;
+    };
+    const int64_t n22 = n(2, 2), n42 = n(4, 2);
+    *tr = *tc = 1;
+    if (slow) {
+        if (n22 >= 900 && (f.fam == FAM_F64 || fills(n22, 512, 90))) *tr = *tc = 2;
+        *kg = n(*tr, *tc) >= 8192 ? 1 : 4;
+    } else if (split && chunks >= (f.form == 1 ? 64 : 128) && n42 > 256 && n42 <= 1024 &&
+               fills(n42, n42 <= 512 ? 512 : 1024, 75)) {
+        *tr = 4;
+        *tc = 2;
+        *kg = n42 <= 512 ? 2 : 1;
+    } else if (b16 && n22 > kCUs && n(3, 2) <= kCUs && chunks >= 8) {
+        *tr = 3;
+        *tc = 2;
+        *kg = 8;
+    } else if (n22 >= 256) {
+        *tr = *tc = 2;
+        *kg = n22 >= 1024 ? 1 : n22 >= 512 && !split ? 2 : 4;
+    } else {
+        *kg = n(1, 1) >= 768 ? 2 : 4;
+    }
+    // long sums on few tiles: 300 x 320 x 6000 BF16 13 against 15
+    if (*tr * *tc <= 4 && n(*tr, *tc) <= 128 && chunks >= 256) *kg = 8;
     while (*kg > 1 && chunks < 2 * *kg) *kg /= 2;
 }
 
@@ -200,24 +243,23 @@ void plan_wave(Plan *P) {
     if (P->M == 0 || P->N == 0 || P->Kd == 0) return;
     const int fam = P->f.fam;
     const int64_t tiles = (int64_t)P->K * ceil_div(P->Kt, P->G) * P->ga.GS * P->gb.GS * P->nsplit;
-    if (tiles * 100 >= ceil_div(tiles, kCUs) * kCUs * wave_percent(P->f)) return;
     Plan W = *P;
     const int64_t L = (int64_t)P->Kt * P->ga.S_r;         // rows of a residue class
     const int CBY = wave_chunk_bytes(fam);
     const int64_t nch = ceil_div(P->ga.S_k, CBY / P->f.packed_esz), chunks = P->p * nch;
-    auto count = [&](int t) {
-        const int64_t R = wave_tile(fam, t);
-        return (int64_t)P->K * ceil_div(L, R) * ceil_div(P->N, R);
+    auto count = [&](int tr, int tc) {
+        return (int64_t)P->K * ceil_div(L, wave_tile(fam, tr)) * ceil_div(P->N, wave_tile(fam, tc));
     };
-    wave_shape(P->f, count(1), count(2), chunks, &W.wave, &W.kg);
-    const int64_t wt = count(W.wave);
+    wave_shape(P->f, count, chunks, &W.tr, &W.tc, &W.kg);
+    if (tiles * 100 >= ceil_div(tiles, kCUs) * kCUs * wave_percent(P->f, W.tr)) return;
+    const int64_t wt = count(W.tr, W.tc);
     if (wt > (int64_t)1 << 26) return;                    // 32-bit grid in threads
-    const int R = wave_tile(fam, W.wave);
+    const int R = wave_tile(fam, W.tr), C = wave_tile(fam, W.tc);
     OperandGeom &a = W.ga, &b = W.gb;
     a.striped = OPG_CLASSES;
     a.grp_rows = (int)std::min<int64_t>(R, L);
     a.GS = ceil_div(L, a.grp_rows);
-    b.grp_rows = R; b.GS = ceil_div(P->N, R);
+    b.grp_rows = C; b.GS = ceil_div(P->N, C);
     a.nch = b.nch = nch;
     a.chunk_bytes = b.chunk_bytes = CBY;
     finish_geom(&a, P->p, P->K, P->K, L);
@@ -309,11 +351,11 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
         P->nsplit = (int)ceil_div(nstages, P->split_stages);
     }
 
-    P->wave = 0;
+    P->tr = P->tc = 0;
     P->kg = 0;
     layout_workspace(P);
     plan_wave(P);
-    if (P->f.fam == FAM_F64 && P->wave == 0 && P->total > 0) return HS_ERR_NOT_SUPPORTED;   // no other FP64 kernel
+    if (P->f.fam == FAM_F64 && P->tr == 0 && P->total > 0) return HS_ERR_NOT_SUPPORTED;   // no other FP64 kernel
     return HS_OK;
 }
 
@@ -430,7 +472,7 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
     if (e != hipSuccess) return HS_ERR_LAUNCH_FAILED;
 
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    if (P.wave) {
+    if (P.tr) {
         WaveArgs v{};
         v.A = w + P.off_a; v.a_group = P.ga.group_bytes; v.a_class = P.ga.list_bytes;
         v.B = w + P.off_b; v.b_group = P.gb.group_bytes;
@@ -443,7 +485,7 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
         batch_shape(P.gb.GS, P.ga.GS, &v.grp_v, &v.grp_t);
         v.kg = P.kg; v.nsplit = P.nsplit; v.split_chunks = P.split_stages; v.part = w + P.off_part;
         if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
-        e = launch_wave(P.f.fam, P.f.form, P.wave, v, stream);
+        e = launch_wave(P.f.fam, P.f.form, P.tr, P.tc, v, stream);
         if (g_prof) keep_timing(ev0, ev1);
         if (e == hipSuccess && P.nsplit > 1)
             e = launch_backshift(f64, v.part, P.M * P.N, P.nsplit, P.M, P.N, out, ldo, stream);

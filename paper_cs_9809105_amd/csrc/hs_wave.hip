@@ -4,7 +4,8 @@
 //
 // What bounds such a launch is not the MFMA rate but how many SIMDs have work
 // and how long one wave's chain of chunks is.  So the output tile is small
-// (64 x 64, or 32 x 32 where even those are fewer than the CUs), and the
+// (64 x 64, or 32 x 32 where even those are fewer than the CUs; 96 x 64 or
+// 128 x 64 where these come out just under a round of the chip), and the
 // workgroup's kg waves share one tile: each walks its own run of the
 // tile's chunks in the step order of mm_kernel (partials l = K-1 .. 0, steps
 // of stride K, chunks of a block) with its own accumulators, and the kg sums
@@ -25,30 +26,33 @@ namespace hs {
 
 bool take_timed_launch(hipEvent_t *start, hipEvent_t *stop);   // hs_kernels.hip
 
-// T x T MFMA tiles per wave.  D: register sets of fragments (chunks in
-// flight + 1); a set is 2 T NP LD x 4 registers.  One or two sets more changed
+// TR x TC MFMA tiles per wave.  D: register sets of fragments (chunks in
+// flight + 1); a set is (TR + TC) NP LD x 4 registers.  MAX_KG: eight waves
+// share a tile, two to a SIMD, where sets and sums fit 256 registers (3 x 2
+// tiles at 1100 x 900 x 1000: 22.4 us with 8 waves, 23.8 with 4).  One or two sets more changed
 // nothing beyond noise (split-BF16 1024^3 19.1 against 18.9 us, FP32 2500^3 287
 // against 289): the vector-memory path is the limit there, at about 28 bytes
 // per clock and CU with it busy three quarters of the time.
-template <int FAM, int FORM, int T>
+template <int FAM, int FORM, int TR, int TC>
 struct WvCfg {
     static const int NP = Pieces<FAM, FORM>::NP;
     static const int MT = Mfma<FAM>::T;
-    static const int ROWS = T * MT;                              // tile rows and columns
+    static const int ROWS = TR * MT, COLS = TC * MT;
     static const int CB = FAM == FAM_FP8 || FAM == FAM_F64 ? 64 : 32;   // bytes per chunk row
     static const int LD = FAM == FAM_FP8 ? 2 : 1;                // 16-byte loads per fragment
-    static const int SET = 2 * T * NP * LD * 4;                  // registers of one set
+    static const int SET = (TR + TC) * NP * LD * 4;                 // registers of one set
     static const int D = SET <= 8 ? 8 : SET <= 16 ? 4 : SET <= 24 ? 3 : 2;
+    static const int MAX_KG = TR * TC <= 6 && SET * D + TR * TC * 16 <= 216 ? 8 : 4;
     typedef typename Mfma<FAM>::Acc Acc;
     static const int NE = (int)(sizeof(Acc) / (FAM == FAM_F64 ? 8 : 4));
 };
 
-template <int FAM, int FORM, int T>
-__global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
-    typedef WvCfg<FAM, FORM, T> C;
+template <int FAM, int FORM, int TR, int TC>
+__global__ __launch_bounds__(64 * (WvCfg<FAM, FORM, TR, TC>::MAX_KG)) void wave_kernel(WaveArgs a) {
+    typedef WvCfg<FAM, FORM, TR, TC> C;
     typedef typename C::Acc Acc;
     typedef typename std::conditional<FAM == FAM_F64, double, float>::type E;
-    extern __shared__ __attribute__((aligned(32))) uint8_t red[];   // kg > 1: kg accumulator sets
+    extern __shared__ __attribute__((aligned(32))) uint8_t red[];   // kg > 1: min(kg, 4) accumulator sets
     constexpr int NP = C::NP, MT = C::MT, LD = C::LD;
     const int lane = threadIdx.x & 63;
     const int kgi = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -60,7 +64,7 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
     const uint32_t ntile = wg.col, gi = wg.member;        // column tile, group of the class
     const int rows = gi + 1 == a.GS ? a.a_last : a.a_rows;        // rows of this group
     const uint32_t nch = (uint32_t)a.nch;
-    const uint32_t a_chunk = (uint32_t)(rows * C::CB), b_chunk = (uint32_t)(C::ROWS * C::CB);
+    const uint32_t a_chunk = (uint32_t)(rows * C::CB), b_chunk = (uint32_t)(C::COLS * C::CB);
     const uint32_t a_piece = (uint32_t)p * nch * a_chunk, b_piece = (uint32_t)p * nch * b_chunk;
     const __amdgpu_buffer_rsrc_t rsA = packed_rsrc(a.A + cls * a.a_class + (int64_t)gi * a.a_group, a_piece * NP);
     const __amdgpu_buffer_rsrc_t rsB = packed_rsrc(a.B + (int64_t)ntile * a.b_group, b_piece * NP);
@@ -69,14 +73,14 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
     // 2g, 2g + 1) of row lane % MT.  Tile rows past the group's own re-read
     // row 0; they are never stored.
     const int r = lane & (MT - 1), g = lane / MT;
-    int a_off[T], a_pl;
+    int a_off[TR], a_pl;
 #pragma unroll
-    for (int mi = 0; mi < T; ++mi) {
+    for (int mi = 0; mi < TR; ++mi) {
         const int row = mi * MT + r < rows ? mi * MT + r : 0;
         a_off[mi] = (g * LD * rows + row) * 16;
     }
     a_pl = rows * 16;
-    const int b_off = (g * LD * C::ROWS + r) * 16;
+    const int b_off = (g * LD * C::COLS + r) * 16;
 
     // this wave's chunks of the workgroup's [split per, (split + 1) per)
     const int total = p * (int)nch;
@@ -106,7 +110,7 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
         x.kb = (int)((uint32_t)(cls + K - 1 - x.t) % (uint32_t)K);
     };
 
-    struct Set { u32x4 a[NP][T][LD], b[NP][T][LD]; };
+    struct Set { u32x4 a[NP][TR][LD], b[NP][TC][LD]; };
     Set f[C::D];
     auto load = [&](Set &x) {
         const uint32_t ch = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)q.kb * nch + (uint32_t)q.cs));
@@ -115,36 +119,41 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
 #pragma unroll
         for (int P = 0; P < NP; ++P)
 #pragma unroll
-            for (int i = 0; i < T; ++i)
+            for (int h = 0; h < LD; ++h) {
 #pragma unroll
-                for (int h = 0; h < LD; ++h) {
+                for (int i = 0; i < TR; ++i)
                     x.a[P][i][h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
                         rsA, a_off[i] + h * a_pl, (int)(sa + P * a_piece), 0));
+#pragma unroll
+                for (int i = 0; i < TC; ++i)
                     x.b[P][i][h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                        rsB, b_off + (i * MT + h * C::ROWS) * 16, (int)(sb + P * b_piece), 0));
-                }
+                        rsB, b_off + (i * MT + h * C::COLS) * 16, (int)(sb + P * b_piece), 0));
+            }
     };
 
     // FP8: scale tile of each row / column tile (uniform across the wave)
-    int tra[T], trb[T];
+    int tra[TR], trb[TC];
     if constexpr (FAM == FAM_FP8) {
 #pragma unroll
-        for (int i = 0; i < T; ++i) {
+        for (int i = 0; i < TR; ++i) {
             const int64_t at = (int64_t)gi * a.a_rows + i * MT;
             int64_t row = (cls + at / a.S_r * K) * a.S_r + at % a.S_r;
             row = row < a.M ? row : a.M - 1;             // rows past M are never stored
             tra[i] = (int)(row / FP8_TILE);
-            int64_t col = (int64_t)ntile * C::ROWS + i * MT;
+        }
+#pragma unroll
+        for (int i = 0; i < TC; ++i) {
+            int64_t col = (int64_t)ntile * C::COLS + i * MT;
             col = col < a.N ? col : a.N - 1;
             trb[i] = (int)(col / FP8_TILE);
         }
     }
 
-    Acc acc[T][T];
+    Acc acc[TR][TC];
 #pragma unroll
-    for (int mi = 0; mi < T; ++mi)
+    for (int mi = 0; mi < TR; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < T; ++ni) acc[mi][ni] = Acc{};
+        for (int ni = 0; ni < TC; ++ni) acc[mi][ni] = Acc{};
 
     auto multiply = [&](const Set &x) {
         if constexpr (FAM == FAM_FP8) {
@@ -155,26 +164,27 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
             kk = kk < a.Kd ? kk : a.Kd - 1;              // padding chunks hold zeros
             advance(qc);
             const int tc = __builtin_amdgcn_readfirstlane((int)(kk / FP8_TILE));
-            int sa[NP][T], sb[NP][T];
+            int sa[NP][TR], sb[NP][TC];
 #pragma unroll
-            for (int i = 0; i < T; ++i) {
+            for (int i = 0; i < TR; ++i) {
                 const int ta = __builtin_amdgcn_readfirstlane((int)((tra[i] * a.a_tiles_k + tc) * 2));
-                const int tb = __builtin_amdgcn_readfirstlane((int)((trb[i] * a.b_tiles_k + tc) * 2));
                 sa[0][i] = 127 - ea[ta];
+                if constexpr (NP == 2) sa[1][i] = sa[0][i] - ea[ta + 1];
+            }
+#pragma unroll
+            for (int i = 0; i < TC; ++i) {
+                const int tb = __builtin_amdgcn_readfirstlane((int)((trb[i] * a.b_tiles_k + tc) * 2));
                 sb[0][i] = 127 - eb[tb];
-                if constexpr (NP == 2) {
-                    sa[1][i] = sa[0][i] - ea[ta + 1];
-                    sb[1][i] = sb[0][i] - eb[tb + 1];
-                }
+                if constexpr (NP == 2) sb[1][i] = sb[0][i] - eb[tb + 1];
             }
             auto frag = [](const u32x4 (&w)[LD]) {
                 const u32x4 lo = w[0], hi = w[LD - 1];
                 return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
             };
 #pragma unroll
-            for (int mi = 0; mi < T; ++mi)
+            for (int mi = 0; mi < TR; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < T; ++ni) {
+                for (int ni = 0; ni < TC; ++ni) {
                     if constexpr (NP == 2) {             // q1 q0', q0 q1', q0 q0': smallest first
                         acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                             frag(x.a[1][mi]), frag(x.b[0][ni]), acc[mi][ni], 0, 0, 0, sa[1][mi], 0, sb[0][ni]);
@@ -190,26 +200,26 @@ __global__ __launch_bounds__(64 * 8) void wave_kernel(WaveArgs a) {
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int mi = 0; mi < T; ++mi)
+                for (int mi = 0; mi < TR; ++mi)
 #pragma unroll
-                    for (int ni = 0; ni < T; ++ni) {
+                    for (int ni = 0; ni < TC; ++ni) {
                         const u32x4 av = x.a[0][mi][0], bv = x.b[0][ni][0];
                         acc[mi][ni] = __builtin_amdgcn_mfma_f64_16x16x4f64(
                             __hiloint2double((int)av[2 * t + 1], (int)av[2 * t]),
                             __hiloint2double((int)bv[2 * t + 1], (int)bv[2 * t]), acc[mi][ni], 0, 0, 0);
                     }
         } else {
-            u32x4 bv[NP][T];
+            u32x4 bv[NP][TC];
 #pragma unroll
             for (int P = 0; P < NP; ++P)
 #pragma unroll
-                for (int ni = 0; ni < T; ++ni) bv[P][ni] = x.b[P][ni][0];
+                for (int ni = 0; ni < TC; ++ni) bv[P][ni] = x.b[P][ni][0];
 #pragma unroll
-            for (int mi = 0; mi < T; ++mi) {
+            for (int mi = 0; mi < TR; ++mi) {
                 u32x4 av[NP];
 #pragma unroll
                 for (int P = 0; P < NP; ++P) av[P] = x.a[P][mi][0];
-                mfma_row<FAM, FORM, T>(acc[mi], av, bv);
+                mfma_row<FAM, FORM, TC>(acc[mi], av, bv);
             }
         }
     };
@@ -237,7 +247,7 @@ done:
         const int rho = mi * MT + (FAM == FAM_F64 ? 4 * e + g : (e >> 2) * 8 + g * 4 + (e & 3));
         const uint32_t at = base + rho, i = at / S;
         const int64_t row = (int64_t)(cls + i * K) * S + (at - i * S);
-        const int64_t col = (int64_t)ntile * C::ROWS + ni * MT + r;
+        const int64_t col = (int64_t)ntile * C::COLS + ni * MT + r;
         if (rho >= rows || row >= a.M || col >= a.N) return;
         if constexpr (ROWSCALE) v = ldexpf(v, -(row_scale_exp(eca[row]) + row_scale_exp(ecb[col])));
         if (to_part) ((E *)a.part)[((int64_t)split * a.M + row) * a.N + col] = v;
@@ -245,50 +255,74 @@ done:
     };
     if (a.kg == 1) {
 #pragma unroll
-        for (int mi = 0; mi < T; ++mi)
+        for (int mi = 0; mi < TR; ++mi)
 #pragma unroll
             for (int e = 0; e < C::NE; ++e)
 #pragma unroll
-                for (int ni = 0; ni < T; ++ni) store(mi, ni, e, acc[mi][ni][e]);
+                for (int ni = 0; ni < TC; ++ni) store(mi, ni, e, acc[mi][ni][e]);
         return;
     }
-    // every wave leaves its sums in LDS; then wave w adds and stores quads
-    // w, w + kg, .. of accumulator elements, the waves' sums in their order.
+    // every wave leaves its sums in LDS (of eight, the upper four first, which
+    // the lower four add to theirs, so that LDS holds four sets); then wave w adds and stores
+    // quads w, w + kg, .. of accumulator elements, the sets in their order.
     // (A pairwise tree after which one wave stored the tile took longer:
     // split-BF16 256^3 7.9 us against 5.8, 1024^3 22 against 19.)
     typedef E E4 __attribute__((ext_vector_type(4)));
-    constexpr int NQ = T * T * C::NE / 4;                // quads per lane: (mi, ni, e / 4)
+    constexpr int NQ = TR * TC * C::NE / 4;                // quads per lane: (mi, ni, e / 4)
     E4 *buf = (E4 *)red;
+    auto leave = [&](int w) {
 #pragma unroll
-    for (int mi = 0; mi < T; ++mi)
+        for (int mi = 0; mi < TR; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < T; ++ni)
+            for (int ni = 0; ni < TC; ++ni)
 #pragma unroll
-            for (int h = 0; h < C::NE / 4; ++h)
-                buf[(kgi * NQ + (mi * T + ni) * (C::NE / 4) + h) * 64 + lane] =
-                    E4{acc[mi][ni][4 * h], acc[mi][ni][4 * h + 1], acc[mi][ni][4 * h + 2], acc[mi][ni][4 * h + 3]};
+                for (int h = 0; h < C::NE / 4; ++h)
+                    buf[(w * NQ + (mi * TC + ni) * (C::NE / 4) + h) * 64 + lane] =
+                        E4{acc[mi][ni][4 * h], acc[mi][ni][4 * h + 1], acc[mi][ni][4 * h + 2], acc[mi][ni][4 * h + 3]};
+    };
+    int sets = a.kg;
+    if (C::MAX_KG == 8 && a.kg == 8) {                   // the upper half first, added by the lower half
+        sets = 4;
+        if (kgi >= 4) leave(kgi - 4);
+        __syncthreads();
+        if (kgi < 4) {
+#pragma unroll
+            for (int mi = 0; mi < TR; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < TC; ++ni)
+#pragma unroll
+                    for (int h = 0; h < C::NE / 4; ++h) {
+                        const E4 v = buf[(kgi * NQ + (mi * TC + ni) * (C::NE / 4) + h) * 64 + lane];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[mi][ni][4 * h + e] += v[e];
+                    }
+            leave(kgi);                                  // its own quads: no other wave reads them before the barrier
+        }
+    } else {
+        leave(kgi);
+    }
     __syncthreads();
     for (int q4 = kgi; q4 < NQ; q4 += a.kg) {
         E4 v = buf[q4 * 64 + lane];
-        for (int w = 1; w < a.kg; ++w) v += buf[(w * NQ + q4) * 64 + lane];
+        for (int w = 1; w < sets; ++w) v += buf[(w * NQ + q4) * 64 + lane];
         const int h = q4 % (C::NE / 4), tile = q4 / (C::NE / 4);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) store(tile / T, tile % T, 4 * h + e, v[e]);
+        for (int e = 0; e < 4; ++e) store(tile / TC, tile % TC, 4 * h + e, v[e]);
     }
 }
 
-template <int FAM, int FORM, int T>
+template <int FAM, int FORM, int TR, int TC>
 static hipError_t launch_wave_t(const WaveArgs &a, hipStream_t st) {
-    typedef WvCfg<FAM, FORM, T> C;
+    typedef WvCfg<FAM, FORM, TR, TC> C;
     const int64_t nwg = (int64_t)a.K * a.GS * a.n_ntiles * a.nsplit;
-    const unsigned lds = a.kg == 1 ? 0 : (unsigned)a.kg * T * T * sizeof(typename C::Acc) * 64;   // <= 128 KiB
+    const unsigned lds = a.kg == 1 ? 0 : (unsigned)(a.kg < 4 ? a.kg : 4) * TR * TC * sizeof(typename C::Acc) * 64;   // <= 128 KiB
     // LDS beyond 64 KiB has to be allowed per kernel and device, once
     static std::atomic<uint64_t> allowed{0};
     int dev = 0;
     if (lds > 65536) {
         if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
         if (dev >= 64 || !(allowed.load() >> dev & 1)) {
-            hipError_t e = hipFuncSetAttribute((const void *)wave_kernel<FAM, FORM, T>,
+            hipError_t e = hipFuncSetAttribute((const void *)wave_kernel<FAM, FORM, TR, TC>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 131072);
             if (e != hipSuccess) return e;
             if (dev < 64) allowed.fetch_or((uint64_t)1 << dev);
@@ -296,29 +330,38 @@ static hipError_t launch_wave_t(const WaveArgs &a, hipStream_t st) {
     }
     hipEvent_t ts, te;
     if (take_timed_launch(&ts, &te))
-        hipExtLaunchKernelGGL((wave_kernel<FAM, FORM, T>), dim3((unsigned)nwg), dim3(64 * a.kg), lds, st, ts, te, 0, a);
+        hipExtLaunchKernelGGL((wave_kernel<FAM, FORM, TR, TC>), dim3((unsigned)nwg), dim3(64 * a.kg), lds, st, ts, te, 0, a);
     else
-        hipLaunchKernelGGL((wave_kernel<FAM, FORM, T>), dim3((unsigned)nwg), dim3(64 * a.kg), lds, st, a);
+        hipLaunchKernelGGL((wave_kernel<FAM, FORM, TR, TC>), dim3((unsigned)nwg), dim3(64 * a.kg), lds, st, a);
     return hipGetLastError();
 }
 
 // Bytes per chunk row of the packed operands of this kernel.
 int wave_chunk_bytes(int fam) { return fam == FAM_FP8 || fam == FAM_F64 ? 64 : 32; }
-// Tile rows (and columns) with t MFMA tiles per side.
+// Tile rows (or columns) of t MFMA tiles.
 int wave_tile(int fam, int t) { return t * (fam == FAM_F64 ? 16 : 32); }
 
-hipError_t launch_wave(int fam, int form, int t, const WaveArgs &a, hipStream_t st) {
-#define HS_WV(F, O)                                            \
-    if (fam == F && form == O)                                 \
-        return t == 1 ? launch_wave_t<F, O, 1>(a, st) : launch_wave_t<F, O, 2>(a, st)
-    HS_WV(FAM_F64, 0);
-    HS_WV(FAM_F32, 0);
-    HS_WV(FAM_F16, 0);
-    HS_WV(FAM_F16, 2);
-    HS_WV(FAM_BF16, 0);
-    HS_WV(FAM_BF16, 1);
-    HS_WV(FAM_FP8, 0);
-    HS_WV(FAM_FP8, 1);
+hipError_t launch_wave(int fam, int form, int tr, int tc, const WaveArgs &a, hipStream_t st) {
+#define HS_WV(F, O, R, C) \
+    if (fam == F && form == O && tr == R && tc == C) return launch_wave_t<F, O, R, C>(a, st)
+#define HS_WALL(R, C)          \
+    HS_WV(FAM_F64, 0, R, C);   \
+    HS_WV(FAM_F32, 0, R, C);   \
+    HS_WV(FAM_F16, 0, R, C);   \
+    HS_WV(FAM_F16, 2, R, C);   \
+    HS_WV(FAM_BF16, 0, R, C);  \
+    HS_WV(FAM_BF16, 1, R, C);  \
+    HS_WV(FAM_FP8, 0, R, C);   \
+    HS_WV(FAM_FP8, 1, R, C)
+    HS_WALL(1, 1);
+    HS_WALL(2, 2);
+    HS_WV(FAM_F16, 0, 3, 2);
+    HS_WV(FAM_F16, 2, 3, 2);
+    HS_WV(FAM_BF16, 0, 3, 2);
+    HS_WV(FAM_BF16, 1, 3, 2);
+    HS_WV(FAM_F16, 2, 4, 2);
+    HS_WV(FAM_BF16, 1, 4, 2);
+#undef HS_WALL
 #undef HS_WV
     return hipErrorInvalidValue;
 }

@@ -107,3 +107,33 @@ def test_wave_fp8(dt, case):
             assert np.array_equal(host(C), ref)
         else:
             assert err_row(host(C), ref) <= ROW_TOL[dt]
+
+
+# 96 x 64 tiles (two-round counts of 64 x 64 ones): last groups of 65, 1 and 96
+# rows, eight waves and the four that eight chunks allow; 128 x 64 tiles (split
+# forms): 512 tiles of two waves, 800 of one, last groups of 127, 98 and 1 rows
+TALL = ([(dt, c) for dt in ("bf16", "f16", "split3_bf16", "split2_f16")
+         for c in [(1090, 961, 250, 2, 2), (1537, 700, 113, 1, 1), (2016, 577, 516, 3, 3)]] +
+        [(dt, c) for dt in ("split3_bf16", "split2_f16")
+         for c in [(2047, 2010, 2050, 2, 1), (2500, 2500, 2100, 4, 2), (1281, 2500, 2049, 1, 1)]])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt, case", TALL)
+def test_wave_tall_tiles(dt, case):
+    if not gpu_available():
+        pytest.skip("no GPU")
+    m, n, k, p, K = case
+    rows = sorted({r for t in range(0, m, 96) for r in (t, t + 31, t + 95) if r < m} | {m - 2, m - 1})
+    A, A64 = to_dev(inputs.normal((m, k), seed=4120), dt)
+    Bm, B64 = to_dev(inputs.normal((k, n), seed=4121), dt)
+    note("wave tall", dt, case)
+    C = hs.hs_gemm(A, Bm, dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
+    torch.cuda.synchronize()
+    assert np.isfinite(host(C)).all()
+    check(host(C)[rows], oracle.gemm_rows(A64, B64, rows), dt, A64[rows], B64, what="wave tall %s" % (case,))
+    Ai, Ai64 = to_dev(inputs.small_int((m, k), 4122, -4, 4), dt)
+    Bi, Bi64 = to_dev(inputs.small_int((k, n), 4123, -4, 4), dt)
+    Ci = hs.hs_gemm(Ai, Bi, dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(Ci), Ai64 @ Bi64)         # exact in float64 in any order
