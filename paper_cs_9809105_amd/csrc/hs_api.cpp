@@ -398,22 +398,6 @@ struct Operand {
 
 hs_status launch_status(hipError_t e) { return e == hipSuccess ? HS_OK : HS_ERR_LAUNCH_FAILED; }
 
-// A K-major source may be read 16 bytes at a time when every unit's
-// elements are contiguous, aligned and either all inside or all outside
-// the matrix and its contraction block.
-int pack_vec_ok(const Plan &P, const Operand &X) {
-    if (!X.kmajor || X.embed != EMB_NONE) return 0;
-    const int64_t ue = 16 / P.f.packed_esz;          // source elements per unit
-    const int64_t in = P.f.in_esz;
-    if (P.f.pack == PK_SPLIT3 || P.f.pack == PK_SPLIT2F16) {   // 8 fp32 per unit (two loads)
-        return (X.ld % 4 == 0 && aligned(X.ptr, 16) && P.ga.S_k % 8 == 0 && P.Kd % 8 == 0) ? 1 : 0;
-    }
-    if (P.f.pack == PK_FP8) {                        // 16 fp32 per unit (four loads)
-        return (X.ld % 4 == 0 && aligned(X.ptr, 16) && P.ga.S_k % 16 == 0 && P.Kd % 16 == 0) ? 1 : 0;
-    }
-    return (X.ld * in % 16 == 0 && aligned(X.ptr, 16) && P.ga.S_k % ue == 0 && P.Kd % ue == 0) ? 1 : 0;
-}
-
 // How an operand's source is read.  An MN-major one goes through LDS (16-byte
 // runs of 4 FP32 or 8 16-bit rows) when its rows are 16-byte aligned and every
 // run of a group lies in one stripe.
@@ -430,7 +414,6 @@ PackArgs pack_args(const Plan &P, const Operand &X, const OperandGeom &g, void *
     a.src = X.ptr; a.ld = X.ld; a.g = g; a.dst = dst;
     a.total_units = pack_units(g, X.kmajor);
     a.mode = pack_mode(P, X, g);
-    a.vec = pack_vec_ok(P, X);
     a.exps = exps; a.exp_tiles_k = P.tiles_k; a.refine = P.f.form;
     a.embed = X.embed;
     return a;

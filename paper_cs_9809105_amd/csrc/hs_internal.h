@@ -113,7 +113,6 @@ struct PackArgs {
     void *dst;
     int64_t total_units;     // < 2^32
     int mode;                // PackMode
-    int vec;                 // K-major source: 16-byte vector loads are legal
     const int32_t *exps;     // fp8: tile exponents (Fp8ExpArgs); two-piece FP16:
                              // the rows' amax bits (RowAmaxArgs), as uint32
     int64_t exp_tiles_k;
