@@ -434,51 +434,60 @@ DEVI MnUnit mn_decode(uint32_t u, const OperandGeom &g) {
 // each thread packs and writes its own unit, so consecutive threads write
 // consecutive 16-byte rows.  Host: rows of the source 16-byte aligned, grp_rows
 // and, for a striped operand, S_r multiples of RW; total_units is then one too.
-template <int KIND>
+// U: such blocks of 256 units per workgroup, their loads issued together.
+template <int KIND, int U>
 DEVI void pack_mn_block(const PackArgs &a, uint32_t blk, void *lds) {
     typedef PackTraits<KIND> T;
     typedef typename T::S S;
     constexpr int UE = T::UE, RW = 16 / (int)sizeof(S), RUNS = 256 / RW;
-    S(*tile)[256] = (S(*)[256])lds;             // [UE][256]
+    S(*tile)[256] = (S(*)[256])lds;             // [U][UE][256]
     const OperandGeom &g = a.g;
     const S *src = (const S *)a.src;
-    const uint32_t base = blk * 256u;
+    const uint32_t base = blk * (256u * U);
+    constexpr int PER = UE * RUNS / 256;        // runs per thread and block of units
+    union Run { u32x4 w; S s[RW]; } v[U * PER];
 #pragma unroll
-    for (int i = 0; i < UE * RUNS / 256; ++i) {
-        const uint32_t q = threadIdx.x + 256u * i;
+    for (int i = 0; i < U * PER; ++i) {
+        const uint32_t q = threadIdx.x + 256u * (i % PER);
         const uint32_t run = q % RUNS, e = q / RUNS;
-        const uint32_t u = base + run * RW;     // units u .. u + RW - 1: rows rr .. of one group
-        union { u32x4 w; S s[RW]; } v;
-        v.w = u32x4{0, 0, 0, 0};
+        const uint32_t u = base + i / PER * 256u + run * RW;     // units u .. u + RW - 1: rows rr .. of one group
+        v[i].w = u32x4{0, 0, 0, 0};
         if (u < (uint32_t)a.total_units) {
             const MnUnit d = mn_decode<KIND>(u, g);
             const int64_t kk = d.kk0 + e;
             if (d.at.valid && d.kin0 + e < g.S_k && kk < g.Kd) {
                 const S *q4 = src + kk * a.ld + d.at.row;
                 if (d.at.row + RW <= g.R) {     // one stripe: S_r % RW == 0
-                    v.w = *(const u32x4 *)q4;
+                    v[i].w = *(const u32x4 *)q4;
                 } else {
 #pragma unroll
                     for (int r = 0; r < RW; ++r)
-                        if (d.at.row + r < g.R) v.s[r] = q4[r];
+                        if (d.at.row + r < g.R) v[i].s[r] = q4[r];
                 }
             }
         }
-        *(u32x4 *)&tile[e][run * RW] = v.w;
+    }
+#pragma unroll
+    for (int i = 0; i < U * PER; ++i) {
+        const uint32_t q = threadIdx.x + 256u * (i % PER);
+        *(u32x4 *)&tile[i / PER * UE + q / RUNS][q % RUNS * RW] = v[i].w;
     }
     __syncthreads();
-    const uint32_t u = base + threadIdx.x;
-    if (u >= (uint32_t)a.total_units) return;
-    const MnUnit d = mn_decode<KIND>(u, g);
-    float vals_f[UE];
-    double vals_d[1] = {0.0};
-    uint16_t vals_h[UE];
 #pragma unroll
-    for (int e = 0; e < UE; ++e) {
-        if constexpr (KIND == PK_B16) vals_h[e] = tile[e][threadIdx.x];
-        else vals_f[e] = tile[e][threadIdx.x];
+    for (int b = 0; b < U; ++b) {
+        const uint32_t u = base + b * 256u + threadIdx.x;
+        if (u >= (uint32_t)a.total_units) return;
+        const MnUnit d = mn_decode<KIND>(u, g);
+        float vals_f[UE];
+        double vals_d[1] = {0.0};
+        uint16_t vals_h[UE];
+#pragma unroll
+        for (int e = 0; e < UE; ++e) {
+            if constexpr (KIND == PK_B16) vals_h[e] = tile[b * UE + e][threadIdx.x];
+            else vals_f[e] = tile[b * UE + e][threadIdx.x];
+        }
+        pack_emit<KIND>(a, d.at, d.kb, d.ch, d.half, d.rr, d.kk0, vals_f, vals_d, vals_h);
     }
-    pack_emit<KIND>(a, d.at, d.kb, d.ch, d.half, d.rr, d.kk0, vals_f, vals_d, vals_h);
 }
 
 // One thread makes one 16-byte unit of the packed image (for the split form,
@@ -486,13 +495,25 @@ DEVI void pack_mn_block(const PackArgs &a, uint32_t blk, void *lds) {
 // consecutive rows of one (group, block, chunk, plane), so the packed writes
 // are contiguous; for a row-major (MN-major) source the reads are contiguous
 // too, for a K-major source each thread reads its own 16-32 bytes of a row.
+// A unit: where it goes, and its 16-byte loads if its elements lie side by side.
+template <int KIND>
+struct PackUnit {
+    typedef PackTraits<KIND> T;
+    static const int NV = T::UE * (int)sizeof(typename T::S) / 16;
+    GroupAt at;
+    uint32_t rr, half, ch, kb;
+    int64_t kin0, kk0;
+    bool live, run;
+    u32x4 w[NV];
+};
+
 template <int KIND, int KMAJOR>
-DEVI void pack_block(const PackArgs &a, uint32_t blk) {
+DEVI void unit_load(const PackArgs &a, uint32_t u, PackUnit<KIND> &x) {
     typedef PackTraits<KIND> T;
     typedef typename T::S S;
     const OperandGeom &g = a.g;
-    const uint32_t u = blk * 256u + threadIdx.x;            // host: total_units < 2^32
-    if (u >= (uint32_t)a.total_units) return;
+    x.live = false;
+    if (u >= (uint32_t)a.total_units) return;               // host: total_units < 2^32
     const int KC = g.chunk_bytes / T::ESZ;      // elements per chunk row
     const uint32_t UPR = (uint32_t)(g.chunk_bytes / 16);  // 16-byte planes per chunk row
     const uint32_t nch = (uint32_t)g.nch, p = (uint32_t)g.p, gr = (uint32_t)g.grp_rows;
@@ -521,38 +542,49 @@ DEVI void pack_block(const PackArgs &a, uint32_t blk) {
         kb = t % p;
         grp = t / p;
     }
-    const GroupAt at = group_at(g, grp, rr);
-    const int64_t row = at.row;
-    const bool rvalid = at.valid;
-    const int64_t kin0 = (int64_t)ch * KC + half * T::UE;
-    const int64_t kk0 = (int64_t)kb * g.S_k + kin0;
-    const S *src = (const S *)a.src;
-    float vals_f[T::UE];
-    double vals_d[T::UE];
-    uint16_t vals_h[T::UE];
-    if (KMAJOR && a.embed == EMB_NONE && kk0 + T::UE <= g.Kd) {
+    x.live = true;
+    x.at = group_at(g, grp, rr);
+    x.rr = rr; x.half = half; x.ch = ch; x.kb = kb;
+    x.kin0 = (int64_t)ch * KC + half * T::UE;
+    x.kk0 = (int64_t)kb * g.S_k + x.kin0;
+    x.run = KMAJOR && a.embed == EMB_NONE && x.kk0 + T::UE <= g.Kd;
+    if (x.run) {
         // The unit's elements lie side by side in the row: 16-byte loads at the
         // elements' own alignment, what belongs to the next block cleared.
         // (One element a load wherever rows or blocks were not 16-byte aligned:
         // split-BF16 1100 x 900 x 1000 in 125-wide blocks, the call, 31.3 us, 30.0 here;
         // the complex step of 1000 x 700 x 900 149.2 and 147.8.)
-        constexpr int SB = (int)sizeof(S);             // source element bytes
-        constexpr int NV = T::UE * SB / 16;            // 16-byte loads per unit
-        const bool ok = rvalid && kin0 < g.S_k;
-        const S *q = src + row * a.ld + kk0;
-        const int have = g.S_k - kin0 < T::UE ? (int)(g.S_k - kin0) : T::UE;
-        u32x4 w[NV];
+        const bool ok = x.at.valid && x.kin0 < g.S_k;
+        const S *q = (const S *)a.src + x.at.row * a.ld + x.kk0;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            w[i] = u32x4{0, 0, 0, 0};
-            if (ok) __builtin_memcpy(&w[i], q + i * (16 / SB), 16);
+        for (int i = 0; i < x.NV; ++i) {
+            x.w[i] = u32x4{0, 0, 0, 0};
+            if (ok) __builtin_memcpy(&x.w[i], q + i * (16 / (int)sizeof(S)), 16);
         }
+    }
+}
+
+template <int KIND, int KMAJOR>
+DEVI void unit_store(const PackArgs &a, const PackUnit<KIND> &x) {
+    typedef PackTraits<KIND> T;
+    typedef typename T::S S;
+    if (!x.live) return;
+    const OperandGeom &g = a.g;
+    const int64_t row = x.at.row, kin0 = x.kin0, kk0 = x.kk0;
+    const bool rvalid = x.at.valid;
+    const S *src = (const S *)a.src;
+    float vals_f[T::UE];
+    double vals_d[T::UE];
+    uint16_t vals_h[T::UE];
+    if (KMAJOR && x.run) {
+        constexpr int SB = (int)sizeof(S);             // source element bytes
+        const int have = g.S_k - kin0 < T::UE ? (int)(g.S_k - kin0) : T::UE;
 #pragma unroll
         for (int e = 0; e < T::UE; ++e) {
             const int byte = e * SB;
-            const uint32_t word = w[byte / 16][(byte % 16) / 4];
+            const uint32_t word = x.w[byte / 16][(byte % 16) / 4];
             if constexpr (KIND == PK_F64) {
-                vals_d[e] = e < have ? __hiloint2double((int)w[byte / 16][(byte % 16) / 4 + 1], (int)word) : 0.0;
+                vals_d[e] = e < have ? __hiloint2double((int)x.w[byte / 16][(byte % 16) / 4 + 1], (int)word) : 0.0;
             } else if constexpr (KIND == PK_B16) {
                 vals_h[e] = e < have ? (uint16_t)(word >> ((byte % 4) * 8)) : (uint16_t)0;
             } else {
@@ -588,7 +620,17 @@ DEVI void pack_block(const PackArgs &a, uint32_t blk) {
             else vals_f[e] = ok ? (neg ? -(float)src[idx] : (float)src[idx]) : 0.0f;
         }
     }
-    pack_emit<KIND>(a, at, kb, ch, half, rr, kk0, vals_f, vals_d, vals_h);
+    pack_emit<KIND>(a, x.at, x.kb, x.ch, x.half, x.rr, kk0, vals_f, vals_d, vals_h);
+}
+
+// U units a thread, 256 apart, their loads issued before the first is used.
+template <int KIND, int KMAJOR, int U>
+DEVI void pack_block(const PackArgs &a, uint32_t blk) {
+    PackUnit<KIND> x[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) unit_load<KIND, KMAJOR>(a, (blk * U + i) * 256u + threadIdx.x, x[i]);
+#pragma unroll
+    for (int i = 0; i < U; ++i) unit_store<KIND, KMAJOR>(a, x[i]);
 }
 
 // Both operands of a product in one launch: workgroups below nb0 pack the
@@ -600,19 +642,19 @@ struct PackPair {
     uint32_t nb0;
 };
 
-template <int KIND, int MODE>
+template <int KIND, int MODE, int U>
 DEVI void pack_one(const PackArgs &a, uint32_t blk, void *lds) {
-    if constexpr (MODE == PACK_MN_LDS) pack_mn_block<KIND>(a, blk, lds);
-    else pack_block<KIND, MODE == PACK_K>(a, blk);
+    if constexpr (MODE == PACK_MN_LDS) pack_mn_block<KIND, U>(a, blk, lds);
+    else pack_block<KIND, MODE == PACK_K, U>(a, blk);
 }
 
-template <int KIND, int MA, int MB>
+template <int KIND, int MA, int MB, int U>
 __global__ __launch_bounds__(256) void pack_kernel(PackPair p) {
     constexpr bool LDS = MA == PACK_MN_LDS || MB == PACK_MN_LDS;
     typedef PackTraits<KIND> T;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS ? T::UE * 256 * sizeof(typename T::S) : 16];
-    if (blockIdx.x < p.nb0) pack_one<KIND, MA>(p.x[0], blockIdx.x, lds);
-    else pack_one<KIND, MB>(p.x[1], blockIdx.x - p.nb0, lds);
+    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS ? U * T::UE * 256 * sizeof(typename T::S) : 16];
+    if (blockIdx.x < p.nb0) pack_one<KIND, MA, U>(p.x[0], blockIdx.x, lds);
+    else pack_one<KIND, MB, U>(p.x[1], blockIdx.x - p.nb0, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -620,13 +662,33 @@ __global__ __launch_bounds__(256) void pack_kernel(PackPair p) {
 // ---------------------------------------------------------------------------
 static inline unsigned nblocks(int64_t work) { return (unsigned)((work + 255) / 256); }
 
+// Units per thread.  A unit of the 16-bit and FP32 forms is one 16-byte load and
+// one such store; with one a thread too few bytes are in flight.  Four where
+// that leaves every CU 16 workgroups, and not for the element-wise MN reads:
+// both operands of FP32 4096^3, transposed, 65 to 56 us (268 MB: 4.1 to 4.8 TB/s),
+// of BF16 8192^3 143 to 138 (537 MB: 3.8 to 3.9 TB/s).  The forms with pieces have
+// two loads and two or three stores a unit and reach 5 to 6 TB/s with one.
+static int units_per_thread(int kind, const PackArgs &a, const PackArgs &b) {
+    if ((kind != PK_B16 && kind != PK_F32) || a.mode == PACK_MN || b.mode == PACK_MN) return 1;
+    const int64_t n = a.total_units + b.total_units;
+    return n >= (int64_t)16 * 256 * 1024 && n < (int64_t)1 << 31 ? 4 : 1;
+}
+
 template <int KIND>
-static hipError_t launch_pack_k(const PackPair &p, unsigned nb, hipStream_t st) {
-    const int ma = p.x[0].mode, mb = p.x[1].mode;
-#define HS_PACK(A_, B_)                                                                          \
-    if (ma == A_ && mb == B_) {                                                                  \
-        hipLaunchKernelGGL((pack_kernel<KIND, A_, B_>), dim3(nb), dim3(256), 0, st, p);          \
+static hipError_t launch_pack_k(const PackArgs &a, const PackArgs &b, hipStream_t st) {
+    const int ma = a.mode, mb = b.mode, U = units_per_thread(KIND, a, b);
+    const unsigned na = nblocks((a.total_units + U - 1) / U), nb = na + nblocks((b.total_units + U - 1) / U);
+    const PackPair p{{a, b}, na};
+    if (nb == 0) return hipSuccess;
+#define HS_PACK_U(A_, B_, U_)                                                                    \
+    if (ma == A_ && mb == B_ && U == U_) {                                                       \
+        hipLaunchKernelGGL((pack_kernel<KIND, A_, B_, U_>), dim3(nb), dim3(256), 0, st, p);      \
         return hipGetLastError();                                                                \
+    }
+#define HS_PACK(A_, B_)                                                                          \
+    HS_PACK_U(A_, B_, 1)                                                                         \
+    if constexpr ((KIND == PK_B16 || KIND == PK_F32) && A_ != PACK_MN && B_ != PACK_MN) {        \
+        HS_PACK_U(A_, B_, 4)                                                                     \
     }
     // the static operand is read along the contraction (NN, NT) or across it (TN)
     HS_PACK(PACK_K, PACK_K)
@@ -639,20 +701,18 @@ static hipError_t launch_pack_k(const PackPair &p, unsigned nb, hipStream_t st) 
         HS_PACK(PACK_MN_LDS, PACK_MN_LDS)
     }
 #undef HS_PACK
+#undef HS_PACK_U
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_pack(int kind, const PackArgs &a, const PackArgs &b, hipStream_t st) {
-    PackPair p{{a, b}, nblocks(a.total_units)};
-    const unsigned nb = p.nb0 + nblocks(b.total_units);
-    if (nb == 0) return hipSuccess;
     switch (kind) {
-        case PK_F64: return launch_pack_k<PK_F64>(p, nb, st);
-        case PK_F32: return launch_pack_k<PK_F32>(p, nb, st);
-        case PK_B16: return launch_pack_k<PK_B16>(p, nb, st);
-        case PK_SPLIT3: return launch_pack_k<PK_SPLIT3>(p, nb, st);
-        case PK_FP8: return launch_pack_k<PK_FP8>(p, nb, st);
-        case PK_SPLIT2F16: return launch_pack_k<PK_SPLIT2F16>(p, nb, st);
+        case PK_F64: return launch_pack_k<PK_F64>(a, b, st);
+        case PK_F32: return launch_pack_k<PK_F32>(a, b, st);
+        case PK_B16: return launch_pack_k<PK_B16>(a, b, st);
+        case PK_SPLIT3: return launch_pack_k<PK_SPLIT3>(a, b, st);
+        case PK_FP8: return launch_pack_k<PK_FP8>(a, b, st);
+        case PK_SPLIT2F16: return launch_pack_k<PK_SPLIT2F16>(a, b, st);
     }
     return hipErrorInvalidValue;
 }

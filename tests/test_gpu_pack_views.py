@@ -39,3 +39,31 @@ def test_rows_at_any_element(dt, case):
     C0 = hs.hs_gemm(A, Bm, dtype=dt, p=p, K=K, out=poisoned((m, n), out))
     torch.cuda.synchronize()
     assert np.array_equal(host(C), host(C0))
+
+
+# packed operands of 64 MiB and more are laid out four units a thread: rows,
+# columns and blocks that end inside a thread's four, each way of reading them
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("m, n, k, p, K", [(4090, 4104, 4133, 3, 3), (4096, 4096, 4096, 4, 2)])
+def test_four_units_a_thread(dt, m, n, k, p, K):
+    if not gpu_available():
+        pytest.skip("no GPU")
+    A, A64 = to_dev(inputs.small_int((m, k), 4310, -4, 4), dt)
+    At, _ = to_dev(np.ascontiguousarray(A64.T), dt)
+    Bm, B64 = to_dev(inputs.small_int((k, n), 4311, -4, 4), dt)
+    G, G64 = to_dev(inputs.small_int((m, n), 4312, -4, 4), "f32")
+    note("four units", dt, m, n, k, p, K)
+    C = hs.hs_gemm(A, Bm, dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
+    Ct = hs.hs_gemm_tn(At, Bm, dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
+    torch.cuda.synchronize()
+    # sums of at most 4133 products of magnitude 16: exact in FP32 in any order
+    a32, b32, g32 = (x.astype(np.float32) for x in (A64, B64, G64))
+    ref = a32 @ b32
+    assert np.array_equal(host(C), ref)
+    assert np.array_equal(host(Ct), ref)
+    if dt == "f32":
+        dA, dB = hs.hs_gemm_backward(A, Bm, G, dtype=dt, p=p, K=K)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(dA), g32 @ b32.T)
+        assert np.array_equal(host(dB), a32.T @ g32)
