@@ -177,7 +177,8 @@ int wave_percent(const FormInfo &f, int tr) {
 }
 
 // MFMA tiles down and across the wave kernel's tile, and waves per workgroup;
-// n(tr, tc) counts the output tiles.  Times in us, n x n x k products.
+// n(tr, tc) counts the output tiles; wide: columns padded to 96 take no more
+// workspace than to 256.  Times in us, n x n x k products.
 //
 // A wave of the FP32 and FP64 forms spends 64 cycles on the MFMA of two cheap
 // fragments: small tiles, 4 waves (FP32 2048^3: 139 with 4 waves, 193 with 2,
@@ -197,14 +198,15 @@ int wave_percent(const FormInfo &f, int tr) {
 // are at most 256, the 16-bit forms take these with 8 waves (1100 x 900 x 1000,
 // 270 tiles against 180: split-BF16 28.4 to 23.0, two-piece FP16 20.4 to 17.4,
 // BF16 13.9 to 12.8; 800 x 1100 x 3000: 62 to 43, 43 to 31, 24 to 19; FP8 gains
-// nothing, 11.3 and 11.4, nor do fewer than 8 chunks).  4 x 2 tiles need all
+// nothing, 11.3 and 11.4, nor do fewer than 8 chunks); or 2 x 3 ones likewise
+// (1000 x 1400 x 1400: split-BF16 35 to 29, two-piece FP16 25.4 to 21.6, BF16 16.3 to 14.6).  4 x 2 tiles need all
 // registers of a SIMD for one wave; for the split forms they win where such
 // waves are on nearly every SIMD, 512 tiles of two waves or 1024 of one (2048^3:
 // 99 to 93 and 65 to 61; 2500^3, 800 tiles: 193 to 167 and 134 to 117; 1800 x
 // 2200 x 1000, 560: 64, 73 here), from 64 chunks (split-BF16 2048 x 2048 x 512: 32, 35
 // here) or 128 (two-piece FP16 2560 x 2560 x 1024: 60, 65 here).
 template <class Count>
-void wave_shape(const FormInfo &f, Count n, int64_t chunks, int *tr, int *tc, int *kg) {
+void wave_shape(const FormInfo &f, Count n, bool wide, int64_t chunks, int *tr, int *tc, int *kg) {
     const bool slow = f.fam == FAM_F64 || f.fam == FAM_F32, b16 = f.fam == FAM_BF16 || f.fam == FAM_F16;
     const bool split = b16 && f.form != 0;
     auto fills = [](int64_t tiles, int64_t slots, int percent) {
@@ -223,6 +225,10 @@ void wave_shape(const FormInfo &f, Count n, int64_t chunks, int *tr, int *tc, in
     } else if (b16 && n22 > kCUs && n(3, 2) <= kCUs && chunks >= 8) {
         *tr = 3;
         *tc = 2;
+        *kg = 8;
+    } else if (b16 && n22 > kCUs && wide && n(2, 3) <= kCUs && chunks >= 8) {
+        *tr = 2;
+        *tc = 3;
         *kg = 8;
     } else if (n22 >= 256) {
         *tr = *tc = 2;
@@ -250,7 +256,8 @@ void plan_wave(Plan *P) {
     auto count = [&](int tr, int tc) {
         return (int64_t)P->K * ceil_div(L, wave_tile(fam, tr)) * ceil_div(P->N, wave_tile(fam, tc));
     };
-    wave_shape(P->f, count, chunks, &W.tr, &W.tc, &W.kg);
+    const bool wide = ceil_div(P->N, 96) * 96 <= P->gb.GS * P->gb.grp_rows;
+    wave_shape(P->f, count, wide, chunks, &W.tr, &W.tc, &W.kg);
     if (tiles * 100 >= ceil_div(tiles, kCUs) * kCUs * wave_percent(P->f, W.tr)) return;
     const int64_t wt = count(W.tr, W.tc);
     if (wt > (int64_t)1 << 26) return;                    // 32-bit grid in threads

@@ -4,7 +4,7 @@
 //
 // What bounds such a launch is not the MFMA rate but how many SIMDs have work
 // and how long one wave's chain of chunks is.  So the output tile is small
-// (64 x 64, or 32 x 32 where even those are fewer than the CUs; 96 x 64 or
+// (64 x 64, or 32 x 32 where even those are fewer than the CUs; 96 x 64, 64 x 96 or
 // 128 x 64 where these come out just under a round of the chip), and the
 // workgroup's kg waves share one tile: each walks its own run of the
 // tile's chunks in the step order of mm_kernel (partials l = K-1 .. 0, steps
@@ -359,6 +359,10 @@ hipError_t launch_wave(int fam, int form, int tr, int tc, const WaveArgs &a, hip
     HS_WV(FAM_F16, 2, 3, 2);
     HS_WV(FAM_BF16, 0, 3, 2);
     HS_WV(FAM_BF16, 1, 3, 2);
+    HS_WV(FAM_F16, 0, 2, 3);
+    HS_WV(FAM_F16, 2, 2, 3);
+    HS_WV(FAM_BF16, 0, 2, 3);
+    HS_WV(FAM_BF16, 1, 2, 3);
     HS_WV(FAM_F16, 2, 4, 2);
     HS_WV(FAM_BF16, 1, 4, 2);
 #undef HS_WALL

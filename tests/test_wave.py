@@ -110,10 +110,12 @@ def test_wave_fp8(dt, case):
 
 
 # 96 x 64 tiles (two-round counts of 64 x 64 ones): last groups of 65, 1 and 96
-# rows, eight waves and the four that eight chunks allow; 128 x 64 tiles (split
+# rows, eight waves and the four that eight chunks allow; 64 x 96 tiles with last
+# columns of 56, 96 and 4; 128 x 64 tiles (split
 # forms): 512 tiles of two waves, 800 of one, last groups of 127, 98 and 1 rows
 TALL = ([(dt, c) for dt in ("bf16", "f16", "split3_bf16", "split2_f16")
-         for c in [(1090, 961, 250, 2, 2), (1537, 700, 113, 1, 1), (2016, 577, 516, 3, 3)]] +
+         for c in [(1090, 961, 250, 2, 2), (1537, 700, 113, 1, 1), (2016, 577, 516, 3, 3),
+                   (1000, 1400, 113, 2, 2), (1000, 1152, 200, 10, 10), (995, 1060, 333, 10, 10)]] +
         [(dt, c) for dt in ("split3_bf16", "split2_f16")
          for c in [(2047, 2010, 2050, 2, 1), (2500, 2500, 2100, 4, 2), (1281, 2500, 2049, 1, 1)]])
 
