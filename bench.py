@@ -190,7 +190,7 @@ def kernel_source_sha256():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_cs_9809105_amd", "csrc")
-    for name in ("hs_kernels.hip", "hs_internal.h", "hs_api.cpp"):
+    for name in ("hs_kernels.hip", "hs_mfma.h", "hs_internal.h", "hs_api.cpp"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

@@ -17,8 +17,8 @@
  *
  * This is Algorithm HYPER-SYSTOLIC applied to C^T = B^T A^T (the paper moves
  * A and keeps columns; here rows are kept and B moves).  The "cshift" of a
- * stripe is the order in which its tiles are fetched from HBM into registers
- * and a double-buffered LDS ring.  The back-shift is done by a collector:
+ * stripe is the order in which its tiles are fetched from HBM into an LDS
+ * ring or into registers.  The back-shift is done by a collector:
  * the workgroup that owns an output tile of stripe r visits the virtual
  * processors r + K - 1, .., r (base C reversed), forms each one's partial
  * c^l on the spot and accumulates it into the same registers, so the K
