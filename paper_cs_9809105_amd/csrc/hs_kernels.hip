@@ -831,11 +831,11 @@ hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t l
 template <typename T, int CX>
 static hipError_t launch_gemv_t(const GemvArgs &a, hipStream_t st) {
     const dim3 grid((unsigned)((a.m * a.waves + 3) / 4));
-    // A of 256 MiB or more does not stay whole in the memory-side cache between
-    // calls; called one after the other it is then read faster past the caches
-    // (FP32 8192 x 8192: 42.8 us a call against 46.3; 8192 x 2048, which stays:
-    // 13.8 against 12.6).  Only the same 8192 x 8192 matrix replayed back to back
-    // in a graph, of which most does stay, would gain from caching: 41.7 here, 38.9.
+    // A of 256 MiB or more does not stay whole in the memory-side cache.  Read
+    // past the caches, matrices not read just before take less time (FP32 8192 x
+    // 8192, four in turn: 42.8 us a call against 46.3) and the same one of just
+    // that size over and over takes more, as most of it does stay (41.1 against
+    // 38.2).  8192 x 2048, which stays whole: 13.8 against 12.6.
     if (a.m * a.n * (int64_t)(sizeof(T) * (1 + CX)) >= (int64_t)256 << 20)
         HS_LAUNCH_TIMED((gemv_kernel<T, CX, 1>), grid, dim3(256), 0, st, a);
     else
