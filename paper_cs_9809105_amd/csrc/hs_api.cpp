@@ -168,10 +168,10 @@ void layout_workspace(Plan *P) {
 // Far left of the line: 1024^3 FP32 35 / 240, split-BF16 30 / 105.  FP64
 // always takes it (an LDS-tiled 64 x 64 kernel measured 3075 us at 4096^3
 // against 1852, 400 against 259 at 2048^3, 18.6 against 5.8 at 256^3).
-// 4 x 2 tiles (wave_shape: only where they fill the chip) move the line to u =
-// 0.97, split-BF16 and two-piece FP16: u = 1/2 (2048^3) 93 / 103 and 61 / 67;
-// u = 0.78 (2500^3) 167 / 252 and 117 / 140; u = 0.95 (2816^3) 207 / 274 and 142 / 155;
-// u = 1 (4096 x 2048 x 2048) 157 / 142 and 110 / 91.
+// 4 x 2 tiles (wave_shape: only where they fill the chip) move the line, split-BF16
+// and two-piece FP16: u = 1/2 (2048^3) 102 / 122 and 84 / 96, 1792 x 1792 x 2500 108 /
+// 140 and 91 / 107, split-BF16 u = 0.47 (2816 x 2816 x 1900) 159 / 191; u = 1 (4096 x
+// 2048 x 2048) 157 / 142 and 110 / 91, so r is 0.97.
 int wave_percent(const FormInfo &f, int tr) {
     return f.fam == FAM_F64 ? 101 : f.fam == FAM_F32 ? 88 : tr == 4 ? 97 : 50;
 }
@@ -201,12 +201,19 @@ int wave_percent(const FormInfo &f, int tr) {
 // nothing, 11.3 and 11.4, nor do fewer than 8 chunks); or 2 x 3 ones likewise
 // (1000 x 1400 x 1400: split-BF16 35 to 29, two-piece FP16 25.4 to 21.6, BF16 16.3 to 14.6).  4 x 2 tiles need all
 // registers of a SIMD for one wave; for the split forms they win where such
-// waves are on nearly every SIMD, 512 tiles of two waves or 1024 of one (2048^3:
-// 99 to 93 and 65 to 61; 2500^3, 800 tiles: 193 to 167 and 134 to 117; 1800 x
-// 2200 x 1000, 560: 64, 73 here), from 64 chunks (split-BF16 2048 x 2048 x 512: 32, 35
-// here) or 128 (two-piece FP16 2560 x 2560 x 1024: 60, 65 here).
+// waves are on nearly every SIMD, 512 tiles of two waves or 1024 of one (2 x 2
+// tiles here, split-BF16 2048^3: 124 to 102, 2500 x 2500 x 1500, 800 tiles: 151 to 118;
+// but 1800 x 2200 x 1000, 560: 64, 73 here), from 64 chunks (split-BF16 2048 x 2048 x
+// 512: 32, 35 here) or 128 (two-piece FP16 2560 x 2560 x 1024: 60, 65 here).
+//
+// parts: the workgroups that mm_kernel would split a tile's step order over.  An
+// FP32 sum's rounding error grows with the length of its chain, so a tile has at
+// least as many waves, and 4 x 2 tiles are for products that need no more than
+// their one or two: with twice the waves they lose to mm_kernel (split-BF16 2500 x
+// 2500 x 2500, two parts: 215 against 177; 2048 x 1500 x 6000, four: 252 against 213;
+// with one wave or two 188 and 233, at 1.4 times the error).
 template <class Count>
-void wave_shape(const FormInfo &f, Count n, bool wide, int64_t chunks, int *tr, int *tc, int *kg) {
+void wave_shape(const FormInfo &f, Count n, bool wide, int64_t chunks, int parts, int *tr, int *tc, int *kg) {
     const bool slow = f.fam == FAM_F64 || f.fam == FAM_F32, b16 = f.fam == FAM_BF16 || f.fam == FAM_F16;
     const bool split = b16 && f.form != 0;
     auto fills = [](int64_t tiles, int64_t slots, int percent) {
@@ -218,7 +225,7 @@ void wave_shape(const FormInfo &f, Count n, bool wide, int64_t chunks, int *tr, 
         if (n22 >= 900 && (f.fam == FAM_F64 || fills(n22, 512, 90))) *tr = *tc = 2;
         *kg = n(*tr, *tc) >= 8192 ? 1 : 4;
     } else if (split && chunks >= (f.form == 1 ? 64 : 128) && n42 > 256 && n42 <= 1024 &&
-               fills(n42, n42 <= 512 ? 512 : 1024, 75)) {
+               fills(n42, n42 <= 512 ? 512 : 1024, 75) && parts <= (n42 <= 512 ? 2 : 1)) {
         *tr = 4;
         *tc = 2;
         *kg = n42 <= 512 ? 2 : 1;
@@ -239,6 +246,7 @@ void wave_shape(const FormInfo &f, Count n, bool wide, int64_t chunks, int *tr, 
     // long sums on few tiles: 300 x 320 x 6000 BF16 13 against 15
     if (*tr * *tc <= 4 && n(*tr, *tc) <= 128 && chunks >= 256) *kg = 8;
     while (*kg > 1 && chunks < 2 * *kg) *kg /= 2;
+    while (*kg < parts) *kg *= 2;
 }
 
 // Replans *P for the wave kernel where that is the faster one.  The packed
@@ -257,7 +265,7 @@ void plan_wave(Plan *P) {
         return (int64_t)P->K * ceil_div(L, wave_tile(fam, tr)) * ceil_div(P->N, wave_tile(fam, tc));
     };
     const bool wide = ceil_div(P->N, 96) * 96 <= P->gb.GS * P->gb.grp_rows;
-    wave_shape(P->f, count, wide, chunks, &W.tr, &W.tc, &W.kg);
+    wave_shape(P->f, count, wide, chunks, P->nsplit, &W.tr, &W.tc, &W.kg);
     if (tiles * 100 >= ceil_div(tiles, kCUs) * kCUs * wave_percent(P->f, W.tr)) return;
     const int64_t wt = count(W.tr, W.tc);
     if (wt > (int64_t)1 << 26) return;                    // 32-bit grid in threads
@@ -344,15 +352,15 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
     if ((int64_t)p * nch >= (int64_t)1 << 31) return HS_ERR_NOT_SUPPORTED;
 
     // Output tiles under the CU count: split each tile's step order over
-    // nsplit workgroups (at most 4, at least 64 stages each; 128 of the plain
-    // 16-bit and FP8 forms' short ones), whose sums a fixed-order FP64 pass adds
-    // (the planes below)
+    // nsplit workgroups (at most 4, at least 64 stages each, the plain 16-bit and
+    // FP8 forms' short ones counted in pairs), whose sums a fixed-order FP64 pass
+    // adds (the planes below)
     {
-        const int64_t nstages = (int64_t)p * (nch / CPS);
+        const int64_t spb = nch / CPS, nstages = (int64_t)p * spb;
         const int64_t tiles = (int64_t)P->K * ceil_div(P->Kt, P->G) * a.GS * b.GS;
-        const int64_t least = P->f.form == 0 && (fp8 || P->f.packed_esz == 2) ? 128 : 64;
+        const int64_t pair = P->f.form == 0 && (fp8 || P->f.packed_esz == 2) ? 2 : 1;
         int64_t ns = 1;
-        if (tiles > 0 && tiles < kCUs) ns = std::min<int64_t>({4, kCUs / tiles, nstages / least});
+        if (tiles > 0 && tiles < kCUs) ns = std::min<int64_t>({4, kCUs / tiles, p * ceil_div(spb, pair) / 64});
         if (ns < 2) ns = 1;
         P->split_stages = (int)ceil_div(nstages, ns);
         P->nsplit = (int)ceil_div(nstages, P->split_stages);

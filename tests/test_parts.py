@@ -1,0 +1,87 @@
+"""Sums over long contractions keep short FP32 chains: a product of few 256 x 256
+tiles is summed in parts (1024 contraction elements or more each, 4096 of the
+plain 16-bit forms and refined FP8, 8192 of FP8; at most four, and no more than
+fill the 256 CUs), whichever kernel and tile takes it."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_cs_9809105_amd import binding as B
+from paper_cs_9809105_amd import inputs
+from tests._gpu import check, gpu_available, host, note, poisoned, to_dev
+from tests._launches import launches
+
+if gpu_available():
+    import torch
+    import paper_cs_9809105_amd as hs
+
+# (dtype, m, n, k, p, K, 256 x 256 tiles, parts)
+CASES = [("split3_bf16", 2500, 2500, 2560, 1, 1, 100, 2), ("split2_f16", 2500, 2500, 6016, 1, 1, 100, 2),
+         ("split3_bf16", 2816, 2816, 2816, 1, 1, 121, 2), ("split3_bf16", 2048, 1500, 6016, 1, 1, 48, 4),
+         ("split2_f16", 1300, 2300, 5056, 1, 1, 54, 4), ("split2_f16", 1792, 2500, 3072, 1, 1, 70, 3),
+         ("bf16", 2500, 2500, 8192, 1, 1, 100, 2), ("f16", 2048, 1500, 16384, 1, 1, 48, 4),
+         ("fp8_e4m3", 2496, 2496, 16384, 1, 1, 100, 2), ("fp8_e4m3_r1", 2496, 2496, 8192, 1, 1, 100, 2),
+         ("f32", 1600, 1600, 6144, 1, 1, 49, 4), ("f32", 2560, 2304, 12288, 1, 1, 90, 2),
+         # blocks that end inside a pair of the short stages
+         ("bf16", 2048, 2048, 4160, 64, 1, 64, 2), ("f16", 1024, 2048, 12480, 64, 1, 32, 4)]
+
+
+def test_no_fewer_parts_than_tiles_leave_cus_idle():
+    got = launches([("gemm", m, n, k, B.DTYPES[dt], p, K) for dt, m, n, k, p, K, _, _ in CASES])
+    for (dt, m, n, k, p, K, tiles, parts), r in zip(CASES, got):
+        assert r["status"] == 0
+        main = [x for x in r["launches"] if "wave_kernel" in x["kernel"] or "mm_kernel" in x["kernel"]]
+        assert len(main) == 1
+        planes = any("backshift_kernel" in x["kernel"] for x in r["launches"])
+        if "mm_kernel" in main[0]["kernel"]:
+            assert main[0]["grid"][0] == tiles * parts and planes, (dt, m, n, k, p, K)
+        else:
+            assert planes or main[0]["block"][0] // 64 >= parts, (dt, m, n, k, p, K, main)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [c for c in CASES if c[4] == 1 and c[7] in (2, 4)])
+def test_a_part_does_not_see_the_sum_before_it(case):
+    """First part 2^24 + 2, second 1 - 2^24: each exact in FP32, and their sum, 3,
+    exact.  In one chain 2^24 + 2 + 1 has no FP32 value, and the sum is 2 or 4."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    dt, m, n, k, p, K, _, parts = case
+    h = k // parts
+    A, Bm = np.zeros((m, k)), np.zeros((k, n))
+    for at, a, b in ((0, 2.0 ** 12, 2.0 ** 12), (128, 1, 2), (h, 1, 1), (h + 128, -2.0 ** 12, 2.0 ** 12)):
+        A[:, at], Bm[at, :] = a, b
+    note("parts", case)
+    C = hs.hs_gemm(to_dev(A, dt)[0], to_dev(Bm, dt)[0], dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(C), np.full((m, n), 3.0))
+
+
+# 128 x 64 tiles of one wave (no parts): last groups of 98 and 54 rows
+WIDE = [("split3_bf16", 2500, 2500, 1100, 4, 2, "Li2ELi1ELi4ELi2E"), ("split2_f16", 2366, 2305, 2100, 13, 13, "Li3ELi2ELi4ELi2E")]
+
+
+def test_wide_tiles_of_one_wave_are_taken_where_there_is_one_part():
+    for c, r in zip(WIDE, launches([("gemm", m, n, k, B.DTYPES[dt], p, K) for dt, m, n, k, p, K, _ in WIDE])):
+        main = [x for x in r["launches"] if "wave_kernel" in x["kernel"]][0]
+        assert c[6] in main["kernel"] and main["block"][0] == 64, (c, main)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", WIDE)
+def test_wide_tiles_of_one_wave(case):
+    if not gpu_available():
+        pytest.skip("no GPU")
+    dt, m, n, k, p, K, _ = case
+    rows = sorted({r for t in range(0, m, 128) for r in (t, t + 31, t + 127) if r < m} | {m - 2, m - 1})
+    A, A64 = to_dev(inputs.normal((m, k), seed=4300), dt)
+    Bm, B64 = to_dev(inputs.normal((k, n), seed=4301), dt)
+    note("wide tiles", case)
+    C = hs.hs_gemm(A, Bm, dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
+    torch.cuda.synchronize()
+    check(host(C)[rows], oracle.gemm_rows(A64, B64, rows), dt, A64[rows], B64, what="wide tiles %s" % (case,))
+    Ai, Ai64 = to_dev(inputs.small_int((m, k), 4302, -4, 4), dt)
+    Bi, Bi64 = to_dev(inputs.small_int((k, n), 4303, -4, 4), dt)
+    Ci = hs.hs_gemm(Ai, Bi, dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(Ci), Ai64 @ Bi64)         # exact in float64 in any order
