@@ -94,6 +94,7 @@ struct Plan {
     size_t off_part;                  // their partial planes (nsplit > 1)
     int tr, tc;                       // MFMA tiles down and across the wave kernel's tile; 0: mm_kernel
     int kg;                           // its waves per workgroup
+    bool sums64;                      // their sums are added in FP64
 };
 
 // Compute units of the MI355X: a launch with fewer output tiles than this
@@ -283,6 +284,7 @@ void plan_wave(Plan *P) {
     if (pack_units(a, 1) > kMaxUnits || pack_units(b, 1) > kMaxUnits) return;
     int64_t ns = std::min<int64_t>({(int64_t)P->nsplit, kCUs / wt, chunks / (16 * W.kg)});
     if (ns < 2) ns = 1;
+    W.sums64 = P->nsplit > 1 && W.kg > 2;                 // they stand for its planes; two round alike in FP32
     W.split_stages = (int)ceil_div(chunks, ns);
     W.nsplit = (int)ceil_div(chunks, W.split_stages);
     layout_workspace(&W);
@@ -368,6 +370,7 @@ hs_status make_plan(int64_t M, int64_t N, int64_t Kd, int dt, hs_schedule s, Pla
 
     P->tr = P->tc = 0;
     P->kg = 0;
+    P->sums64 = false;
     layout_workspace(P);
     plan_wave(P);
     if (P->f.fam == FAM_F64 && P->tr == 0 && P->total > 0) return HS_ERR_NOT_SUPPORTED;   // no other FP64 kernel
@@ -481,7 +484,7 @@ hs_status run_product(const Plan &P, const Operand &X, const Operand &Y, void *o
         v.p = P.p; v.K = P.K; v.Kt = P.Kt; v.nch = P.ga.nch; v.S_r = P.ga.S_r;
         v.M = P.M; v.N = P.N; v.n_ntiles = P.gb.GS;
         batch_shape(P.gb.GS, P.ga.GS, &v.grp_v, &v.grp_t);
-        v.kg = P.kg; v.nsplit = P.nsplit; v.split_chunks = P.split_stages; v.part = w + P.off_part;
+        v.kg = P.kg; v.sums64 = P.sums64; v.nsplit = P.nsplit; v.split_chunks = P.split_stages; v.part = w + P.off_part;
         if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
         e = launch_wave(P.f.fam, P.f.form, P.tr, P.tc, v, stream);
         if (g_prof) keep_timing(ev0, ev1);

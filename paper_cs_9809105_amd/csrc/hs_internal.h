@@ -198,6 +198,7 @@ struct WaveArgs {
     int64_t n_ntiles;
     int64_t grp_v, grp_t;          // members x column tiles that run together
     int kg;                        // waves per workgroup, a power of two
+    int sums64;                    // the sums of up to four are added in FP64 (of eight they always are)
     int nsplit;                    // workgroups per tile (planes of part if > 1)
     int split_chunks;              // chunks each of them walks
     void *part;

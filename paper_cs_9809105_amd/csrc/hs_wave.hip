@@ -262,12 +262,16 @@ done:
                 for (int ni = 0; ni < TC; ++ni) store(mi, ni, e, acc[mi][ni][e]);
         return;
     }
-    // every wave leaves its sums in LDS (of eight, the upper four first, which
-    // the lower four add to theirs, so that LDS holds four sets); then wave w adds and stores
-    // quads w, w + kg, .. of accumulator elements, the sets in their order.
+    // Every wave leaves its sums in LDS (of eight, the upper four first, so that
+    // LDS holds four sets); then wave w adds and stores quads w, w + kg, .. of
+    // accumulator elements, the sets in a fixed order: in FP64, rounded once,
+    // where there are eight or they stand for the parts of a split step order (as
+    // its planes are added), else in FP32 (there FP64 takes longer for nothing
+    // that one chain had: BF16 1024^3 16.9 us against 16.4, 256^3 7.5 against 7.3).
     // (A pairwise tree after which one wave stored the tile took longer:
     // split-BF16 256^3 7.9 us against 5.8, 1024^3 22 against 19.)
     typedef E E4 __attribute__((ext_vector_type(4)));
+    typedef double D4 __attribute__((ext_vector_type(4)));
     constexpr int NQ = TR * TC * C::NE / 4;                // quads per lane: (mi, ni, e / 4)
     E4 *buf = (E4 *)red;
     auto leave = [&](int w) {
@@ -280,34 +284,43 @@ done:
                     buf[(w * NQ + (mi * TC + ni) * (C::NE / 4) + h) * 64 + lane] =
                         E4{acc[mi][ni][4 * h], acc[mi][ni][4 * h + 1], acc[mi][ni][4 * h + 2], acc[mi][ni][4 * h + 3]};
     };
-    int sets = a.kg;
-    if (C::MAX_KG == 8 && a.kg == 8) {                   // the upper half first, added by the lower half
-        sets = 4;
-        if (kgi >= 4) leave(kgi - 4);
-        __syncthreads();
-        if (kgi < 4) {
-#pragma unroll
-            for (int mi = 0; mi < TR; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < TC; ++ni)
-#pragma unroll
-                    for (int h = 0; h < C::NE / 4; ++h) {
-                        const E4 v = buf[(kgi * NQ + (mi * TC + ni) * (C::NE / 4) + h) * 64 + lane];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[mi][ni][4 * h + e] += v[e];
-                    }
-            leave(kgi);                                  // its own quads: no other wave reads them before the barrier
-        }
-    } else {
-        leave(kgi);
-    }
-    __syncthreads();
-    for (int q4 = kgi; q4 < NQ; q4 += a.kg) {
-        E4 v = buf[q4 * 64 + lane];
-        for (int w = 1; w < sets; ++w) v += buf[(w * NQ + q4) * 64 + lane];
+    auto sum64 = [&](D4 v, int q4, int sets) {             // v + a quad of the sets
+        for (int w = 0; w < sets; ++w) v += __builtin_convertvector(buf[(w * NQ + q4) * 64 + lane], D4);
+        return v;
+    };
+    auto store_quad = [&](int q4, const E4 &v) {
         const int h = q4 % (C::NE / 4), tile = q4 / (C::NE / 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) store(tile / TC, tile % TC, 4 * h + e, v[e]);
+    };
+    if constexpr (C::MAX_KG == 8 && TR * TC != 4)          // host: 2 x 2 tiles have at most four waves
+        if (a.kg == 8) {
+            constexpr int QW = (NQ + 7) / 8;               // quads per wave
+            D4 v[QW];
+            if (kgi >= 4) leave(kgi - 4);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < QW; ++i)
+                if (kgi + 8 * i < NQ) v[i] = sum64(D4{}, kgi + 8 * i, 4);
+            __syncthreads();                               // the upper sets are read
+            if (kgi < 4) leave(kgi);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < QW; ++i)
+                if (kgi + 8 * i < NQ) store_quad(kgi + 8 * i, __builtin_convertvector(sum64(v[i], kgi + 8 * i, 4), E4));
+            return;
+        }
+    leave(kgi);
+    __syncthreads();
+    for (int q4 = kgi; q4 < NQ; q4 += a.kg) {
+        E4 v;
+        if (a.sums64) {
+            v = __builtin_convertvector(sum64(D4{}, q4, a.kg), E4);
+        } else {
+            v = buf[q4 * 64 + lane];
+            for (int w = 1; w < a.kg; ++w) v += buf[(w * NQ + q4) * 64 + lane];
+        }
+        store_quad(q4, v);
     }
 }
 

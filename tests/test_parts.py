@@ -85,3 +85,34 @@ def test_wide_tiles_of_one_wave(case):
     Ci = hs.hs_gemm(Ai, Bi, dtype=dt, p=p, K=K, out=poisoned((m, n), torch.float32))
     torch.cuda.synchronize()
     assert np.array_equal(host(Ci), Ai64 @ Bi64)         # exact in float64 in any order
+
+
+# (dtype, m, n, k, waves of a tile): products of two parts or more whose tiles'
+# waves stand for them
+JOINED = [("f32", 1600, 1600, 6144, 4), ("split3_bf16", 1024, 1024, 6144, 4), ("split2_f16", 512, 512, 6144, 4),
+          ("bf16", 1024, 1024, 16384, 4), ("fp8_e4m3", 1024, 1024, 16384, 4), ("fp8_e4m3_r1", 1024, 1024, 16384, 4),
+          ("split3_bf16", 1100, 900, 4096, 8), ("split2_f16", 1000, 1400, 4096, 8), ("f16", 1100, 900, 16384, 8)]
+
+
+def test_joined_cases_are_summed_by_the_waves_of_a_tile():
+    for c, r in zip(JOINED, launches([("gemm", m, n, k, B.DTYPES[dt], 1, 1) for dt, m, n, k, _ in JOINED])):
+        main = [x for x in r["launches"] if "wave_kernel" in x["kernel"]][0]
+        assert main["block"][0] == 64 * c[4] and "backshift" not in r["launches"][-1]["kernel"], (c, r)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", JOINED)
+def test_parts_are_added_in_fp64(case):
+    """The waves' sums are 2^30, 1, -2^30, 1, ..: FP32 additions lose the ones
+    that follow a 2^30."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    dt, m, n, k, waves = case
+    A, Bm = np.zeros((m, k)), np.zeros((k, n))
+    for w in range(waves):
+        at = w * k // waves
+        A[:, at], Bm[at, :] = ((2.0 ** 15, 2.0 ** 15), (1, 1), (-2.0 ** 15, 2.0 ** 15), (1, 1))[w % 4]
+    note("joined", case)
+    C = hs.hs_gemm(to_dev(A, dt)[0], to_dev(Bm, dt)[0], dtype=dt, p=1, K=1, out=poisoned((m, n), torch.float32))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(C), np.full((m, n), float(waves // 2)))
