@@ -25,7 +25,7 @@ class HsMatmul(torch.autograd.Function):
         A, B = ctx.saved_tensors
         dtype, p, K = ctx.cfg
         need_a, need_b = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
-        G = G.contiguous()
+        G = G.resolve_conj().resolve_neg().contiguous()
         dA, dB = binding.hs_gemm_backward(A, B, G, dtype=dtype, p=p, K=K,
                                           need_a=need_a, need_b=need_b)
         return dA, dB, None, None, None

@@ -186,7 +186,15 @@ def row_layout(shape, strides, name="tensor"):
     return max(strides[0] if rows > 1 else cols, cols, 1)
 
 
-def _mat(t, name, dt):
+def _values(t):
+    """The tensor with the conjugation or negation that PyTorch has left as a
+    mark on it carried out (the library reads the stored values)."""
+    return t.resolve_conj().resolve_neg()
+
+
+def _operand(t, name, dt):
+    """A matrix operand's values (kept by the caller until the call is made),
+    their address and leading dimension."""
     torch = _torch()
     if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
         raise TypeError("%s must be a GPU tensor" % name)
@@ -194,7 +202,14 @@ def _mat(t, name, dt):
         raise ValueError("%s must be 2-D" % name)
     if t.dtype != getattr(torch, IN_TYPES[dt]):
         raise TypeError("%s must be %s for this dtype, got %s" % (name, IN_TYPES[dt], t.dtype))
-    return t.data_ptr(), row_layout(tuple(t.shape), t.stride(), name)
+    row_layout(tuple(t.shape), t.stride(), name)
+    t = _values(t)
+    return t, t.data_ptr(), row_layout(tuple(t.shape), t.stride(), name)
+
+
+def _check_out(out, name):
+    if out.is_conj() or out.is_neg():
+        raise ValueError("%s must not be a lazy conjugate or negative view" % name)
 
 
 def _stream(stream):
@@ -229,6 +244,7 @@ def _new_out(shape, dt, device, out, name):
     if tuple(out.shape) != tuple(shape) or out.dtype != getattr(torch, _out_type(dt)):
         raise ValueError("%s must be %s %s" % (name, shape, _out_type(dt)))
     row_layout(tuple(out.shape), out.stride(), name)
+    _check_out(out, name)
     return out
 
 
@@ -239,13 +255,13 @@ def hs_gemm(A, B, dtype="f32", p=1, K=0, out=None, stream=None):
         r = (_native_mod or _native()).product(0, A, B, out, dt, p, K)
         if r is not None:
             return _result(r, "hs_gemm")
-    a, lda = _mat(A, "A", dt)
-    b, ldb = _mat(B, "B", dt)
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("inner dimensions differ: %d vs %d" % (k, k2))
     with _on(stream):
+        A, a, lda = _operand(A, "A", dt)
+        B, b, ldb = _operand(B, "B", dt)
+        m, k = A.shape
+        k2, n = B.shape
+        if k != k2:
+            raise ValueError("inner dimensions differ: %d vs %d" % (k, k2))
         C = _new_out((m, n), dt, A.device, out, "out")
         ws, nb = _workspace(hs_workspace_size(HS_OP_GEMM, m, n, k, dt, p, K), A.device)
         st = lib().hs_gemm(m, n, k, dt, hs_schedule(p, K), a, lda, b, ldb, C.data_ptr(),
@@ -263,8 +279,11 @@ def hs_gemm_noalloc(A, B, out, dtype="f32", p=1, K=0, stream=None):
         r = (_native_mod or _native()).product(2, A, B, out, dt, p, K)
         if r is not None:
             return _result(r, "hs_gemm_noalloc")
-    a, lda = _mat(A, "A", dt)
-    b, ldb = _mat(B, "B", dt)
+    for t in (A, B):
+        if isinstance(t, _torch().Tensor) and (t.is_conj() or t.is_neg()):
+            raise ValueError("a lazy conjugate or negative view needs a copy; pass A and B resolved")
+    A, a, lda = _operand(A, "A", dt)
+    B, b, ldb = _operand(B, "B", dt)
     m, k = A.shape
     k2, n = B.shape
     if k != k2:
@@ -283,13 +302,13 @@ def hs_gemm_tn(A, B, dtype="f32", p=1, K=0, out=None, stream=None):
         r = (_native_mod or _native()).product(1, A, B, out, dt, p, K)
         if r is not None:
             return _result(r, "hs_gemm_tn")
-    a, lda = _mat(A, "A", dt)
-    b, ldb = _mat(B, "B", dt)
-    k, m = A.shape
-    k2, n = B.shape
-    if k != k2:
-        raise ValueError("contraction dimensions differ: %d vs %d" % (k, k2))
     with _on(stream):
+        A, a, lda = _operand(A, "A", dt)
+        B, b, ldb = _operand(B, "B", dt)
+        k, m = A.shape
+        k2, n = B.shape
+        if k != k2:
+            raise ValueError("contraction dimensions differ: %d vs %d" % (k, k2))
         C = _new_out((m, n), dt, A.device, out, "out")
         ws, nb = _workspace(hs_workspace_size(HS_OP_GEMM_TN, m, n, k, dt, p, K), A.device)
         st = lib().hs_gemm_tn(m, n, k, dt, hs_schedule(p, K), a, lda, b, ldb, C.data_ptr(),
@@ -307,15 +326,16 @@ def hs_gemv(A, x, dtype="f32", p=1, K=0, out=None, stream=None):
         if r is not None:
             return _result(r, "hs_gemv")
     torch = _torch()
-    a, lda = _mat(A, "A", dt)
-    m, n = A.shape
-    if x.dim() != 1 or x.shape[0] != n or x.dtype != A.dtype or x.device != A.device:
-        raise ValueError("x must be a length-%d vector of A's dtype on A's device" % n)
     with _on(stream):
-        x = x.contiguous()
+        A, a, lda = _operand(A, "A", dt)
+        m, n = A.shape
+        if x.dim() != 1 or x.shape[0] != n or x.dtype != A.dtype or x.device != A.device:
+            raise ValueError("x must be a length-%d vector of A's dtype on A's device" % n)
+        x = _values(x).contiguous()
         y = torch.empty(m, dtype=A.dtype, device=A.device) if out is None else out
         if y.shape != (m,) or y.dtype != A.dtype or (m and y.stride(0) != 1):
             raise ValueError("out must be a contiguous length-%d vector" % m)
+        _check_out(y, "out")
         st = lib().hs_gemv(m, n, dt, hs_schedule(p, K), a, lda, x.data_ptr(), y.data_ptr(),
                            None, 0, _stream(stream))
     _check(st, "hs_gemv")
@@ -330,15 +350,15 @@ def hs_gemm_backward(A, B, G, dtype="f32", p=1, K=0, need_a=True, need_b=True, s
         if r is not None:
             return _result(r, "hs_gemm_backward")
     torch = _torch()
-    a, lda = _mat(A, "A", dt)
-    b, ldb = _mat(B, "B", dt)
-    g, ldg = _mat(G, "G", dt)
-    m, k = A.shape
-    k2, n = B.shape
-    if k != k2 or tuple(G.shape) != (m, n):
-        raise ValueError("shape mismatch: A %s, B %s, G %s" % (tuple(A.shape), tuple(B.shape), tuple(G.shape)))
     ot = getattr(torch, _out_type(dt))
     with _on(stream):
+        A, a, lda = _operand(A, "A", dt)
+        B, b, ldb = _operand(B, "B", dt)
+        G, g, ldg = _operand(G, "G", dt)
+        m, k = A.shape
+        k2, n = B.shape
+        if k != k2 or tuple(G.shape) != (m, n):
+            raise ValueError("shape mismatch: A %s, B %s, G %s" % (tuple(A.shape), tuple(B.shape), tuple(G.shape)))
         dA = torch.empty((m, k), dtype=ot, device=A.device) if need_a else None
         dB = torch.empty((k, n), dtype=ot, device=A.device) if need_b else None
         ws, nb = _workspace(hs_workspace_size(HS_OP_BACKWARD, m, n, k, dt, p, K), A.device)
@@ -372,10 +392,11 @@ def hs_nbody(bodies, eps2=0.0, dtype=None, p=1, K=0, out=None, stream=None):
         raise TypeError("bodies must be float32 (f32) or float64 (f64)")
     n = bodies.shape[0]
     with _on(stream):
-        bodies = bodies.contiguous()
+        bodies = _values(bodies).contiguous()
         o = torch.empty((n, 4), dtype=bodies.dtype, device=bodies.device) if out is None else out
         if tuple(o.shape) != (n, 4) or o.dtype != bodies.dtype or (n and not o.is_contiguous()):
             raise ValueError("out must be a contiguous n x 4 tensor of the bodies' dtype")
+        _check_out(o, "out")
         ws, nb = _workspace(hs_workspace_size(HS_OP_NBODY, n, 0, 0, dt, p, K), bodies.device)
         st = lib().hs_nbody(n, dt, hs_schedule(p, K), bodies.data_ptr(), float(eps2), o.data_ptr(),
                             ws.data_ptr() if ws is not None else None, nb, _stream(stream))

@@ -7,8 +7,9 @@
 // Every function takes the arguments already resolved by binding.py and
 // returns the result, the hs_status as an int where the library refused the
 // call, or None where the arguments are not the ordinary ones (a tensor
-// subclass, another dtype, shape, stride or device, an empty matrix); binding.py
-// then takes its general path, which raises the error that belongs to them.
+// subclass, a lazy view, another dtype, shape, stride or device, an empty matrix);
+// binding.py then takes its general path, which answers the call or raises the
+// error that belongs to it.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -47,12 +48,13 @@ at::ScalarType out_type(int dt) {
     return complex_form(dt) ? at::kComplexFloat : dt == HS_F64 ? at::kDouble : at::kFloat;
 }
 
-// A plain GPU tensor of this dtype and dimension, or nullptr.
+// A plain GPU tensor of this dtype and dimension that stores its values (no lazy
+// conjugate or negative view), or nullptr.
 const at::Tensor *plain(PyObject *o, at::ScalarType st, int64_t dim) {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
     if (!t.defined() || !t.is_cuda() || t.layout() != at::kStrided || t.dim() != dim || t.scalar_type() != st ||
-        !t.has_storage() || t.unsafeGetTensorImpl()->has_symbolic_sizes_strides())
+        t.is_conj() || t.is_neg() || !t.has_storage() || t.unsafeGetTensorImpl()->has_symbolic_sizes_strides())
         return nullptr;
     return &t;
 }
