@@ -207,7 +207,9 @@ def _operand(t, name, dt):
     return t, t.data_ptr(), row_layout(tuple(t.shape), t.stride(), name)
 
 
-def _check_out(out, name):
+def _check_out(out, name, device):
+    if out.device != device:
+        raise ValueError("%s must be on the operands' device %s, not on %s" % (name, device, out.device))
     if out.is_conj() or out.is_neg():
         raise ValueError("%s must not be a lazy conjugate or negative view" % name)
 
@@ -244,7 +246,7 @@ def _new_out(shape, dt, device, out, name):
     if tuple(out.shape) != tuple(shape) or out.dtype != getattr(torch, _out_type(dt)):
         raise ValueError("%s must be %s %s" % (name, shape, _out_type(dt)))
     row_layout(tuple(out.shape), out.stride(), name)
-    _check_out(out, name)
+    _check_out(out, name, device)
     return out
 
 
@@ -335,7 +337,7 @@ def hs_gemv(A, x, dtype="f32", p=1, K=0, out=None, stream=None):
         y = torch.empty(m, dtype=A.dtype, device=A.device) if out is None else out
         if y.shape != (m,) or y.dtype != A.dtype or (m and y.stride(0) != 1):
             raise ValueError("out must be a contiguous length-%d vector" % m)
-        _check_out(y, "out")
+        _check_out(y, "out", A.device)
         st = lib().hs_gemv(m, n, dt, hs_schedule(p, K), a, lda, x.data_ptr(), y.data_ptr(),
                            None, 0, _stream(stream))
     _check(st, "hs_gemv")
@@ -396,7 +398,7 @@ def hs_nbody(bodies, eps2=0.0, dtype=None, p=1, K=0, out=None, stream=None):
         o = torch.empty((n, 4), dtype=bodies.dtype, device=bodies.device) if out is None else out
         if tuple(o.shape) != (n, 4) or o.dtype != bodies.dtype or (n and not o.is_contiguous()):
             raise ValueError("out must be a contiguous n x 4 tensor of the bodies' dtype")
-        _check_out(o, "out")
+        _check_out(o, "out", bodies.device)
         ws, nb = _workspace(hs_workspace_size(HS_OP_NBODY, n, 0, 0, dt, p, K), bodies.device)
         st = lib().hs_nbody(n, dt, hs_schedule(p, K), bodies.data_ptr(), float(eps2), o.data_ptr(),
                             ws.data_ptr() if ws is not None else None, nb, _stream(stream))

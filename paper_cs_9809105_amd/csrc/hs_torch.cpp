@@ -125,7 +125,7 @@ PyObject *product(PyObject *, PyObject *const *a, Py_ssize_t n) {
         C = empty({m, nc}, out_type(dt), *A);
     } else {
         const at::Tensor *o = plain(a[3], out_type(dt), 2);
-        if (!o || o->size(0) != m || o->size(1) != nc || !leading(*o)) return none();
+        if (!o || o->device() != A->device() || o->size(0) != m || o->size(1) != nc || !leading(*o)) return none();
         C = *o;
     }
     const int64_t ldc = leading(C);
@@ -205,7 +205,7 @@ PyObject *gemv(PyObject *, PyObject *const *a, Py_ssize_t n) {
         y = empty({m}, in_type(dt), *A);
     } else {
         const at::Tensor *o = plain(a[2], in_type(dt), 1);
-        if (!o || o->size(0) != m || o->stride(0) != 1) return none();
+        if (!o || o->device() != A->device() || o->size(0) != m || o->stride(0) != 1) return none();
         y = *o;
     }
     void *st = current_stream();
@@ -234,7 +234,7 @@ PyObject *nbody(PyObject *, PyObject *const *a, Py_ssize_t n) {
         o = empty({nb, 4}, in_type(dt), *b);
     } else {
         const at::Tensor *g = plain(a[2], in_type(dt), 2);
-        if (!g || g->size(0) != nb || g->size(1) != 4 || !g->is_contiguous()) return none();
+        if (!g || g->device() != b->device() || g->size(0) != nb || g->size(1) != 4 || !g->is_contiguous()) return none();
         o = *g;
     }
     const Workspace ws(f_workspace_size(HS_OP_NBODY, nb, 0, 0, dt, s), *b);
