@@ -269,7 +269,7 @@ void plan_wave(Plan *P) {
     wave_shape(P->f, count, wide, chunks, P->nsplit, &W.tr, &W.tc, &W.kg);
     if (tiles * 100 >= ceil_div(tiles, kCUs) * kCUs * wave_percent(P->f, W.tr)) return;
     const int64_t wt = count(W.tr, W.tc);
-    if (wt > (int64_t)1 << 26) return;                    // 32-bit grid in threads
+    if (wt >= (int64_t)1 << 26) return;                   // 32-bit grid in threads
     const int R = wave_tile(fam, W.tr), C = wave_tile(fam, W.tc);
     OperandGeom &a = W.ga, &b = W.gb;
     a.striped = OPG_CLASSES;

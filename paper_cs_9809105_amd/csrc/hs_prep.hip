@@ -662,6 +662,29 @@ __global__ __launch_bounds__(256) void pack_kernel(PackPair p) {
 // ---------------------------------------------------------------------------
 static inline unsigned nblocks(int64_t work) { return (unsigned)((work + 255) / 256); }
 
+// Launches one grid of na + nb workgroups of `threads` for both operands, or,
+// where those are 2^32 threads or more (the runtime's limit), a grid for each:
+// launch(pair, workgroups) with pair.nb0 workgroups for the first operand.
+template <class Pair, class Launch>
+static hipError_t launch_pair(Pair p, unsigned na, unsigned nb, unsigned threads, Launch launch) {
+    p.nb0 = na;
+    if (na + nb == 0) return hipSuccess;
+    if (((uint64_t)na + nb) * threads >> 32 == 0) {
+        launch(p, na + nb);
+        return hipGetLastError();
+    }
+    if (na) {
+        launch(p, na);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (nb) {
+        p.nb0 = 0;
+        launch(p, nb);
+    }
+    return hipGetLastError();
+}
+
 // Units per thread.  A unit of the 16-bit and FP32 forms is one 16-byte load and
 // one such store; with one a thread too few bytes are in flight.  Four where
 // that leaves every CU 16 workgroups, and not for the element-wise MN reads:
@@ -677,14 +700,12 @@ static int units_per_thread(int kind, const PackArgs &a, const PackArgs &b) {
 template <int KIND>
 static hipError_t launch_pack_k(const PackArgs &a, const PackArgs &b, hipStream_t st) {
     const int ma = a.mode, mb = b.mode, U = units_per_thread(KIND, a, b);
-    const unsigned na = nblocks((a.total_units + U - 1) / U), nb = na + nblocks((b.total_units + U - 1) / U);
-    const PackPair p{{a, b}, na};
-    if (nb == 0) return hipSuccess;
-#define HS_PACK_U(A_, B_, U_)                                                                    \
-    if (ma == A_ && mb == B_ && U == U_) {                                                       \
-        hipLaunchKernelGGL((pack_kernel<KIND, A_, B_, U_>), dim3(nb), dim3(256), 0, st, p);      \
-        return hipGetLastError();                                                                \
-    }
+    const unsigned na = nblocks((a.total_units + U - 1) / U), nb = nblocks((b.total_units + U - 1) / U);
+#define HS_PACK_U(A_, B_, U_)                                                                                  \
+    if (ma == A_ && mb == B_ && U == U_)                                                                       \
+        return launch_pair(PackPair{{a, b}, 0}, na, nb, 256, [&](const PackPair &p, unsigned n) {               \
+            hipLaunchKernelGGL((pack_kernel<KIND, A_, B_, U_>), dim3(n), dim3(256), 0, st, p);                  \
+        });
 #define HS_PACK(A_, B_)                                                                          \
     HS_PACK_U(A_, B_, 1)                                                                         \
     if constexpr ((KIND == PK_B16 || KIND == PK_F32) && A_ != PACK_MN && B_ != PACK_MN) {        \
@@ -723,6 +744,7 @@ hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t l
 // rows on fewer than 128 workgroups of 32 columns) goes through the slab
 // kernel: there a workgroup's walk over all rows would be the longer wait.
 hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream_t st) {
+    if (!a.kmajor && b.kmajor) return hipErrorInvalidValue;    // no product reads its operands so
     AmaxPair p{};
     unsigned nb[2] = {0, 0};
     const RowAmaxArgs *in[2] = {&a, &b};
@@ -749,14 +771,11 @@ hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    p.nb0 = nb[0];
-    if (nb[0] + nb[1] == 0) return hipSuccess;
-    const dim3 grid(nb[0] + nb[1]);
-    if (a.kmajor && b.kmajor) hipLaunchKernelGGL((row_amax_kernel<1, 1>), grid, dim3(512), 0, st, p);
-    else if (a.kmajor) hipLaunchKernelGGL((row_amax_kernel<1, 0>), grid, dim3(512), 0, st, p);
-    else if (!b.kmajor) hipLaunchKernelGGL((row_amax_kernel<0, 0>), grid, dim3(512), 0, st, p);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    return launch_pair(p, nb[0], nb[1], 512, [&](const AmaxPair &q, unsigned n) {
+        if (!a.kmajor) hipLaunchKernelGGL((row_amax_kernel<0, 0>), dim3(n), dim3(512), 0, st, q);
+        else if (b.kmajor) hipLaunchKernelGGL((row_amax_kernel<1, 1>), dim3(n), dim3(512), 0, st, q);
+        else hipLaunchKernelGGL((row_amax_kernel<1, 0>), dim3(n), dim3(512), 0, st, q);
+    });
 }
 
 hipError_t launch_fp8_exps(const Fp8ExpArgs &a, int64_t ta, const Fp8ExpArgs &b, int64_t tb, hipStream_t st) {
