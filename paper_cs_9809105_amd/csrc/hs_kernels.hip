@@ -597,7 +597,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(OT *Cout, int64_t M, int
 // and (p = 64, K = 8) 45 us; the same walk as one pipelined sequence 42.5, 10.7
 // and 4.4, but 5000 x 10000 44.5 against 35.5 here, for its index arithmetic.
 // CX: complex64 (VE complex elements per load).  NT: A is read past the caches
-// (it is larger than they are, see launch_gemv_t).
+// (it is larger than they are, by a fifth: launch_gemv_t).
 template <typename T, int CX, int NT>
 __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs a) {
     constexpr int VE = 16 / (int)(sizeof(T) * (1 + CX)), U = 4, NT4 = VE * (1 + CX);
@@ -831,12 +831,14 @@ hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t l
 template <typename T, int CX>
 static hipError_t launch_gemv_t(const GemvArgs &a, hipStream_t st) {
     const dim3 grid((unsigned)((a.m * a.waves + 3) / 4));
-    // A of 256 MiB or more does not stay whole in the memory-side cache.  Read
-    // past the caches, matrices not read just before take less time (FP32 8192 x
-    // 8192, four in turn: 42.8 us a call against 46.3) and the same one of just
-    // that size over and over takes more, as most of it does stay (41.1 against
-    // 38.2).  8192 x 2048, which stays whole: 13.8 against 12.6.
-    if (a.m * a.n * (int64_t)(sizeof(T) * (1 + CX)) >= (int64_t)256 << 20)
+    // Reads past the caches: matrices not read just before take less time (FP32,
+    // two in turn, 8192 x 8192 42.9 us a call against 46.5, 8192 x 9728 50.9 against
+    // 56.0), but the same one over and over, as in an iterative solver, takes more
+    // while most of it stays in the 256 MiB memory-side cache: FP32 256 MiB 41.5
+    // against 38.8, 280 MiB 46.5 against 44.0, 288 MiB 46.6 against 45.8 (FP64 48.8,
+    // 47.5; complex 49.8, 48.2).  From 304 MiB on that is the faster one too: FP32
+    // 49.5 against 51.9, FP64 50.9 against 52.9, FP32 12288 x 12288 94 against 101.
+    if (a.m * a.n * (int64_t)(sizeof(T) * (1 + CX)) >= (int64_t)304 << 20)
         HS_LAUNCH_TIMED((gemv_kernel<T, CX, 1>), grid, dim3(256), 0, st, a);
     else
         HS_LAUNCH_TIMED((gemv_kernel<T, CX, 0>), grid, dim3(256), 0, st, a);
