@@ -562,6 +562,10 @@ hs_status nbody_plan(int64_t n, int dtype, hs_schedule s, double eps2, NbodyArgs
     a->K = r.K;
     a->Kt = r.p / r.K;
     a->S = (int)std::max<int64_t>(1, ceil_div(n, r.p));
+    // The size limit of a call: 2^31 - 1 slices of 256 positions by replicas, a pair
+    // of replicas counted once (n = 2^28, p = K = 4096: half a day of pairs).
+    if ((int64_t)r.p * ceil_div(a->S, 256) * (r.K % 2 ? r.K : r.K / 2) > std::numeric_limits<int32_t>::max())
+        return HS_ERR_NOT_SUPPORTED;
     a->sub = (int)ceil_div(a->S, 64);
     const int64_t gx = (int64_t)a->sub * r.K;         // times 64: at most n + 64 K, below 2^32 threads
     a->ss = gx * r.p < 1024 ? 16 : 8;

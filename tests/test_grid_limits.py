@@ -21,3 +21,13 @@ def test_accepted_sizes_launch():
         assert len(mine) == count, (call, mine)
         for x in r["launches"]:
             assert x["grid"][0] * x["block"][0] < 1 << 32, (call, x)
+
+
+def test_nbody_size_limit():
+    """p ceil(S / 256) K below 2^31, pairs of replicas counted once (S = ceil(n / p))."""
+    for n, p, K, ok in [((1 << 28) - 4096 * 256, 4096, 4096, True), (1 << 28, 4096, 4096, False),
+                        ((1 << 29) - (1 << 20), 4096, 2048, True), (1 << 29, 4096, 2048, False),
+                        ((1 << 31) - 1, 4096, 512, False), ((1 << 31) - 1, 4096, 256, True),
+                        ((1 << 31) - 1, 1024, 1024, False), ((1 << 31) - 1, 3, 3, True)]:
+        for dt in ("f32", "f64"):
+            assert (B.hs_workspace_size(B.HS_OP_NBODY, n, 0, 0, dt, p, K) != B.SIZE_MAX) == ok, (n, p, K, dt)
