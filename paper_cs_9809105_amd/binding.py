@@ -89,7 +89,11 @@ def _native():
     global _native_mod
     if _native_mod is None:
         L = lib()
-        from . import _hs_torch
+        try:
+            from . import _hs_torch
+        except ImportError as e:
+            raise RuntimeError("_hs_torch.so is not built or does not load (%s); run paper_cs_9809105_amd.build"
+                               % e) from e
         _hs_torch.connect(*[ctypes.cast(f, ctypes.c_void_p).value for f in
                             (L.hs_workspace_size, L.hs_gemm, L.hs_gemm_tn, L.hs_gemm_noalloc, L.hs_gemv,
                              L.hs_gemm_backward, L.hs_nbody)])

@@ -56,12 +56,13 @@ def build_native():
 
     import torch
     root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))          # the headers beside the compiler
     tmp = NATIVE + ".tmp"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "hs_torch.cpp"), "-o", tmp, "-L", os.path.join(root, "lib"),
            "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip"]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
