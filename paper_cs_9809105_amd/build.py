@@ -56,7 +56,7 @@ def build_native():
 
     import torch
     root = os.path.dirname(torch.__file__)
-    rocm = os.path.dirname(os.path.dirname(HIPCC))          # the headers beside the compiler
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     tmp = NATIVE + ".tmp"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
