@@ -50,7 +50,6 @@ struct RowAmaxArgs {
     int64_t R, Kd;
     uint32_t *amax;           // [R] float bits of max |x| over the row
     int embed;
-    int vec;                  // 16-byte loads are legal (set by launch_row_amax)
 };
 
 // FP8 scale tiles: 128 x 128 blocks of the logical operand (rows x

@@ -268,19 +268,27 @@ DEVI void pack_emit(const PackArgs &a, const GroupAt &at, uint32_t kb, uint32_t 
 // ---------------------------------------------------------------------------
 // One launch scans both operands (workgroups below nb0 take the first).  It is
 // bound by reading each operand once.  NaNs are skipped (fmaxf); they reach the
-// product through the values themselves.
-//   K-major source: one wave per row, 16-byte loads where the rows allow it.
+// product through the values themselves.  Every source is read 16 bytes at a
+// time at whatever alignment its elements have (one element a load where rows
+// are not 16-byte aligned, whole calls of two-piece FP16: tn 4097 x 2049 x 8191 741
+// us, 575 here; 64 x 513 x 4097 105 and 42).
+//   K-major source: one wave per row.
 //   MN-major source (element (kk, c) of the float view at src[kk ld + c]): a
 //   workgroup owns 32 float columns (one 128-byte line) over all contraction
-//   rows, 64 rows per pass (16 unaligned), 8 passes in flight, so the result
-//   needs neither atomics nor a cleared buffer (columns of 4096 x 2048 and of
-//   4096 x 8192 together 49 us; two fills and two slab scans with atomics 93).
+//   rows, 64 rows per pass, 8 passes in flight, so the result needs neither
+//   atomics nor a cleared buffer (columns of 4096 x 2048 and of 4096 x 8192
+//   together 49 us; two fills and two slab scans with atomics 93).
 struct AmaxPair {
     RowAmaxArgs x[2];
     uint32_t nb0;
 };
 const int AMAX_COLS = 32;
 
+DEVI float4 load4(const float *q) {
+    float4 v;
+    __builtin_memcpy(&v, q, 16);
+    return v;
+}
 DEVI int64_t amax_ncol(const RowAmaxArgs &a) { return (a.embed == EMB_TRANS || a.embed == EMB_CONJ) ? 2 * a.R : a.R; }
 DEVI int64_t amax_nk(const RowAmaxArgs &a) { return a.embed == EMB_NONE ? a.Kd : a.Kd / 2; }
 
@@ -293,31 +301,27 @@ DEVI void row_amax_one(const RowAmaxArgs &a, uint32_t blk, float (&red)[64][AMAX
         if (row >= a.R) return;
         const float *q = a.src + (a.embed == EMB_BLOCKS_H ? row >> 1 : row) * a.ld;
         float m = 0.f;
-        int64_t k = 0;
-        if (a.vec) {
-            const int64_t k4 = a.Kd / 4 * 4;
+        const int64_t k4 = a.Kd / 4 * 4;
 #pragma unroll 4
-            for (k = lane * 4; k < k4; k += 256) {
-                const float4 v = *(const float4 *)(q + k);
-                m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-            }
-            k = k4;
+        for (int64_t k = lane * 4; k < k4; k += 256) {
+            const float4 v = load4(q + k);
+            m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
         }
-        for (int64_t kk = k + lane; kk < a.Kd; kk += 64) m = fmaxf(m, fabsf(q[kk]));
+        if (k4 + lane < a.Kd) m = fmaxf(m, fabsf(q[k4 + lane]));
         m = wave_max(m);
         if (lane == 0) a.amax[row] = __float_as_uint(m);
         return;
     }
     const int64_t ncol = amax_ncol(a), nk = amax_nk(a);
     const int64_t c0 = (int64_t)blk * AMAX_COLS;
-    const int lanes = a.vec ? 8 : AMAX_COLS, cw = AMAX_COLS / lanes;   // threads per row, columns each
-    const int64_t c = c0 + (tid % lanes) * cw;
-    const int r0 = tid / lanes, rows = 512 / lanes;
+    constexpr int LANES = AMAX_COLS / 4, ROWS = 512 / LANES;   // threads per row, 4 columns each
+    const int64_t c = c0 + (tid % LANES) * 4;
+    const int r0 = tid / LANES;
     float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
-    if (a.vec && c + 3 < ncol) {
+    if (c + 3 < ncol) {
 #pragma unroll 8
-        for (int64_t kk = r0; kk < nk; kk += rows) {
-            const float4 v = *(const float4 *)(a.src + kk * a.ld + c);
+        for (int64_t kk = r0; kk < nk; kk += ROWS) {
+            const float4 v = load4(a.src + kk * a.ld + c);
             m0 = fmaxf(m0, fabsf(v.x));
             m1 = fmaxf(m1, fabsf(v.y));
             m2 = fmaxf(m2, fabsf(v.z));
@@ -325,22 +329,19 @@ DEVI void row_amax_one(const RowAmaxArgs &a, uint32_t blk, float (&red)[64][AMAX
         }
     } else {
 #pragma unroll 8
-        for (int64_t kk = r0; kk < nk; kk += rows) {
+        for (int64_t kk = r0; kk < nk; kk += ROWS) {
             const float *q = a.src + kk * a.ld + c;
             if (c < ncol) m0 = fmaxf(m0, fabsf(q[0]));
-            if (cw == 4) {
-                if (c + 1 < ncol) m1 = fmaxf(m1, fabsf(q[1]));
-                if (c + 2 < ncol) m2 = fmaxf(m2, fabsf(q[2]));
-            }
+            if (c + 1 < ncol) m1 = fmaxf(m1, fabsf(q[1]));
+            if (c + 2 < ncol) m2 = fmaxf(m2, fabsf(q[2]));
         }
     }
-    float *d = &red[r0][(tid % lanes) * cw];
-    d[0] = m0;
-    if (cw == 4) { d[1] = m1; d[2] = m2; d[3] = m3; }
+    float *d = &red[r0][(tid % LANES) * 4];
+    d[0] = m0; d[1] = m1; d[2] = m2; d[3] = m3;
     __syncthreads();
     if (tid >= AMAX_COLS || c0 + tid >= ncol) return;
     float m = 0.f;
-    for (int r = 0; r < rows; ++r) m = fmaxf(m, red[r][tid]);
+    for (int r = 0; r < ROWS; ++r) m = fmaxf(m, red[r][tid]);
     // complex sources: a pair of float columns (both in this workgroup, and in
     // neighbouring lanes) shares its rows of the embedding
     if (a.embed != EMB_NONE) {
@@ -360,23 +361,25 @@ __global__ __launch_bounds__(512) void row_amax_kernel(AmaxPair p) {
     else row_amax_one<KB>(p.x[1], blockIdx.x - p.nb0, red);
 }
 
-// The same for a tall MN-major source with few columns (too few workgroups
-// above): thread columns (4 per thread when vec) over a slab of 64 contraction
-// rows, then one atomic max per column into its row (two for EMB_BLOCKS) of
-// the zero-filled amax.  Workgroup b takes column block b % ncb of slab b / ncb.
-__global__ __launch_bounds__(256) void row_amax_tall_kernel(RowAmaxArgs a) {
-    const int cw = a.vec ? 4 : 1;
+// The same by slabs of 256 contraction rows (where launch_row_amax says): 4
+// columns per thread, a workgroup's four waves side by side (`across`) or one
+// below the other with 64 rows each, then one atomic max per
+// column into its row (two for EMB_BLOCKS) of the zero-filled amax.  Workgroup b
+// takes column block b % ncb of slab b / ncb.
+__global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a, int across) {
     const int64_t ncol = amax_ncol(a), nk = amax_nk(a);
-    const int64_t ncb = (ncol + 64 * cw - 1) / (64 * cw);
-    const int64_t c = ((int64_t)(blockIdx.x % ncb) * 64 + (threadIdx.x & 63)) * cw;
+    const int width = across ? 1024 : 256, t = across ? threadIdx.x : threadIdx.x & 63;
+    const int64_t ncb = (ncol + width - 1) / width;
+    const int64_t c = (int64_t)(blockIdx.x % ncb) * width + t * 4;
     if (c >= ncol) return;
-    const int64_t k0 = (int64_t)(blockIdx.x / ncb) * 256 + (threadIdx.x >> 6) * 64;
-    const int64_t k1 = k0 + 64 < nk ? k0 + 64 : nk;
+    const int rows = across ? 256 : 64;
+    const int64_t k0 = (int64_t)(blockIdx.x / ncb) * 256 + (across ? 0 : (threadIdx.x >> 6) * 64);
+    const int64_t k1 = k0 + rows < nk ? k0 + rows : nk;
     float m[4] = {0.f, 0.f, 0.f, 0.f};
-    if (a.vec && c + 3 < ncol) {
+    if (c + 3 < ncol) {
 #pragma unroll 8
         for (int64_t kk = k0; kk < k1; ++kk) {
-            const float4 v = *(const float4 *)(a.src + kk * a.ld + c);
+            const float4 v = load4(a.src + kk * a.ld + c);
             m[0] = fmaxf(m[0], fabsf(v.x));
             m[1] = fmaxf(m[1], fabsf(v.y));
             m[2] = fmaxf(m[2], fabsf(v.z));
@@ -385,12 +388,12 @@ __global__ __launch_bounds__(256) void row_amax_tall_kernel(RowAmaxArgs a) {
     } else {
         for (int64_t kk = k0; kk < k1; ++kk)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (j < cw && c + j < ncol) m[j] = fmaxf(m[j], fabsf(a.src[kk * a.ld + c + j]));
+            for (int j = 0; j < 3; ++j)
+                if (c + j < ncol) m[j] = fmaxf(m[j], fabsf(a.src[kk * a.ld + c + j]));
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        if (j >= cw || c + j >= ncol) continue;
+        if (c + j >= ncol) continue;
         const uint32_t bits = __float_as_uint(m[j]);
         if (a.embed == EMB_BLOCKS) {
             atomicMax(a.amax + ((c + j) & ~(int64_t)1), bits);
@@ -740,9 +743,19 @@ hipError_t launch_pack(int kind, const PackArgs &a, const PackArgs &b, hipStream
 
 hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t ldc, hipStream_t st);
 
-// Row amaxes of both operands.  A tall MN-major source (over 8192 contraction
-// rows on fewer than 128 workgroups of 32 columns) goes through the slab
-// kernel: there a workgroup's walk over all rows would be the longer wait.
+// Row amaxes of both operands.  An MN-major source goes through the slab kernel
+// where a workgroup's walk over all rows would be the longer wait (over 8192 rows
+// on fewer than 128 workgroups of 32 columns), and where it is larger than the
+// memory-side cache: there long stretches of a row are read faster, and of rows
+// that do not start on 128-byte lines each line between two workgroups' columns
+// would be read twice.  Whole calls with m = 64, n x k (slabs / columns), us:
+// 33 x 65537 159 / 401, 512 x 131072 527 / 733, 2048 x 32768 283 / 331, but 32 x 8192
+// 32 / 27, 2048 x 8192 72 / 67, 32 x 16384 46 / 42; 10240 x 10240 393 / 418, 16384 x 16384
+// 931 / 945, 16384 x 4096 270 / 273, but 16384 x 2048 151 / 144; 8191 x 16385 641 / 852,
+// 16383 x 4097 338 / 364, but 16383 x 3001 274 / 272.  Waves side by side for whole
+// lines (16384 x 16384 931, one below the other 945), else one below the other
+// (16383 x 8193 612, side by side 696).  Of complex sources on whole lines the slabs'
+// atomics, two per column, cost what they save: 4096 x 8192 558 / 548.
 hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream_t st) {
     if (!a.kmajor && b.kmajor) return hipErrorInvalidValue;    // no product reads its operands so
     AmaxPair p{};
@@ -752,7 +765,6 @@ hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream
         RowAmaxArgs &x = p.x[i];
         x = *in[i];
         if (x.R == 0) continue;
-        x.vec = x.ld % 4 == 0 && ((uintptr_t)x.src % 16) == 0;
         if (x.kmajor) {
             nb[i] = (unsigned)((x.R + 7) / 8);
             continue;
@@ -760,14 +772,18 @@ hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream
         const int64_t ncol = (x.embed == EMB_TRANS || x.embed == EMB_CONJ) ? 2 * x.R : x.R;
         const int64_t nk = x.embed == EMB_NONE ? x.Kd : x.Kd / 2;
         const int64_t wide = (ncol + AMAX_COLS - 1) / AMAX_COLS;
-        if (nk <= 8192 || wide >= 128) {
+        const bool lines = x.ld % 32 == 0 && (uintptr_t)x.src % 128 == 0;
+        const bool slabs = (nk > 8192 && wide < 128) ||
+                           (ncol * nk * 4 >= (int64_t)256 << 20 && (x.embed == EMB_NONE || !lines));
+        if (!slabs) {
             nb[i] = (unsigned)wide;
             continue;
         }
         hipError_t e = launch_fill_zero(0, x.amax, 1, x.R, x.R, st);   // zero bits = 0.0f
         if (e != hipSuccess) return e;
-        const int64_t ncb = (ncol + (x.vec ? 256 : 64) - 1) / (x.vec ? 256 : 64);
-        hipLaunchKernelGGL(row_amax_tall_kernel, dim3((unsigned)(ncb * ((nk + 255) / 256))), dim3(256), 0, st, x);
+        const int across = ncol >= 1024 && lines, width = across ? 1024 : 256;
+        const int64_t ncb = (ncol + width - 1) / width;
+        hipLaunchKernelGGL(row_amax_slab_kernel, dim3((unsigned)(ncb * ((nk + 255) / 256))), dim3(256), 0, st, x, across);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
