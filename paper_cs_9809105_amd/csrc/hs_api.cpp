@@ -187,7 +187,12 @@ int wave_percent(const FormInfo &f, int tr) {
 // idle), one wave from 8192 tiles on.  Of these 2 x 2 tiles two workgroups
 // fit a CU (LDS): taken from 900 tiles, and for FP32, where they gain little
 // (2048^3, 1024 tiles: 134 against 140) only if 512 at a time fill nine tenths
-// of the rounds (1800 x 2200 x 1000, 1050 tiles: 91 against 72).
+// of the rounds (1800 x 2200 x 1000, 1050 tiles: 91 against 72).  FP64 takes them
+// where they fill the rounds, or there are 64 with long sums, and little of them
+// is padding: whole calls (2 x 2 / 1 x 1, and the LDS-tiled kernel), 1008 x 448 x
+// 15616, 448 tiles, 316 / 550, 433; 64 x 8192 x 8192, 512, 406 / 538, 411; 512^3, 256,
+// 15.2 / 16.2; 100 x 1000 x 10000, 128, 88 / 93; but 405 x 658 x 1074, 273, 31.3 / 28.8;
+// 256^3, 64 short ones, 9.9 / 8.0; 33 x 5000 x 5000, a third of it padding, 163 / 159.
 //
 // The 16-bit and FP8 forms are bound by fragment reads, which larger tiles
 // save: 2 x 2 from 256 tiles (1024^3: split-BF16 19 against 22, FP8 8.9 against
@@ -223,7 +228,8 @@ void wave_shape(const FormInfo &f, Count n, bool wide, int64_t chunks, int parts
     const int64_t n22 = n(2, 2), n42 = n(4, 2);
     *tr = *tc = 1;
     if (slow) {
-        if (n22 >= 900 && (f.fam == FAM_F64 || fills(n22, 512, 90))) *tr = *tc = 2;
+        const bool wide64 = (n22 >= 256 ? fills(n22, 256, 75) : n22 >= 64 && chunks >= 512) && 16 * n22 <= 5 * n(1, 1);
+        if (f.fam == FAM_F64 ? n22 >= 900 || wide64 : n22 >= 900 && fills(n22, 512, 90)) *tr = *tc = 2;
         *kg = n(*tr, *tc) >= 8192 ? 1 : 4;
     } else if (split && chunks >= (f.form == 1 ? 64 : 128) && n42 > 256 && n42 <= 1024 &&
                fills(n42, n42 <= 512 ? 512 : 1024, 75) && parts <= (n42 <= 512 ? 2 : 1)) {
@@ -245,7 +251,7 @@ void wave_shape(const FormInfo &f, Count n, bool wide, int64_t chunks, int parts
         *kg = n(1, 1) >= 768 ? 2 : 4;
     }
     // long sums on few tiles: 300 x 320 x 6000 BF16 13 against 15
-    if (*tr * *tc <= 4 && n(*tr, *tc) <= 128 && chunks >= 256) *kg = 8;
+    if (*tr == 1 && n(1, 1) <= 128 && chunks >= 256) *kg = 8;
     while (*kg > 1 && chunks < 2 * *kg) *kg /= 2;
     while (*kg < parts) *kg *= 2;
 }

@@ -43,6 +43,7 @@ struct WvCfg {
     static const int SET = (TR + TC) * NP * LD * 4;                 // registers of one set
     static const int D = SET <= 8 ? 8 : SET <= 16 ? 4 : SET <= 24 ? 3 : 2;
     static const int MAX_KG = TR * TC <= 6 && SET * D + TR * TC * 16 <= 216 ? 8 : 4;
+    static const bool EIGHT = MAX_KG == 8 && TR * TC != 4;          // 2 x 2 tiles have at most four waves
     typedef typename Mfma<FAM>::Acc Acc;
     static const int NE = (int)(sizeof(Acc) / (FAM == FAM_F64 ? 8 : 4));
 };
@@ -293,7 +294,7 @@ done:
 #pragma unroll
         for (int e = 0; e < 4; ++e) store(tile / TC, tile % TC, 4 * h + e, v[e]);
     };
-    if constexpr (C::MAX_KG == 8 && TR * TC != 4)          // host: 2 x 2 tiles have at most four waves
+    if constexpr (C::EIGHT)
         if (a.kg == 8) {
             constexpr int QW = (NQ + 7) / 8;               // quads per wave
             D4 v[QW];
@@ -327,6 +328,7 @@ done:
 template <int FAM, int FORM, int TR, int TC>
 static hipError_t launch_wave_t(const WaveArgs &a, hipStream_t st) {
     typedef WvCfg<FAM, FORM, TR, TC> C;
+    if (a.kg > (C::EIGHT ? 8 : 4)) return hipErrorInvalidValue;     // the kernel has no place for more sums
     const int64_t nwg = (int64_t)a.K * a.GS * a.n_ntiles * a.nsplit;
     const unsigned lds = a.kg == 1 ? 0 : (unsigned)(a.kg < 4 ? a.kg : 4) * TR * TC * sizeof(typename C::Acc) * 64;   // <= 128 KiB
     // LDS beyond 64 KiB has to be allowed per kernel and device, once

@@ -116,3 +116,53 @@ def test_parts_are_added_in_fp64(case):
     C = hs.hs_gemm(to_dev(A, dt)[0], to_dev(Bm, dt)[0], dtype=dt, p=1, K=1, out=poisoned((m, n), torch.float32))
     torch.cuda.synchronize()
     assert np.array_equal(host(C), np.full((m, n), float(waves // 2)))
+
+
+def test_tiles_and_waves_that_the_kernel_has_sums_for():
+    """At most four waves share a 2 x 2 tile (eight a smaller or a 6-MFMA-tile one),
+    and LDS holds a set of sums for each, four of eight."""
+    g = inputs.rng(2025)
+    calls = []
+    for _ in range(1500):
+        m, n, k = (int(x) for x in np.exp(g.uniform(np.log(8), np.log((3000, 3000, 20000)))))
+        p = int(g.choice([1, 2, 8, 16]))
+        dt = str(g.choice(["f64", "f32", "bf16", "f16", "split3_bf16", "split2_f16", "fp8_e4m3", "fp8_e4m3_r1"]))
+        if dt.startswith("fp8"):
+            m, k = m + -m % (32 * p), k + -k % (64 * p)
+        calls.append(("gemm", m, n, k, B.DTYPES[dt], p, 1))
+    seen = set()
+    for c, r in zip(calls, launches(calls)):
+        assert r["status"] == 0, (c, r)
+        for x in r["launches"]:
+            if "wave_kernel" in x["kernel"]:
+                fam, form, tr, tc = (int(v) for v in x["kernel"].split("wave_kernelI")[1].split("EEE")[0][2:].split("ELi"))
+                kg = x["block"][0] // 64
+                assert kg <= (4 if tr * tc in (4, 8) else 8), (c, x)
+                set_bytes = tr * tc * (16 * 4 if fam else 4 * 8) * 64
+                assert x["lds"] == (0 if kg == 1 else min(kg, 4) * set_bytes), (c, x)
+                seen.add((fam, tr, tc, kg))
+    assert {(0, 2, 2, 4), (0, 1, 1, 8), (2, 3, 2, 8), (2, 2, 2, 1)} <= seen
+
+
+# FP64 on 32 x 32 tiles where there are few: 64 and more with long sums (planes and
+# none), 256 with short ones; last groups of 24 rows, 4 and 1 columns
+FEW = [(339, 230, 4115, 8, 1), (248, 1001, 4100, 1, 1), (512, 481, 200, 2, 2), (1000, 449, 4096, 4, 2)]
+
+
+def test_fp64_takes_wide_tiles():
+    for c, r in zip(FEW, launches([("gemm", m, n, k, B.HS_F64, p, K) for m, n, k, p, K in FEW])):
+        assert any("wave_kernelILi0ELi0ELi2ELi2E" in x["kernel"] for x in r["launches"]), (c, r)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", FEW)
+def test_fp64_wide_tiles(case):
+    if not gpu_available():
+        pytest.skip("no GPU")
+    m, n, k, p, K = case
+    A, A64 = to_dev(inputs.normal((m, k), seed=4600), "f64")
+    Bm, B64 = to_dev(inputs.normal((k, n), seed=4601), "f64")
+    note("fp64 wide tiles", case)
+    C = hs.hs_gemm(A, Bm, dtype="f64", p=p, K=K, out=poisoned((m, n), torch.float64))
+    torch.cuda.synchronize()
+    check(host(C), oracle.gemm(A64, B64), "f64", A64, B64, what="fp64 wide tiles %s" % (case,))
