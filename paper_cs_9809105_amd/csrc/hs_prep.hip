@@ -183,10 +183,11 @@ struct GroupAt {
     int64_t base;             // byte offset of the group
 };
 
-DEVI GroupAt group_at(const OperandGeom &g, uint32_t grp, uint32_t rr) {
-    const uint32_t GS = (uint32_t)g.GS, c = grp / GS, gi = grp - c * GS;
+DEVI GroupAt group_at(const PackArgs &a, uint32_t grp, uint32_t rr) {
+    const OperandGeom &g = a.g;
+    const uint32_t GS = (uint32_t)g.GS, c = fast_div(grp, a.by_GS), gi = grp - c * GS;
     const uint32_t at = gi * (uint32_t)g.grp_rows + rr;      // host: below 2^32
-    const uint32_t i = at / g.run;
+    const uint32_t i = fast_div(at, a.by_run);
     GroupAt r;
     r.row = (int64_t)(c + i * g.step) * g.run + (at - i * g.run);
     r.valid = i < g.runs && r.row < g.R;
@@ -404,6 +405,13 @@ __global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a, int a
     }
 }
 
+// t mod v.d, and t divided by it
+DEVI uint32_t pop(uint32_t &t, const FastDiv &v) {
+    const uint32_t q = fast_div(t, v), r = t - q * v.d;
+    t = q;
+    return r;
+}
+
 // An MN-major unit of pack_kernel's numbering: row rr of group grp, block
 // kb, chunk ch, plane half, and where its elements lie in the source.
 struct MnUnit {
@@ -413,18 +421,18 @@ struct MnUnit {
 };
 
 template <int KIND>
-DEVI MnUnit mn_decode(uint32_t u, const OperandGeom &g) {
+DEVI MnUnit mn_decode(uint32_t u, const PackArgs &a) {
     typedef PackTraits<KIND> T;
+    const OperandGeom &g = a.g;
     const int KC = g.chunk_bytes / T::ESZ;
-    const uint32_t UPR = (uint32_t)(g.chunk_bytes / 16), nch = (uint32_t)g.nch, p = (uint32_t)g.p;
-    const uint32_t gr = (uint32_t)g.grp_rows;
     MnUnit d;
     uint32_t t = u;
-    d.rr = t % gr;    t /= gr;
-    d.half = t % UPR; t /= UPR;
-    d.ch = t % nch;   t /= nch;
-    d.kb = t % p;
-    d.at = group_at(g, t / p, d.rr);
+    d.rr = pop(t, a.by_rows);
+    d.half = t & ((1u << a.upr_log) - 1);
+    t >>= a.upr_log;
+    d.ch = pop(t, a.by_nch);
+    d.kb = pop(t, a.by_p);
+    d.at = group_at(a, t, d.rr);
     d.kin0 = (int64_t)d.ch * KC + d.half * T::UE;
     d.kk0 = (int64_t)d.kb * g.S_k + d.kin0;
     return d;
@@ -456,7 +464,7 @@ DEVI void pack_mn_block(const PackArgs &a, uint32_t blk, void *lds) {
         const uint32_t u = base + i / PER * 256u + run * RW;     // units u .. u + RW - 1: rows rr .. of one group
         v[i].w = u32x4{0, 0, 0, 0};
         if (u < (uint32_t)a.total_units) {
-            const MnUnit d = mn_decode<KIND>(u, g);
+            const MnUnit d = mn_decode<KIND>(u, a);
             const int64_t kk = d.kk0 + e;
             if (d.at.valid && d.kin0 + e < g.S_k && kk < g.Kd) {
                 const S *q4 = src + kk * a.ld + d.at.row;
@@ -480,7 +488,7 @@ DEVI void pack_mn_block(const PackArgs &a, uint32_t blk, void *lds) {
     for (int b = 0; b < U; ++b) {
         const uint32_t u = base + b * 256u + threadIdx.x;
         if (u >= (uint32_t)a.total_units) return;
-        const MnUnit d = mn_decode<KIND>(u, g);
+        const MnUnit d = mn_decode<KIND>(u, a);
         float vals_f[UE];
         double vals_d[1] = {0.0};
         uint16_t vals_h[UE];
@@ -518,35 +526,28 @@ DEVI void unit_load(const PackArgs &a, uint32_t u, PackUnit<KIND> &x) {
     x.live = false;
     if (u >= (uint32_t)a.total_units) return;               // host: total_units < 2^32
     const int KC = g.chunk_bytes / T::ESZ;      // elements per chunk row
-    const uint32_t UPR = (uint32_t)(g.chunk_bytes / 16);  // 16-byte planes per chunk row
-    const uint32_t nch = (uint32_t)g.nch, p = (uint32_t)g.p, gr = (uint32_t)g.grp_rows;
-    uint32_t t = u, rr, half, ch, kb, grp;
+    uint32_t t = u, rr, half, ch, kb;
     if (KMAJOR) {
         // 8 x 8 blocks of (row, unit along the contraction): a wave reads 8
         // rows x 8 consecutive units (128-256 contiguous bytes per row) and
         // writes, per (chunk, plane), 8 consecutive rows (128 bytes).
-        const uint32_t nu = nch * UPR;                  // units along one block row
-        const uint32_t nkg = (nu + 7) / 8, nrg = (gr + 7) / 8;
+        const uint32_t nu = (uint32_t)g.nch << a.upr_log;      // units along one block row
         const uint32_t uu = t % 8;  t /= 8;
         const uint32_t rlo = t % 8; t /= 8;
-        const uint32_t kg = t % nkg; t /= nkg;
-        const uint32_t rhi = t % nrg; t /= nrg;
-        kb = t % p;
-        grp = t / p;
-        const uint32_t ku = kg * 8 + uu;
-        rr = rhi * 8 + rlo;
-        if (ku >= nu || rr >= gr) return;
-        ch = ku / UPR;
-        half = ku % UPR;
+        const uint32_t ku = pop(t, a.by_unit8) * 8 + uu;
+        rr = pop(t, a.by_row8) * 8 + rlo;
+        if (ku >= nu || rr >= (uint32_t)g.grp_rows) return;
+        ch = ku >> a.upr_log;
+        half = ku & ((1u << a.upr_log) - 1);
     } else {
-        rr = t % gr;    t /= gr;
-        half = t % UPR; t /= UPR;
-        ch = t % nch;   t /= nch;
-        kb = t % p;
-        grp = t / p;
+        rr = pop(t, a.by_rows);
+        half = t & ((1u << a.upr_log) - 1);
+        t >>= a.upr_log;
+        ch = pop(t, a.by_nch);
     }
+    kb = pop(t, a.by_p);
     x.live = true;
-    x.at = group_at(g, grp, rr);
+    x.at = group_at(a, t, rr);
     x.rr = rr; x.half = half; x.ch = ch; x.kb = kb;
     x.kin0 = (int64_t)ch * KC + half * T::UE;
     x.kk0 = (int64_t)kb * g.S_k + x.kin0;
