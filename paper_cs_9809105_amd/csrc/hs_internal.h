@@ -113,8 +113,7 @@ struct FastDiv {
     uint32_t d, m, s1, s2;
 };
 constexpr FastDiv fast_div_by(uint32_t d) {
-    uint32_t l = 0;
-    while (((uint64_t)1 << l) < d) ++l;
+    const uint32_t l = d > 1 ? 32 - (uint32_t)__builtin_clz(d - 1) : 0;
     const uint64_t m = (((((uint64_t)1 << l) - d) << 32) / d) + 1;
     return FastDiv{d, (uint32_t)m, l < 1 ? l : 1, l > 0 ? l - 1 : 0};
 }

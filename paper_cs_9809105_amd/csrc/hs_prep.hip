@@ -272,7 +272,8 @@ DEVI void pack_emit(const PackArgs &a, const GroupAt &at, uint32_t kb, uint32_t 
 // product through the values themselves.  Every source is read 16 bytes at a
 // time at whatever alignment its elements have (one element a load where rows
 // are not 16-byte aligned, whole calls of two-piece FP16: tn 4097 x 2049 x 8191 741
-// us, 575 here; 64 x 513 x 4097 105 and 42).
+// us, 575 here; 64 x 513 x 4097 105 and 42), the last columns of a row by reading its
+// last four again.
 //   K-major source: one wave per row.
 //   MN-major source (element (kk, c) of the float view at src[kk ld + c]): a
 //   workgroup owns 32 float columns (one 128-byte line) over all contraction
@@ -316,7 +317,8 @@ DEVI void row_amax_one(const RowAmaxArgs &a, uint32_t blk, float (&red)[64][AMAX
     const int64_t ncol = amax_ncol(a), nk = amax_nk(a);
     const int64_t c0 = (int64_t)blk * AMAX_COLS;
     constexpr int LANES = AMAX_COLS / 4, ROWS = 512 / LANES;   // threads per row, 4 columns each
-    const int64_t c = c0 + (tid % LANES) * 4;
+    int64_t c = c0 + (tid % LANES) * 4;
+    if (c < ncol && c + 3 >= ncol && ncol - 4 >= c0) c = ncol - 4;     // the block's last columns again
     const int r0 = tid / LANES;
     float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
     if (c + 3 < ncol) {
@@ -337,7 +339,7 @@ DEVI void row_amax_one(const RowAmaxArgs &a, uint32_t blk, float (&red)[64][AMAX
             if (c + 2 < ncol) m2 = fmaxf(m2, fabsf(q[2]));
         }
     }
-    float *d = &red[r0][(tid % LANES) * 4];
+    float *d = &red[r0][c - c0];
     d[0] = m0; d[1] = m1; d[2] = m2; d[3] = m3;
     __syncthreads();
     if (tid >= AMAX_COLS || c0 + tid >= ncol) return;
@@ -362,20 +364,19 @@ __global__ __launch_bounds__(512) void row_amax_kernel(AmaxPair p) {
     else row_amax_one<KB>(p.x[1], blockIdx.x - p.nb0, red);
 }
 
-// The same by slabs of 256 contraction rows (where launch_row_amax says): 4
-// columns per thread, a workgroup's four waves side by side (`across`) or one
-// below the other with 64 rows each, then one atomic max per
-// column into its row (two for EMB_BLOCKS) of the zero-filled amax.  Workgroup b
-// takes column block b % ncb of slab b / ncb.
-__global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a, int across) {
+// The same by slabs (where launch_row_amax says): a workgroup takes 1024 columns,
+// 4 per thread, of 256 contraction rows, then one atomic max per column into its
+// row (two for EMB_BLOCKS) of the zero-filled amax.  Workgroup b takes column
+// block b % ncb of slab b / ncb.  (Fewer columns and the threads below one another
+// multiply the atomics: 64 x 32 x 524288, the call, 1044 us; waves below one another
+// 1315, quarter waves 2432.)
+__global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a) {
     const int64_t ncol = amax_ncol(a), nk = amax_nk(a);
-    const int width = across ? 1024 : 256, t = across ? threadIdx.x : threadIdx.x & 63;
-    const int64_t ncb = (ncol + width - 1) / width;
-    const int64_t c = (int64_t)(blockIdx.x % ncb) * width + t * 4;
+    const int64_t ncb = (ncol + 1023) / 1024;
+    int64_t c = (int64_t)(blockIdx.x % ncb) * 1024 + threadIdx.x * 4;
     if (c >= ncol) return;
-    const int rows = across ? 256 : 64;
-    const int64_t k0 = (int64_t)(blockIdx.x / ncb) * 256 + (across ? 0 : (threadIdx.x >> 6) * 64);
-    const int64_t k1 = k0 + rows < nk ? k0 + rows : nk;
+    if (c + 3 >= ncol && ncol >= 4) c = ncol - 4;          // the last columns again: a maximum does not mind
+    const int64_t k0 = (int64_t)(blockIdx.x / ncb) * 256, k1 = k0 + 256 < nk ? k0 + 256 : nk;
     float m[4] = {0.f, 0.f, 0.f, 0.f};
     if (c + 3 < ncol) {
 #pragma unroll 8
@@ -387,6 +388,7 @@ __global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a, int a
             m[3] = fmaxf(m[3], fabsf(v.w));
         }
     } else {
+#pragma unroll 8
         for (int64_t kk = k0; kk < k1; ++kk)
 #pragma unroll
             for (int j = 0; j < 3; ++j)
@@ -750,13 +752,11 @@ hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t l
 // memory-side cache: there long stretches of a row are read faster, and of rows
 // that do not start on 128-byte lines each line between two workgroups' columns
 // would be read twice.  Whole calls with m = 64, n x k (slabs / columns), us:
-// 33 x 65537 159 / 401, 512 x 131072 527 / 733, 2048 x 32768 283 / 331, but 32 x 8192
-// 32 / 27, 2048 x 8192 72 / 67, 32 x 16384 46 / 42; 10240 x 10240 393 / 418, 16384 x 16384
-// 931 / 945, 16384 x 4096 270 / 273, but 16384 x 2048 151 / 144; 8191 x 16385 641 / 852,
-// 16383 x 4097 338 / 364, but 16383 x 3001 274 / 272.  Waves side by side for whole
-// lines (16384 x 16384 931, one below the other 945), else one below the other
-// (16383 x 8193 612, side by side 696).  Of complex sources on whole lines the slabs'
-// atomics, two per column, cost what they save: 4096 x 8192 558 / 548.
+// 33 x 65537 111 / 401, 512 x 131072 420 / 724, 1000 x 16384 71 / 82, 32 x 16384 40.5 /
+// 41.3, but 2048 x 8192 67 / 62; 10240 x 10240 379 / 402, 16384 x 16384 914 / 929, but
+// 16384 x 2048 147 / 140; unaligned 8191 x 16385 586 / 630, 16383 x 4097 304 / 317.
+// Of complex sources on whole lines the slabs' atomics, two per column, cost what
+// they save: 4096 x 8192 558 / 548.
 hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream_t st) {
     if (!a.kmajor && b.kmajor) return hipErrorInvalidValue;    // no product reads its operands so
     AmaxPair p{};
@@ -782,9 +782,8 @@ hipError_t launch_row_amax(const RowAmaxArgs &a, const RowAmaxArgs &b, hipStream
         }
         hipError_t e = launch_fill_zero(0, x.amax, 1, x.R, x.R, st);   // zero bits = 0.0f
         if (e != hipSuccess) return e;
-        const int across = ncol >= 1024 && lines, width = across ? 1024 : 256;
-        const int64_t ncb = (ncol + width - 1) / width;
-        hipLaunchKernelGGL(row_amax_slab_kernel, dim3((unsigned)(ncb * ((nk + 255) / 256))), dim3(256), 0, st, x, across);
+        const int64_t ncb = (ncol + 1023) / 1024;
+        hipLaunchKernelGGL(row_amax_slab_kernel, dim3((unsigned)(ncb * ((nk + 255) / 256))), dim3(256), 0, st, x);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
