@@ -558,10 +558,14 @@ hs_status check_ws(const Plan &P, const void *ws, size_t ws_bytes) {
 }  // namespace
 
 // The n-body call's launch shape and workspace.  A workgroup's ss waves split
-// the travelling bodies: 8 (n = 262144, p = 64, K = 8: 18.1 ms; 18.7 with 16),
-// or 16 where there are fewer than 1024 workgroups (n = 10000, p = 8, K = 1,
-// 160 workgroups: 68 us; 79 with 8), and fewer where a wave would get under 16
-// bodies.
+// the travelling bodies: 8 (n = 262144, p = 64, K = 8: 18.1 ms; 18.7 with 16; n =
+// 16384 88 us, 90), or 16 where there are fewer than 1024 workgroups (n = 10000,
+// p = 8, K = 1, 160 workgroups: 67 us; 82 with 8; n = 3000, p = 16, K = 4, 192: 13.2,
+// 13.7), and fewer where a wave would get under 16 bodies (n = 2000, p = K = 16: 13.0
+// with 4, 14.2 with 16).  From 2048 workgroups on a wave gets 96 at least: there
+// the chip is full, and many replicas leave few travelling bodies to split (n =
+// 61253, p = K = 256: 1197 us with 2, 1613 with 8; n = 16384, p = K = 64: 108, 128;
+// n = 8000, p = K = 32: 39.6, 43.0).
 hs_status nbody_plan(int64_t n, int dtype, hs_schedule s, double eps2, NbodyArgs *a, size_t *ws) {
     if (dtype != HS_F32 && dtype != HS_F64) return HS_ERR_NOT_SUPPORTED;
     hs_schedule r;
@@ -584,7 +588,8 @@ hs_status nbody_plan(int64_t n, int dtype, hs_schedule s, double eps2, NbodyArgs
     a->sub = (int)ceil_div(a->S, 64);
     const int64_t gx = (int64_t)a->sub * r.K;         // times 64: at most n + 64 K, below 2^32 threads
     a->ss = gx * r.p < 1024 ? 16 : 8;
-    while (a->ss > 1 && ((int64_t)a->Kt * a->S < 16 * a->ss || gx * 64 * a->ss >> 32)) a->ss /= 2;
+    const int least = gx * r.p < 2048 ? 16 : 96;
+    while (a->ss > 1 && ((int64_t)a->Kt * a->S < least * a->ss || gx * 64 * a->ss >> 32)) a->ss /= 2;
     const size_t esz = f64 ? 8 : 4;
     *ws = r.K > 1 ? align_up((size_t)r.K * (size_t)n * 4 * esz) : 0;
     return HS_OK;
