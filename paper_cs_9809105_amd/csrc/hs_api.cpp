@@ -764,6 +764,11 @@ hs_status hs_gemv(int64_t m, int64_t n, int dtype, hs_schedule s,
     // 5.3 against 7.6; but 2500 x 5000 10.2 against 8.9)
     const int64_t row_bytes = n * (int64_t)esz;
     g.waves = m < 400 && row_bytes >= 24 * 1024 ? 4 : row_bytes >= 48 * 1024 ? 2 : 1;
+    // sixteen lanes a row, four rows a wave, for many short rows: a wave's sums
+    // across its lanes then serve four (400000 x 122 FP32 48 us against 164 with 64
+    // lanes, 100000 x 500 30, 49, 16384 x 1500 16.5, 18.8; but 32768 x 3000 63, 57, and
+    // 2000 x 1500 4.7, 4.5; FP64 100000 x 122 18, 36, 32768 x 1000 38, 38)
+    g.lanes = m >= 8192 && row_bytes <= 6 * 1024 ? 16 : 64;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (g_prof && !timing_events(&ev0, &ev1)) return HS_ERR_LAUNCH_FAILED;
     hipError_t e = launch_gemv(f64, g, st);

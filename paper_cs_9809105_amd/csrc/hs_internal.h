@@ -235,7 +235,8 @@ struct GemvArgs {
     void *y;
     int64_t m, n;
     int cplx;                // 1: complex64 A, x, y (lda in complex elements)
-    int waves;               // waves per row: 1 (4 rows per workgroup) or 4
+    int waves;               // waves per row: 1, 2 or 4
+    int lanes;               // lanes per row of one wave: 64, or 16 (waves 1)
 };
 
 // All-pairs n-body interaction on the two-array recipe (hs_nbody.hip).

@@ -598,18 +598,42 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(OT *Cout, int64_t M, int
 // and 4.4, but 5000 x 10000 44.5 against 35.5 here, for its index arithmetic.
 // CX: complex64 (VE complex elements per load).  NT: A is read past the caches
 // (it is larger than they are, by a fifth: launch_gemv_t).
-template <typename T, int CX, int NT>
+// L: lanes of a row.  16 where rows are many and short (hs_gemv): a wave then takes
+// four of them, whose sums across lanes cost what one row's do.
+template <int CTRL>
+DEVI double dpp(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// The sum over each L = 16 or 64 lanes, in every lane.
+template <int L>
+DEVI double lanes_sum(double v) {
+    v += dpp<0xB1>(v);                         // quad_perm 1, 0, 3, 2
+    v += dpp<0x4E>(v);                         // quad_perm 2, 3, 0, 1
+    v += dpp<0x141>(v);                        // row_half_mirror
+    v += dpp<0x140>(v);                        // row_mirror
+    if constexpr (L == 64) {
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+    }
+    return v;
+}
+
+template <typename T, int CX, int NT, int L>
 __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs a) {
     constexpr int VE = 16 / (int)(sizeof(T) * (1 + CX)), U = 4, NT4 = VE * (1 + CX);
     typedef T V __attribute__((ext_vector_type(VE * (1 + CX))));
     typedef V VU __attribute__((aligned(sizeof(T) * (1 + CX))));
     __shared__ double red[4][2];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int W = a.waves, part = wave & (W - 1);   // W a power of two: 4 / W rows per workgroup
-    const int64_t row = ((int64_t)blockIdx.x * 4 + wave) / W;
-    const int64_t n = row < a.m ? a.n : 0;
-    const int start = (part * 64 + lane) * VE, stride = 64 * W * VE;
-    const T *Ar = (const T *)a.A + row * a.lda * (1 + CX);
+    const int lane = threadIdx.x & (L - 1), wave = threadIdx.x >> 6;
+    const int W = L == 64 ? a.waves : 1, part = wave & (W - 1);   // W a power of two: 256 / (L W) rows per workgroup
+    const int64_t row = ((int64_t)blockIdx.x * (256 / L) + threadIdx.x / L) / W;
+    // past the last row: nothing to read, or (beside other rows of the wave) the last
+    // row again; never stored
+    const int64_t n = L < 64 || row < a.m ? a.n : 0;
+    const int start = (part * L + lane) * VE, stride = L * W * VE;
+    const T *Ar = (const T *)a.A + (L == 64 || row < a.m ? row : a.m - 1) * a.lda * (1 + CX);
     const T *x = (const T *)a.x;
     double Sr = 0.0, Si = 0.0;
     auto multiply = [&](const V (&av)[U], const V (&xv)[U]) {
@@ -681,11 +705,8 @@ __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs a) {
         }
     }
     multiply(a0, x0);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        Sr += __shfl_xor(Sr, m, 64);
-        if constexpr (CX) Si += __shfl_xor(Si, m, 64);
-    }
+    Sr = lanes_sum<L>(Sr);
+    if constexpr (CX) Si = lanes_sum<L>(Si);
     if (W > 1) {                               // the row's waves
         if (lane == 0) {
             red[wave][0] = Sr;
@@ -830,7 +851,8 @@ hipError_t launch_fill_zero(int f64, void *Cout, int64_t M, int64_t N, int64_t l
 
 template <typename T, int CX>
 static hipError_t launch_gemv_t(const GemvArgs &a, hipStream_t st) {
-    const dim3 grid((unsigned)((a.m * a.waves + 3) / 4));
+    const int rows = 256 / (a.lanes * a.waves);           // per workgroup; at least one
+    const dim3 grid((unsigned)((a.m + rows - 1) / rows));
     // Reads past the caches: matrices not read just before take less time (FP32,
     // two in turn, 8192 x 8192 42.9 us a call against 46.5, 8192 x 9728 50.9 against
     // 56.0), but the same one over and over, as in an iterative solver, takes more
@@ -838,10 +860,11 @@ static hipError_t launch_gemv_t(const GemvArgs &a, hipStream_t st) {
     // against 38.8, 280 MiB 46.5 against 44.0, 288 MiB 46.6 against 45.8 (FP64 48.8,
     // 47.5; complex 49.8, 48.2).  From 304 MiB on that is the faster one too: FP32
     // 49.5 against 51.9, FP64 50.9 against 52.9, FP32 12288 x 12288 94 against 101.
-    if (a.m * a.n * (int64_t)(sizeof(T) * (1 + CX)) >= (int64_t)304 << 20)
-        HS_LAUNCH_TIMED((gemv_kernel<T, CX, 1>), grid, dim3(256), 0, st, a);
-    else
-        HS_LAUNCH_TIMED((gemv_kernel<T, CX, 0>), grid, dim3(256), 0, st, a);
+    const bool past = a.m * a.n * (int64_t)(sizeof(T) * (1 + CX)) >= (int64_t)304 << 20;
+    if (a.lanes == 64 && past) HS_LAUNCH_TIMED((gemv_kernel<T, CX, 1, 64>), grid, dim3(256), 0, st, a);
+    else if (a.lanes == 64) HS_LAUNCH_TIMED((gemv_kernel<T, CX, 0, 64>), grid, dim3(256), 0, st, a);
+    else if (past) HS_LAUNCH_TIMED((gemv_kernel<T, CX, 1, 16>), grid, dim3(256), 0, st, a);
+    else HS_LAUNCH_TIMED((gemv_kernel<T, CX, 0, 16>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
