@@ -374,11 +374,17 @@ __global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a) {
     const int64_t ncol = amax_ncol(a), nk = amax_nk(a);
     const int64_t ncb = (ncol + 1023) / 1024;
     int64_t c = (int64_t)(blockIdx.x % ncb) * 1024 + threadIdx.x * 4;
-    if (c >= ncol) return;
-    if (c + 3 >= ncol && ncol >= 4) c = ncol - 4;          // the last columns again: a maximum does not mind
     const int64_t k0 = (int64_t)(blockIdx.x / ncb) * 256, k1 = k0 + 256 < nk ? k0 + 256 : nk;
     float m[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c + 3 < ncol) {
+    if (ncol < 4) {                                        // fewer than 16 bytes: a thread per row
+        const int64_t kk = k0 + threadIdx.x;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) m[j] = wave_max(kk < k1 && j < ncol ? fabsf(a.src[kk * a.ld + j]) : 0.f);
+        if (threadIdx.x & 63) return;
+        c = 0;
+    } else {
+        if (c >= ncol) return;
+        if (c + 3 >= ncol) c = ncol - 4;                   // the last columns again: a maximum does not mind
 #pragma unroll 8
         for (int64_t kk = k0; kk < k1; ++kk) {
             const float4 v = load4(a.src + kk * a.ld + c);
@@ -387,12 +393,6 @@ __global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a) {
             m[2] = fmaxf(m[2], fabsf(v.z));
             m[3] = fmaxf(m[3], fabsf(v.w));
         }
-    } else {
-#pragma unroll 8
-        for (int64_t kk = k0; kk < k1; ++kk)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                if (c + j < ncol) m[j] = fmaxf(m[j], fabsf(a.src[kk * a.ld + c + j]));
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

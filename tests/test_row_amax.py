@@ -16,7 +16,7 @@ if gpu_available():
 # of 32 columns and one past it, one wave's 256 elements and one past them, and
 # over 8192 rows on one, five and more than 1024 columns (two blocks side by side)
 CASES = [(5, 1, 1), (9, 2, 2), (33, 3, 3), (31, 32, 70), (7, 33, 255), (18, 34, 256), (8, 35, 257), (70, 129, 131),
-         (3, 33, 8193), (33, 130, 8195), (66, 36, 4100), (2, 1026, 8200), (2, 1055, 8193), (2, 3, 8200), (3, 37, 90)]
+         (3, 33, 8193), (33, 130, 8195), (66, 36, 4100), (2, 1026, 8200), (2, 1055, 8193), (2, 3, 8200), (1, 5, 8449), (3, 37, 90)]
 
 
 def _spiked(rows, k, seed):
