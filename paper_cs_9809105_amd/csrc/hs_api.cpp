@@ -184,10 +184,11 @@ int wave_percent(const FormInfo &f, int tr) {
 // A wave of the FP32 and FP64 forms spends 64 cycles on the MFMA of two cheap
 // fragments: small tiles, 4 waves (FP32 2048^3: 139 with 4 waves, 193 with 2,
 // 250 with 1, since workgroups of one or two waves share SIMDs while others
-// idle), one wave from 8192 tiles on.  Of these 2 x 2 tiles two workgroups
-// fit a CU (LDS): taken from 900 tiles, and for FP32, where they gain little
-// (2048^3, 1024 tiles: 134 against 140) only if 512 at a time fill nine tenths
-// of the rounds (1800 x 2200 x 1000, 1050 tiles: 91 against 72).  FP64 takes them
+// idle), one wave from 8192 tiles on (FP64 3000 x 3000 x 256, 8836 tiles: 88, 105
+// with 4; FP32 3000 x 2816 x 1000, 8272: 159, 160; but 2720 x 2880 x 1000, 7650: 195,
+// 159).  Of these 2 x 2 tiles two workgroups fit a CU (LDS): taken from 900 tiles,
+// and for FP32, where they gain little (2048^3, 1024 tiles: 134 against 140) only if
+// 512 at a time fill nine tenths of the rounds (1800 x 2200 x 1000, 1050 tiles: 91 against 72).  FP64 takes them
 // where they fill the rounds, or there are 64 with long sums, and little of them
 // is padding: whole calls (2 x 2 / 1 x 1, and the LDS-tiled kernel), 1008 x 448 x
 // 15616, 448 tiles, 316 / 550, 433; 64 x 8192 x 8192, 512, 406 / 538, 411; 512^3, 256,
@@ -199,7 +200,9 @@ int wave_percent(const FormInfo &f, int tr) {
 // 9.1; below, 256 x 512 x 2048, 64 tiles, refined FP8 8.6 against 6.9) with only
 // as many waves as fill the SIMDs (BF16 2500^3, 1600 tiles: 53 with one wave,
 // 64 with 4; 1500^3, 576: 25, 22 with 2, 24; the split forms with their longer
-// chunks take 4 until 1024: split-BF16 1500^3 54 against 66 with 2).
+// chunks take 4 until 1024: split-BF16 1500^3 54 against 66 with 2).  1 x 1 tiles
+// have 4 waves, 2 from 768 on (BF16 896 x 896 x 2048, 784: 23.2, 24.9 with 4; 640 x
+// 640 x 2048, 400: 19.3, 18.0; between, where 2 can be the faster, 4 sum more exactly).
 // Just past 256 tiles of 2 x 2 a few CUs would run two rounds: where 3 x 2 ones
 // are at most 256, the 16-bit forms take these with 8 waves (1100 x 900 x 1000,
 // 270 tiles against 180: split-BF16 28.4 to 23.0, two-piece FP16 20.4 to 17.4,

@@ -94,7 +94,7 @@ struct OperandGeom {
     int p;
     int64_t S_k;      // contraction block length -- ceil(Kd / p)
     int64_t nch;      // chunks per block (padded)
-    int chunk_bytes;  // 32 (f64, f32, 16-bit) or 64 (fp8)
+    int chunk_bytes;  // 32 (f32, 16-bit) or 64 (fp8, f64)
     int pieces;       // planes written
     int64_t row_bytes;    // one piece of one row: p blocks x nch chunks x chunk_bytes
     int64_t piece_bytes;  // one piece of one group of grp_rows rows

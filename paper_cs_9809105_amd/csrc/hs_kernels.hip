@@ -16,8 +16,9 @@
 //                    accumulator that never leaves the registers.
 //   backshift_kernel the collector of the all-pairs interaction (hs_nbody):
 //                    sums K partial planes in FP64, fixed order.
-//   gemv_kernel      y = A x, collector form: one wave (or two, four) owns a
-//                    row and sums its K partial dot products in FP64.
+//   gemv_kernel      y = A x: one wave (or two, four, or a quarter of one)
+//                    sweeps a row once, its FP32 sums of 16 products added
+//                    in FP64.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -585,21 +586,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(OT *Cout, int64_t M, int
 // ---------------------------------------------------------------------------
 // matrix-vector product
 // ---------------------------------------------------------------------------
-// y = A x.  Every block product of the schedule belongs to one row, and the
-// collector adds all K partials of a row in the wave (or the W = 2, 4 waves) that
-// owns it, so the blocks are visited in storage order: one contiguous sweep over
-// the row, VE elements per lane and load (16 bytes, at any element alignment), U
-// loads in flight while the U before them are multiplied.  Each group's FP32 sum
-// (16 products) goes into an FP64 sum, and the lanes' FP64 sums are added at the
-// end.  Bound by reading A once: FP32 8192 x 8192 42.5 us (6.3 TB/s), 3001 x 2999
-// (rows at any alignment) 7.0, 500 x 500 3.9.  Walking the blocks partial by
-// partial in the order of base A, with a cross-lane sum after each, took 46.0, 11.0
-// and (p = 64, K = 8) 45 us; the same walk as one pipelined sequence 42.5, 10.7
-// and 4.4, but 5000 x 10000 44.5 against 35.5 here, for its index arithmetic.
-// CX: complex64 (VE complex elements per load).  NT: A is read past the caches
-// (it is larger than they are, by a fifth: launch_gemv_t).
-// L: lanes of a row.  16 where rows are many and short (hs_gemv): a wave then takes
-// four of them, whose sums across lanes cost what one row's do.
+// A value moved within its row of 16 lanes (DPP).
 template <int CTRL>
 DEVI double dpp(double v) {
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
@@ -620,6 +607,22 @@ DEVI double lanes_sum(double v) {
     return v;
 }
 
+// y = A x.  Every block product of the schedule belongs to one row, and the
+// collector adds all K partials of a row in the wave (or the W = 2, 4 waves, or the
+// 16 lanes) that owns it, so the blocks are visited in storage order: one contiguous
+// sweep over the row, VE elements per lane and load (16 bytes, at any element
+// alignment), U loads in flight while the U before them are multiplied.  Each
+// group's FP32 sum (16 products) goes into an FP64 sum, and the lanes' FP64 sums are
+// added at the end.  Bound by reading A once: FP32 8192 x 8192 39.0 us the same one
+// over and over (6.9 TB/s), 46.2 others in turn (8192 x 9728, past the caches, 49.5
+// and 50.9), 3001 x 2999 (rows at any alignment) 7.0, 500 x 500 3.9.  Walking the blocks partial by
+// partial in the order of base A, with a cross-lane sum after each, took 39.9 and
+// 47.1, 11.0 and (p = 64, K = 8) 45 us; the same walk as one pipelined sequence
+// 10.7 and 4.4, but 5000 x 10000 44.5 against 35.5 here, for its index arithmetic.
+// CX: complex64 (VE complex elements per load).  NT: A is read past the caches
+// (it is larger than they are, by a fifth: launch_gemv_t).
+// L: lanes of a row.  16 where rows are many and short (hs_gemv): a wave then takes
+// four of them, whose sums across lanes cost what one row's do.
 template <typename T, int CX, int NT, int L>
 __global__ __launch_bounds__(256) void gemv_kernel(GemvArgs a) {
     constexpr int VE = 16 / (int)(sizeof(T) * (1 + CX)), U = 4, NT4 = VE * (1 + CX);

@@ -31,9 +31,9 @@ DEVI int row_scale_exp(uint32_t amax_bits) { return 15 - __builtin_amdgcn_frexp_
 // f16 pieces of the row-scaled operands, the three products a_i b_j with
 // i + j <= 1, smallest first; the epilogue removes the row scales.
 template <int FORM> struct Form;
-template <> struct Form<0> { static const int NP = 1; static const int NPROD = 1; };
-template <> struct Form<1> { static const int NP = 3; static const int NPROD = 6; };
-template <> struct Form<2> { static const int NP = 2; static const int NPROD = 3; };
+template <> struct Form<0> { static const int NP = 1; };
+template <> struct Form<1> { static const int NP = 3; };
+template <> struct Form<2> { static const int NP = 2; };
 
 template <int FAM> struct Mfma;
 template <> struct Mfma<FAM_F64> { static const int T = 16; typedef f64x4 Acc; };

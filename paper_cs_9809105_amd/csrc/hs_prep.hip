@@ -64,7 +64,7 @@ DEVI int fp8_exponent(float amax) {
 }
 
 // ---------------------------------------------------------------------------
-// pack
+// FP8 tile exponents
 // ---------------------------------------------------------------------------
 // One workgroup per 128 x 128 scale tile: amax of the tile, then (with
 // refinement) amax of the residuals a 2^e - q0, both turned into exponents.
@@ -151,6 +151,9 @@ __global__ __launch_bounds__(512) void fp8_tile_exp_kernel(ExpPair p) {
     else fp8_tile_exp(p.x[1], blockIdx.x - p.nb0, red);
 }
 
+// ---------------------------------------------------------------------------
+// pack: one unit
+// ---------------------------------------------------------------------------
 // Eight floats of one row -> the 16-byte units of their two FP16 pieces,
 // x' = x 2^e, a0 = f16(x'), a1 = f16(x' - a0): round to nearest even, the
 // residual exact in FP32 (a0 is within a factor 2 of x', or both lie below
@@ -407,6 +410,9 @@ __global__ __launch_bounds__(256) void row_amax_slab_kernel(RowAmaxArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// pack: the kernel
+// ---------------------------------------------------------------------------
 // t mod v.d, and t divided by it
 DEVI uint32_t pop(uint32_t &t, const FastDiv &v) {
     const uint32_t q = fast_div(t, v), r = t - q * v.d;
