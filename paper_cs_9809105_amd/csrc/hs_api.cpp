@@ -444,10 +444,9 @@ PackArgs pack_args(const Plan &P, const Operand &X, const OperandGeom &g, void *
     a.exps = exps; a.exp_tiles_k = P.tiles_k; a.refine = P.f.form;
     a.embed = X.embed;
     const uint32_t upr = (uint32_t)(g.chunk_bytes / 16), units = (uint32_t)g.nch * upr;
-    a.by_rows = fast_div_by((uint32_t)g.grp_rows);
-    a.by_row8 = fast_div_by((uint32_t)(g.grp_rows + 7) / 8);
-    a.by_nch = fast_div_by((uint32_t)g.nch);
-    a.by_unit8 = fast_div_by((units + 7) / 8);
+    const bool blocks = a.mode == PACK_K;
+    a.by_rows = fast_div_by(blocks ? (uint32_t)(g.grp_rows + 7) / 8 : (uint32_t)g.grp_rows);
+    a.by_chunks = fast_div_by(blocks ? (units + 7) / 8 : (uint32_t)g.nch);
     a.by_p = fast_div_by((uint32_t)g.p);
     a.by_GS = fast_div_by((uint32_t)g.GS);
     a.by_run = fast_div_by(g.run);

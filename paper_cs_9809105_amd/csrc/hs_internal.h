@@ -104,22 +104,23 @@ struct OperandGeom {
 // Exact division of any 32-bit n by a constant d >= 1 that the host prepares
 // (T. Granlund and P. Montgomery, Division by Invariant Integers using
 // Multiplication, 1994): with 2^(l-1) < d <= 2^l, m = floor(2^32 (2^l - d) / d) + 1,
-// t = high word of m n, n / d = (t + ((n - t) >> s1)) >> s2, s1 = min(l, 1), s2 =
-// max(l - 1, 0).  A pack unit's place takes seven such divisions, 5 instructions
-// each against about 25 for a division by a kernel argument (the pack kernel of
-// 16384 x 16384 FP32 read across its rows: plain FP8 395 us to 253, two-piece FP16
-// 502 to 401, refined FP8 378 to 297).
+// t = high word of m n, s1 = min(l, 1), n / d = (t + ((n - t) >> s1)) >> (l - s1).
+// A pack unit's place takes five such divisions, 5 instructions each against about
+// 25 for a division by a kernel argument (the pack kernel of 16384 x 16384 FP32
+// read across its rows: plain FP8 395 us to 253, two-piece FP16 502 to 401, refined
+// FP8 378 to 297).
 struct FastDiv {
-    uint32_t d, m, s1, s2;
+    uint32_t d, m, l;
 };
 constexpr FastDiv fast_div_by(uint32_t d) {
     const uint32_t l = d > 1 ? 32 - (uint32_t)__builtin_clz(d - 1) : 0;
+    if ((d & (d - 1)) == 0) return FastDiv{d, 1, l};
     const uint64_t m = (((((uint64_t)1 << l) - d) << 32) / d) + 1;
-    return FastDiv{d, (uint32_t)m, l < 1 ? l : 1, l > 0 ? l - 1 : 0};
+    return FastDiv{d, (uint32_t)m, l};
 }
 constexpr uint32_t fast_div(uint32_t n, const FastDiv &v) {
-    const uint32_t t = (uint32_t)(((uint64_t)v.m * n) >> 32);
-    return (t + ((n - t) >> v.s1)) >> v.s2;
+    const uint32_t t = (uint32_t)(((uint64_t)v.m * n) >> 32), s1 = v.l < 1 ? v.l : 1;
+    return (t + ((n - t) >> s1)) >> (v.l - s1);
 }
 
 // How a source is read: along the contraction, across it element by element,
@@ -139,9 +140,10 @@ struct PackArgs {
     int refine;              // fp8 only: write q1 as the second piece
     int embed;               // complex sources (interleaved re, im; ld in
                              // floats), see PackEmbed
-    // divisors of the unit numbering: rows and 8-row blocks of a group, chunks and
-    // 8-unit runs of a contraction block, blocks, groups of a list, its run
-    FastDiv by_rows, by_row8, by_nch, by_unit8, by_p, by_GS, by_run;
+    // divisors of the unit numbering: rows of a group (PACK_K: its 8-row blocks),
+    // chunks of a contraction block (PACK_K: its 8-unit runs), blocks, groups of a
+    // list, its run
+    FastDiv by_rows, by_chunks, by_p, by_GS, by_run;
     uint32_t upr_log;        // log2 of the 16-byte units per chunk row
 };
 

@@ -438,7 +438,7 @@ DEVI MnUnit mn_decode(uint32_t u, const PackArgs &a) {
     d.rr = pop(t, a.by_rows);
     d.half = t & ((1u << a.upr_log) - 1);
     t >>= a.upr_log;
-    d.ch = pop(t, a.by_nch);
+    d.ch = pop(t, a.by_chunks);
     d.kb = pop(t, a.by_p);
     d.at = group_at(a, t, d.rr);
     d.kin0 = (int64_t)d.ch * KC + d.half * T::UE;
@@ -542,8 +542,8 @@ DEVI void unit_load(const PackArgs &a, uint32_t u, PackUnit<KIND> &x) {
         const uint32_t nu = (uint32_t)g.nch << a.upr_log;      // units along one block row
         const uint32_t uu = t % 8;  t /= 8;
         const uint32_t rlo = t % 8; t /= 8;
-        const uint32_t ku = pop(t, a.by_unit8) * 8 + uu;
-        rr = pop(t, a.by_row8) * 8 + rlo;
+        const uint32_t ku = pop(t, a.by_chunks) * 8 + uu;
+        rr = pop(t, a.by_rows) * 8 + rlo;
         if (ku >= nu || rr >= (uint32_t)g.grp_rows) return;
         ch = ku >> a.upr_log;
         half = ku & ((1u << a.upr_log) - 1);
@@ -551,7 +551,7 @@ DEVI void unit_load(const PackArgs &a, uint32_t u, PackUnit<KIND> &x) {
         rr = pop(t, a.by_rows);
         half = t & ((1u << a.upr_log) - 1);
         t >>= a.upr_log;
-        ch = pop(t, a.by_nch);
+        ch = pop(t, a.by_chunks);
     }
     kb = pop(t, a.by_p);
     x.live = true;
